@@ -164,7 +164,8 @@ cb_status coulomb_forces(int64_t n, const double* x, const double* y, const doub
  * ion); larger n returns CB_ENOWS.  The configured Newton's-third-law stage
  * runs when its tiles fit in the array (up to about 32768 ions: the result
  * is then bitwise that of coulomb_forces), otherwise the all-pairs kernel
- * with as many j-splits as fit (the same forces up to summation order).
+ * with as many j-splits as fit (the same forces up to summation order; small
+ * n takes the one-launch evaluation of coulomb_forces and no scratch).
  * Every call on one GPU shares that GPU's array: calls that overlap in time
  * on one GPU (other streams, other threads) race and give undefined results;
  * calls ordered on one stream are safe.  Nothing in the array needs to start
@@ -243,19 +244,23 @@ cb_status md_step(int64_t n, const cb_state* s, const double* q, const double* m
  * hold a_0.  When energies is non-NULL (device, [nrun][nsteps/every + 1][4])
  * it receives (K, U_C, U_trap, K + U_C + U_trap) of steps 0, every, 2 every,
  * ..., for each run; every >= 1 then.
- * nrun = 1 runs the multi-workgroup step kernels (any n).  nrun > 1 needs
- * every run to hold at most 4096 ions (CB_EUNSUPPORTED otherwise) and takes
- * one of two ensemble paths (configuration key CB_OP_MD_ENSEMBLE):
+ * nrun = 1 runs the multi-workgroup step kernels (any n): one launch per
+ * step for small runs, each workgroup evaluating whole rows of the pair sum
+ * (algorithm 3 of cb_get_config), else a pair stage and an element-wise
+ * launch.  nrun > 1 needs every run to hold at most 4096 ions
+ * (CB_EUNSUPPORTED otherwise) and takes, when its entry (configuration key
+ * CB_OP_MD_ENSEMBLE) is forced or tuned, one of two ensemble paths:
  *  - algorithm 0: one persistent launch, one workgroup per run at a time,
  *    positions in LDS, runs taken largest first;
  *  - algorithm 2: per step, one launch of the Newton's-third-law pair tiles
  *    of every run and one launch that finishes the forces and applies the
  *    kick and drift (p i-particles per lane, j-segment length JL).
- * Without a forced or tuned entry the path with the smaller estimated step
- * time is taken (algorithm 0 wins only for ensembles of small runs whose
- * step is shorter than the stepped path's launch latency), with p = 4 and
- * JL = 256, or JL = 512 for ensembles of at least 2^30 ordered pairs.  Both paths give the same trajectories up to rounding
- * (different summation orders); each is deterministic.
+ * Without a forced or tuned entry, ensembles of small runs take one launch
+ * per step over the whole rows of every run, the others the stepped path
+ * (the smaller estimated step time decides) with p = 4 and JL = 256, or
+ * JL = 512 for ensembles of at least 2^30 ordered pairs.  All paths give the
+ * same trajectories up to rounding (different summation orders); each is
+ * deterministic.
  * Graph capture: md_run may be called on a stream that is being captured.
  * With nrun = 1 it enqueues kernels and device copies only.  With nrun > 1
  * it also copies run tables (built from offsets and traps at the call) from
@@ -302,11 +307,11 @@ const char* cb_last_error(void);
 
 /* Times the candidate launch configurations (i-particles per lane, workgroup
  * size, j-split count) of `op` at n ions and precision prec on the current
- * device, keeps the fastest for all later calls with n in the same
- * power-of-two bucket, and, when cache_path is non-NULL, merges it into that
+ * device (and, for small n, the one-launch evaluation of whole rows), keeps
+ * the fastest for all later calls with n in the same power-of-two bucket, and, when cache_path is non-NULL, merges it into that
  * JSON-lines file.  For md_step / md_run at n <= 8192 the force kernel is
- * tuned for coulomb_forces, and the j-parts of the one-launch step
- * (algorithm 3) for the md calls.  Uses synthetic inputs it allocates itself (this call, and
+ * tuned for coulomb_forces, and the better of its steps and the one-launch
+ * step (algorithm 3) is kept for the md calls.  Uses synthetic inputs it allocates itself (this call, and
  * cb_load_tuning, are the only ones that allocate).  Synchronous. */
 cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_path);
 
@@ -322,14 +327,18 @@ cb_status cb_load_tuning(const char* cache_path);
  *          j-segment and sum their reactions in LDS before one write, which
  *          cuts the partial sums written and read back by four;
  *          3: md_step / md_run of one run of at most 8192 ions in one launch
- *          per step, every ordered pair evaluated by one wave per 64 ions and
- *          j-part, the parts added in a fixed order by the last to finish,
- *          then trap, kick and drift -- the default up to 256 ions),
+ *          per step, every ordered pair evaluated, a workgroup taking 4 or 8
+ *          ions against all j and then applying trap, kick and drift),
  * out[1] = i-particles per lane, out[2] = workgroup size (algorithm 0) or
  *          j's per reduction group (algorithms 1, 2, 4),
  * out[3] = j-splits (algorithm 0), j-segment length (algorithms 1, 2, 4) or
- *          j-parts per 64 ions (algorithm 3),
+ *          j-parts (algorithm 3; 1..32 are accepted, the launch's shape
+ *          follows n alone),
  * out[4] = 1 if it came from tuning or cb_set_config.
+ * While an entry was not set by cb_set_config, a call of at most 6144 ions
+ * (forces, energy, gradient, md_step, md_run) evaluates whole rows in one
+ * launch (as algorithm 3) in the place of the reported two; a tuned entry
+ * does so where that was the faster.
  * CB_EINVAL for a NULL out, n outside [1, 2^28], or an op or prec outside
  * its enum. */
 cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);

@@ -87,7 +87,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
     const int ps_force[] = {1, 2, 4}, ps_hvp[] = {1, 2};
     const int wgs[] = {64, 128, 256};
     const int splits[] = {1, 2, 4, 8, 16, 24, 32, 48, 64};
-    LaunchCfg best{0, 0, 0, 1, ALGO_DIRECT};
+    LaunchCfg best{0, 0, 0, 1, ALGO_DIRECT, 0};
     float best_ms = 1e30f;
     cb_status rc = CB_OK;
     const int np = hv ? 2 : 3;
@@ -96,7 +96,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             for (int sp : splits) {
                 const int p = hv ? ps_hvp[ip] : ps_force[ip];
                 if (sp > 1 && n / sp < 64) continue;
-                LaunchCfg c{p, wg, sp, 1, ALGO_DIRECT};
+                LaunchCfg c{p, wg, sp, 1, ALGO_DIRECT, 0};
                 const int jlen = split_len(n, sp);
                 auto launch = [&]() -> cb_status {
                     if (hv)
@@ -138,7 +138,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             for (int jl : kSymJL) {
                 if (rc) break;
                 if (algo == ALGO_SYM_ROWS && !sym_rows_p_ok(p)) continue;
-                LaunchCfg c{p, kSymGroup, jl, 1, algo};
+                LaunchCfg c{p, kSymGroup, jl, 1, algo, 0};
                 auto launch = [&]() {
                     return launch_pair_sym(prec, c, (int)n, x, y, z, q, 0.0, sws.p, static_cast<double*>(F.p), st);
                 };
@@ -161,12 +161,47 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             }
         (void)hipStreamSynchronize(st);
     }
+    // forces and energy of at most kRowsForcesMaxN ions: the whole call with
+    // the best configuration (pair launch and epilogue) against the launch of
+    // whole rows, which the entry then takes if it is faster
+    if (rc == CB_OK && best.p != 0 && !hv && n <= kRowsForcesMaxN) {
+        DevBuf out, fws;
+        const int cop = energy_only ? CB_OP_ENERGY : CB_OP_FORCES;
+        put_cfg(cop, n, prec, best);
+        const size_t need = cb_workspace_size(cop, n, 1, 1, prec);
+        if (hipMalloc(&out.p, sizeof(double) * 3 * (size_t)n) != hipSuccess || hipMalloc(&fws.p, need) != hipSuccess)
+            rc = fail(CB_EHIP, "cb_autotune: allocation failed");
+        double* o = static_cast<double*>(out.p);
+        float ms2[2] = {0.f, 0.f};
+        for (int rows = 0; rows < 2 && rc == CB_OK; ++rows) {
+            best.rows = rows;
+            put_cfg(cop, n, prec, best);
+            auto launch = [&]() {
+                return energy_only ? coulomb_energy(n, x, y, z, q, 0.0, prec, o, fws.p, need, st)
+                                   : coulomb_forces(n, x, y, z, q, 0.0, prec, o, o + n, o + 2 * n, fws.p, need, st);
+            };
+            if ((rc = launch())) break;
+            const int reps = 10;
+            (void)hipEventRecord(e0, st);
+            for (int r = 0; r < reps && rc == CB_OK; ++r) rc = launch();
+            (void)hipEventRecord(e1, st);
+            if (rc || hipEventSynchronize(e1) != hipSuccess) {
+                if (!rc) rc = fail(CB_EHIP, "cb_autotune: timing failed");
+                break;
+            }
+            (void)hipEventElapsedTime(&ms2[rows], e0, e1);
+        }
+        best.rows = rc == CB_OK && ms2[1] < ms2[0];
+        drop_cfg(cop, n, prec);
+        (void)hipStreamSynchronize(st);
+    }
     // md_step / md_run of at most kSmallRunMax ions: whole steps (md_run on
     // the synthetic cloud at rest) of the two-launch step with the best force
-    // configuration and of the one-launch step for each j-part count; the
-    // faster is kept for the md calls.
+    // configuration and of the one-launch step; the faster is kept for the
+    // md calls.
     const bool md_op = (op == CB_OP_MD_STEP || op == CB_OP_MD_RUN);
     LaunchCfg md_best = best;
+    md_best.rows = 0;
     float md_ms = 1e30f;
     if (rc == CB_OK && md_op && n <= kSmallRunMax) {
         DevBuf state, mass, mws;
@@ -186,7 +221,8 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         tr.wz = 1.2566370614359172e6;
         const int64_t offs[2] = {0, n};
         std::vector<LaunchCfg> cands{best};
-        for (int S = 1; S <= kSmallPartsMax && (S == 1 || n / S >= 16); S *= 2) cands.push_back({1, 64, S, 1, ALGO_SMALL});
+        cands[0].rows = 0;  // the launches of its own shape
+        cands.push_back({1, 64, small_parts(n), 1, ALGO_SMALL, 0});
         for (const LaunchCfg& c : cands) {
             if (rc) break;
             put_cfg(CB_OP_MD_RUN, n, prec, c);
@@ -238,8 +274,9 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         auto line = [&](int o, const LaunchCfg& c, float ms) {
             std::fprintf(f,
                          "{\"arch\": \"%s\", \"op\": %d, \"prec\": %d, \"bucket\": %d, \"n\": %lld, \"p\": %d, "
-                         "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"ms\": %.6f}\n",
-                         arch_name().c_str(), o, prec, n_bucket(n), (long long)n, c.p, c.wg, c.splits, c.algo, ms);
+                         "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"rows\": %d, \"ms\": %.6f}\n",
+                         arch_name().c_str(), o, prec, n_bucket(n), (long long)n, c.p, c.wg, c.splits, c.algo, c.rows,
+                         ms);
         };
         line(op, best, best_ms);
         if (md_op && n <= kSmallRunMax) line(CB_OP_MD_RUN, md_best, md_ms);
@@ -257,18 +294,20 @@ cb_status cb_load_tuning(const char* cache_path) {
 
     while (std::fgets(line, sizeof line, f)) {
         char a[64] = {0};
-        int op, prec, bucket, p, wg, sp, algo = 0;
+        int op, prec, bucket, p, wg, sp, algo = 0, rows = 0;
         long long n;
         if (std::sscanf(line,
                         "{\"arch\": \"%63[^\"]\", \"op\": %d, \"prec\": %d, \"bucket\": %d, \"n\": %lld, \"p\": %d, "
-                        "\"wg\": %d, \"splits\": %d, \"algo\": %d",
-                        a, &op, &prec, &bucket, &n, &p, &wg, &sp, &algo) < 8)
+                        "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"rows\": %d",
+                        a, &op, &prec, &bucket, &n, &p, &wg, &sp, &algo, &rows) < 8)
             continue;
         if (arch != a || op < 0 || op > CB_OP_ADJOINT || prec < 0 || prec > CB_MIXED_F32D || n < 1 ||
             n > kMaxIons)
             continue;
-        LaunchCfg c{p, wg, sp, 1, algo};
+        LaunchCfg c{p, wg, sp, 1, algo, 0};
         if (!valid_cfg(op, c)) continue;
+        // (a file without the field, or a size the path does not take: 0)
+        if (rows == 1 && sym_op(op) && rows_op(op == CB_OP_ENERGY ? CB_OP_ENERGY : CB_OP_FORCES, n)) c.rows = 1;
         if (op == CB_OP_FORCES || op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) {
             // as cb_autotune: a forces line also sets the md calls above
             // kSmallRunMax ions; an md line sets the md calls (and forces,
@@ -277,6 +316,7 @@ cb_status cb_load_tuning(const char* cache_path) {
             if (c.algo == ALGO_SMALL && n > kSmallRunMax) continue;
             if (c.algo != ALGO_SMALL) put_cfg(CB_OP_FORCES, n, prec, c);
             if (md_line || n > kSmallRunMax) {
+                c.rows = 0;  // (the forces' choice; the md calls' is ALGO_SMALL)
                 put_cfg(CB_OP_MD_STEP, n, prec, c);
                 put_cfg(CB_OP_MD_RUN, n, prec, c);
             }

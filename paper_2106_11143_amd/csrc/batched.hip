@@ -452,12 +452,17 @@ cb_status md_run_batched(int32_t nrun, const int64_t* offsets, const cb_state* s
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return fail(CB_EHIP, "md_run: device query failed");
     // Path.  A forced or tuned entry decides.  Otherwise estimate the time of
-    // one step on each path from rates measured on MI355X: this kernel runs
-    // a small run at about 1.6e9 ordered pairs/s per CU (its runs are spread
-    // over the CUs, the largest bounding the step); the stepped path costs
-    // about 40 us of launch latency per step plus the pairs at 1.8e12/s.
-    // The stepped path uses 256-ion i-blocks, with 512-ion j-segments when
-    // the ensemble holds 2^30 or more ordered pairs (4096 or more tiles) and
+    // one step on each path from rates measured on MI355X.  Whole rows per
+    // workgroup (rows.hip): one launch of about 5 us and every ordered pair
+    // at 1.25e12/s.  Newton's-third-law tiles (ensemble.hip): two launches,
+    // whose longest tile bounds a small ensemble (about 45 us in all), and
+    // the pairs at 2.3e12/s.  us per step, rows / tiles: 4 runs of 30-100
+    // ions 4.8 / 51 (the persistent kernel of this file 25.4); 8 of 64-600
+    // 6.3 / 49; 64 of 64-1024 (2.2e7 pairs) 26.3 / 67.5; 512 of 64-512
+    // (5.0e7) 57 / 89; 512 of 64-1024 (1.9e8) 166 / 159; 16 of 2048-4096
+    // (1.4e8) 114 / 88.
+    // The tiles use 256-ion i-blocks, with 512-ion j-segments when the
+    // ensemble holds 2^30 or more ordered pairs (4096 or more tiles) and
     // 256-ion ones below (measured on MI355X, ms per step with JL 256 / 512:
     // kz512's 512 runs of 64-4096 ions 1.211 / 1.182; 1024 runs of
     // 1024-4096 3.189 / 3.144; 256 of 2048-4096 1.024 / 1.004; but 128 runs
@@ -468,9 +473,12 @@ cb_status md_run_batched(int32_t nrun, const int64_t* offsets, const cb_state* s
         double pairs = 0.0;
         for (int r = 0; r < nrun; ++r)
             pairs += (double)(offsets[r + 1] - offsets[r]) * (double)(offsets[r + 1] - offsets[r]);
-        const double t_persistent = std::ceil((double)nrun / ncu) * (double)nmax * nmax / 1.6e9;
-        const double t_stepped = 40e-6 + pairs / 1.8e12;
-        ec.algo = t_stepped < t_persistent ? ALGO_SYM_LDS : ALGO_DIRECT;
+        if (5e-6 + pairs / 1.25e12 < 45e-6 + pairs / 2.3e12) {
+            const WsLayout LE = ws_layout(CB_OP_MD_RUN, offsets[nrun], nrun, 1, prec);
+            return md_run_rows_ensemble(nrun, offsets, s, q, m, traps, t0, dt, nsteps, eps2, prec, flags, energies,
+                                        every, static_cast<char*>(ws) + LE.aux, ws_bytes - LE.aux, st);
+        }
+        ec.algo = ALGO_SYM_LDS;
         ec.p = 4;
         ec.splits = pairs >= 1073741824.0 ? 512 : 256;
     }

@@ -86,6 +86,11 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
     LaunchCfg c;
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
+    // small runs and clouds: whole rows in one launch whatever is reported
+    // below (us per md_run step on MI355X, this / the two-launch step: 150
+    // ions 4.0 / 7.6, 1024 5.2 / 9.5, 2048 7.8 / 12.5, 4096 16.5 / 21.4, 6000
+    // 31.2 / 35.7, 8192 54.3 / 54.0)
+    c.rows = rows_op(op, n);
     (void)prec;
     if (op == CB_OP_MD_ENSEMBLE) {
         // Stepped ensemble path (ensemble.hip).  While this entry is untuned,
@@ -98,12 +103,6 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
     }
     const bool force_op = sym_op(op);
     if ((op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) && n <= kSmallRunDefault) {
-        // One launch per step: for the smallest runs the two-launch step is
-        // bound by the latency of its second launch (measured on MI355X,
-        // per step without / with energy records: 6.8 / 9.0 us against 7.7 /
-        // 9.0 at 128 ions, 7.1 / 9.5 against 7.5 / 8.6 at 256; from 384 ions
-        // the two-launch step with its 16-thread epilogue is faster, 8.4 /
-        // 9.6 against 8.7 / 11.3).
         c.algo = ALGO_SMALL;
         c.p = 1;
         c.wg = 64;
@@ -148,6 +147,7 @@ LaunchCfg direct_cfg(int op, int64_t n, int prec) {
     LaunchCfg c;
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
+    c.rows = rows_op(op, n);
     (void)prec;
     c.wg = 64;
     c.p = 1;
@@ -214,6 +214,10 @@ bool valid_cfg(int op, const LaunchCfg& c) {
                                                                  : (c.p == 1 || c.p == 2 || c.p == 4);
     return p_ok && (c.wg == 64 || c.wg == 128 || c.wg == 256) && c.splits >= 1 && c.splits <= kMaxSplits;
 }
+
+// j-parts that a default ALGO_SMALL entry reports (the launch's shape follows
+// the run's size alone).
+int small_parts(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(n / 32, 8)); }
 
 // Actual j-range per split for a requested split count (multiple of 8).
 int split_len(int64_t n, int splits) {
@@ -342,7 +346,7 @@ cb_status cb_set_config(int32_t op, int64_t n, int32_t prec, int32_t algo, int32
         drop_cfg(op, n, prec);
         return ok();
     }
-    LaunchCfg c{p, wg, splits, 1, algo};
+    LaunchCfg c{p, wg, splits, 1, algo, 0};
     const bool hv_op = (op == CB_OP_HVP || op == CB_OP_ADJOINT);
     if (!valid_cfg(op, c) || (is_sym(algo) && op != CB_OP_MD_ENSEMBLE && !hv_op && n > kSymMaxN) ||
         (is_sym(algo) && hv_op && n > hvp_sym_max_n(p)) || (algo == ALGO_SMALL && n > kSmallRunMax))

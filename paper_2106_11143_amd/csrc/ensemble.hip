@@ -15,9 +15,7 @@
 //      current positions of the same i-block.
 // When no run is longer than an i-block there are no tiles, and the second
 // launch alone evaluates every pair of each run directly (16 waves per 64
-// ions).  md_run_small steps one small run in one launch per step with no
-// tables at all (k_small_step: one wave per 64 ions and part of the run, the
-// parts added by the last to arrive).
+// ions).  Ensembles of small runs take one launch per step instead (rows.hip).
 // Energy records add each ion's Coulomb potential (a direct pass over its
 // run) on the recording step; the last 64-ion chunk of a run to finish sums
 // the run's chunk partials in chunk order.  Results do not depend on timing.
@@ -29,8 +27,8 @@
 
 #include "internal.hpp"
 #include "pair_sym.hpp"
-#include "split_sum.hpp"
 #include "step_common.hpp"
+#include "step_ion.hpp"
 
 namespace cb {
 
@@ -164,13 +162,6 @@ struct EnsParams {
     int nrun, nchunk;
     long long nrec, rec;
     unsigned* flags;
-    // k_small_step: the run's size and trap, its j-parts per 64 ions, the
-    // parts' sums [nchunk * S][4][64] and the arrival counts [nchunk].
-    int n1;
-    cb_trap trap1;
-    int S;
-    double* spart;
-    unsigned* scount;
 };
 
 // Share w of PARTS of [a, b).
@@ -223,73 +214,6 @@ __device__ __forceinline__ void direct_range(int lo, int hi, int kc, double xk, 
         }
     }
     for (; jg < hi; ++jg) pair(X[jg], Y[jg], Z[jg], Q[jg], jg);
-}
-
-// Trap, kick and drift (as P.mode says) of ion i (packed index) at (x, y, z)
-// with charge qk, Coulomb force (Fx, Fy, Fz) and pot = sum_j q_j / r; its
-// energy terms (EPI_ENERGY) go to eK, eC, eT.  Non-finite results set the
-// flag.
-__device__ __forceinline__ void step_ion(const EnsParams& P, const cb_trap& tr, int i, double x, double y,
-                                         double z, double qk, double Fx, double Fy, double Fz, double pot,
-                                         double& eK, double& eC, double& eT) {
-    const unsigned mode = P.mode;
-    const TrapK kk = trap_k(tr, step_time(P.t0, P.dt, P.step));
-    double vx = P.vx[i], vy = P.vy[i], vz = P.vz[i];
-    double ax = P.ax[i], ay = P.ay[i], az = P.az[i];
-    const double mi = P.m[i];
-    bool ok = true;
-    if (mode & (EPI_ACCEL | EPI_KICK)) {
-        const double anx = Fx / mi - kk.kx * x;
-        const double any = Fy / mi - kk.ky * y;
-        const double anz = Fz / mi - kk.kz * z;
-        if (mode & EPI_KICK) {
-            const double h = 0.5 * P.dt;
-            if (tr.gamma == 0.0) {
-                vx = vx + h * (ax + anx);
-                vy = vy + h * (ay + any);
-                vz = vz + h * (az + anz);
-            } else {  // friction -g v by the trapezoidal rule, g = Gamma / m_i
-                const double g = tr.gamma / mi, lo = 1.0 - g * h, hi = 1.0 + g * h;
-                vx = (vx * lo + h * (ax + anx)) / hi;
-                vy = (vy * lo + h * (ay + any)) / hi;
-                vz = (vz * lo + h * (az + anz)) / hi;
-            }
-            P.vx[i] = vx;
-            P.vy[i] = vy;
-            P.vz[i] = vz;
-        }
-        ax = anx;
-        ay = any;
-        az = anz;
-        P.ax[i] = ax;
-        P.ay[i] = ay;
-        P.az[i] = az;
-        ok = finite3(ax, ay, az) && finite3(vx, vy, vz);
-    }
-    if (mode & EPI_ENERGY) {
-        eK = 0.5 * mi * (vx * vx + vy * vy + vz * vz);
-        eC = 0.5 * kCoulomb * qk * pot;
-        eT = 0.5 * mi * (kk.kx * x * x + kk.ky * y * y + kk.kz * z * z);
-        ok = ok && finite3(eK, eC, eT);
-    }
-    if (mode & EPI_DRIFT) {
-        const double dt = P.dt, h2 = 0.5 * dt * dt;
-        if (tr.gamma == 0.0) {
-            x = x + vx * dt + h2 * ax;
-            y = y + vy * dt + h2 * ay;
-            z = z + vz * dt + h2 * az;
-        } else {  // the drift sees the friction acceleration -g v too
-            const double g = tr.gamma / mi;
-            x = x + vx * dt + h2 * (ax - g * vx);
-            y = y + vy * dt + h2 * (ay - g * vy);
-            z = z + vz * dt + h2 * (az - g * vz);
-        }
-        P.xn[i] = x;
-        P.yn[i] = y;
-        P.zn[i] = z;
-        ok = ok && finite3(x, y, z);
-    }
-    if (!ok) atomicOr(P.flags, 1u);
 }
 
 // Energy record of run r, by one whole wave for chunk cid of the run's
@@ -451,96 +375,14 @@ __global__ void __launch_bounds__(64 * PARTS) k_ens_step(EnsParams P) {
     double eK = 0.0, eC = 0.0, eT = 0.0;
     if (k < n) {
         const double qk = Q[k];
-        step_ion(P, P.traps[ch.x], o + k, xk, yk, zk, qk, kCoulomb * (tot[3] + qk * (tot[0] - tot[6])),
+        const cb_trap& tr = P.traps[ch.x];
+        step_ion(P, trap_k(tr, step_time(P.t0, P.dt, P.step)), tr.gamma, o + k, load_ion(P, o + k), xk, yk, zk, qk,
+                 kCoulomb * (tot[3] + qk * (tot[0] - tot[6])),
                  kCoulomb * (tot[4] + qk * (tot[1] - tot[7])), kCoulomb * (tot[5] + qk * (tot[2] - tot[8])), tot[9],
                  eK, eC, eT);
     }
     if (mode & EPI_ENERGY)
         energy_arrival(P, ch.x, blockIdx.x, ru.w, ch.x + 1 < P.nrun ? P.runs[ch.x + 1].w : P.nchunk, eK, eC, eT);
-}
-
-// Direct pairs of ion kc with the nt j's of an LDS tile (first j = j0), as
-// direct_range; the tile entries are read at a uniform address (broadcast).
-template <int PREC, bool FORCE, bool POT>
-__device__ __forceinline__ void direct_tile(const double4* __restrict__ jt, int nt, int j0, int kc, double xk,
-                                            double yk, double zk, double eps2, const SeriesK& K, double (&f)[3],
-                                            double& u) {
-#pragma unroll 4
-    for (int t = 0; t < nt; ++t) {
-        const double4 r = jt[t];
-        const double dx = xk - r.x, dy = yk - r.y, dz = zk - r.z;
-        const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
-        double s = 0.0, y = 0.0;
-        inv_r<PREC, FORCE, POT>(r2, r.w, K, s, y);
-        if (j0 + t == kc) {
-            s = 0.0;
-            y = 0.0;
-        }
-        if (FORCE) {
-            f[0] = __builtin_fma(dx, s, f[0]);
-            f[1] = __builtin_fma(dy, s, f[1]);
-            f[2] = __builtin_fma(dz, s, f[2]);
-        }
-        if (POT) u = __builtin_fma(r.w, y, u);
-    }
-}
-
-constexpr int kSmallTile = 256;  // j's per LDS tile of k_small_step (8 KB)
-
-// One run of P.n1 ions with trap P.trap1, one launch per step.  Workgroup
-// b = one wave: ions 64 c .. 64 c + 63 (c = b / S) against the s-th of S
-// parts of the run (s = b % S), whose j data are staged through LDS in
-// tiles of kSmallTile (coalesced loads, one memory round trip per tile).
-// It stores its sums, and the last of the chunk's S workgroups to arrive
-// (counted in P.scount[c], zero at launch and left zero) adds them in part
-// order and applies trap, kick and drift.
-template <int PREC>
-__global__ void __launch_bounds__(64) k_small_step(EnsParams P) {
-    __shared__ double4 jt[kSmallTile];
-    const int S = P.S;
-    const int c = blockIdx.x / S, s = blockIdx.x - c * S;
-    const int n = P.n1, lane = threadIdx.x;
-    const int k = c * 64 + lane, kc = min(k, n - 1);
-    const unsigned mode = P.mode;
-    const bool need_f = (mode & (EPI_ACCEL | EPI_KICK)) != 0, need_p = (mode & EPI_ENERGY) != 0;
-    const double xk = P.x[kc], yk = P.y[kc], zk = P.z[kc];
-    const SeriesK K;
-    double f[3] = {0.0, 0.0, 0.0}, u = 0.0;
-    const int len = (n + S - 1) / S;
-    const int lo = min(n, s * len), hi = min(n, lo + len);
-    if (need_f || need_p)
-        for (int t0 = lo; t0 < hi; t0 += kSmallTile) {
-            const int nt = min(hi - t0, kSmallTile);
-            for (int t = lane; t < nt; t += 64) jt[t] = make_double4(P.x[t0 + t], P.y[t0 + t], P.z[t0 + t], P.q[t0 + t]);
-            __syncthreads();
-            if (need_f && need_p) direct_tile<PREC, true, true>(jt, nt, t0, kc, xk, yk, zk, P.eps2, K, f, u);
-            else if (need_f) direct_tile<PREC, true, false>(jt, nt, t0, kc, xk, yk, zk, P.eps2, K, f, u);
-            else direct_tile<PREC, false, true>(jt, nt, t0, kc, xk, yk, zk, P.eps2, K, f, u);
-            __syncthreads();
-        }
-    double* mine = P.spart + (size_t)blockIdx.x * 4 * 64;
-    mine[lane] = f[0];
-    mine[64 + lane] = f[1];
-    mine[128 + lane] = f[2];
-    mine[192 + lane] = u;
-    __threadfence();  // these sums before the arrival
-    int last = 0;
-    if (lane == 0) last = atomicAdd(&P.scount[c], 1u) == (unsigned)(S - 1);
-    last = __shfl(last, 0);
-    if (!last) return;
-    __threadfence();  // every part of this chunk is visible
-    double t[4];
-    const double* pc = P.spart + (size_t)c * S * 4 * 64 + lane;
-    const double* ps[4] = {pc, pc + 64, pc + 128, pc + 192};
-    const size_t st[4] = {4 * 64, 4 * 64, 4 * 64, 4 * 64};
-    split_sums<4>(ps, st, S, t);  // the four sums' loads together, each in part order
-    if (lane == 0) P.scount[c] = 0u;
-    double eK = 0.0, eC = 0.0, eT = 0.0;
-    if (k < n) {
-        const double cq = kCoulomb * P.q[k];
-        step_ion(P, P.trap1, k, xk, yk, zk, P.q[k], cq * t[0], cq * t[1], cq * t[2], t[3], eK, eC, eT);
-    }
-    if (mode & EPI_ENERGY) energy_arrival(P, 0, c, 0, P.nchunk, eK, eC, eT);
 }
 
 __global__ void k_zero_counts(unsigned* __restrict__ c, int n) {
@@ -815,107 +657,6 @@ cb_status md_run_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* 
     if (cur != bufA)
         for (int c = 0; c < 3; ++c)
             if (hipMemcpyAsync(bufA[c], cur[c], sizeof(double) * ntot, hipMemcpyDeviceToDevice, st) != hipSuccess)
-                return fail(CB_EHIP, "md_run: copy of the final positions failed");
-    return ok();
-}
-
-size_t md_small_ws_bytes(int64_t n, int S) {
-    const size_t nch = (size_t)((n + 63) / 64);
-    return al(sizeof(double) * 3 * (size_t)n) + al(sizeof(double) * 3 * nch) + al(sizeof(unsigned)) +
-           al(sizeof(double) * 4 * 64 * nch * (size_t)S) + al(sizeof(unsigned) * nch);
-}
-
-// Parts of at least 32 j's, at most 8 of them (measured on MI355X at
-// 256 and 1024 ions).
-int small_parts(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(n / 32, 8)); }
-
-// One run of n <= kSmallRunMax ions, one launch per step (k_small_step).
-// Kernels and device-to-device copies only (nothing from the host), so a
-// caller may capture it in a graph.
-cb_status md_run_small(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap,
-                       double t0, double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags,
-                       double* energies, int64_t every, int S, void* ws, size_t ws_bytes, hipStream_t st) {
-    if (S < 1 || S > kSmallPartsMax) return fail(CB_EINVAL, "md_run: %d j-parts per 64 ions not supported", S);
-    if (ws_bytes < md_small_ws_bytes(n, S))
-        return fail(CB_ENOWS, "md_run: workspace too small for the one-launch step");
-    unsigned* fl = flags_ptr();
-    if (!fl) return fail(CB_EHIP, "md_run: device flag symbol not found");
-    const size_t N = (size_t)n, nch = (N + 63) / 64;
-    char* base = static_cast<char*>(ws);
-    auto carve = [&](size_t bytes) {
-        char* p = base;
-        base += al(bytes);
-        return p;
-    };
-    double* pos2 = reinterpret_cast<double*>(carve(sizeof(double) * 3 * N));
-    double* echunk = reinterpret_cast<double*>(carve(sizeof(double) * 3 * nch));
-    unsigned* ecount = reinterpret_cast<unsigned*>(carve(sizeof(unsigned)));
-    double* spart = reinterpret_cast<double*>(carve(sizeof(double) * 4 * 64 * nch * (size_t)S));
-    unsigned* scount = reinterpret_cast<unsigned*>(carve(sizeof(unsigned) * nch));
-
-    double* bufA[3] = {s->x, s->y, s->z};
-    double* bufB[3] = {pos2, pos2 + N, pos2 + 2 * N};
-    double** cur = bufA;
-    double** nxt = bufB;
-    EnsParams EP{};
-    EP.q = q;
-    EP.m = m;
-    EP.vx = s->vx; EP.vy = s->vy; EP.vz = s->vz;
-    EP.ax = s->ax; EP.ay = s->ay; EP.az = s->az;
-    EP.eps2 = eps2;
-    EP.t0 = t0;
-    EP.dt = dt;
-    EP.echunk = echunk;
-    EP.ecount = ecount;
-    EP.energies = energies;
-    EP.nrun = 1;
-    EP.nchunk = (int)nch;
-    EP.nrec = energies ? nsteps / every + 1 : 0;
-    EP.flags = fl;
-    EP.n1 = (int)n;
-    EP.trap1 = *trap;
-    EP.S = S;
-    EP.spart = spart;
-    EP.scount = scount;
-    k_zero_counts<<<(unsigned)((nch + 1 + 255) / 256), 256, 0, st>>>(scount, (int)nch);
-    cb_status rc = check_launch("k_zero_counts");
-    if (rc) return rc;
-    k_zero_counts<<<1, 64, 0, st>>>(ecount, 1);
-    if ((rc = check_launch("k_zero_counts"))) return rc;
-    // A launch that reads other ions' positions and drifts writes the other
-    // buffer and swaps; a drift alone works in place.
-    auto step_launch = [&](long long step, unsigned mode, long long rec) -> cb_status {
-        const bool reads = (mode & (EPI_ACCEL | EPI_KICK | EPI_ENERGY)) != 0;
-        double** out = reads ? nxt : cur;
-        EP.x = cur[0]; EP.y = cur[1]; EP.z = cur[2];
-        EP.xn = out[0]; EP.yn = out[1]; EP.zn = out[2];
-        EP.step = step;
-        EP.mode = mode;
-        EP.rec = rec;
-        const unsigned g = (unsigned)(nch * (size_t)S);
-        switch (prec) {
-            case CB_FP64: k_small_step<PREC_FP64><<<g, 64, 0, st>>>(EP); break;
-            case CB_MIXED: k_small_step<PREC_MIXED><<<g, 64, 0, st>>>(EP); break;
-            case CB_FP64_IEEE: k_small_step<PREC_IEEE><<<g, 64, 0, st>>>(EP); break;
-            default: k_small_step<PREC_FP32><<<g, 64, 0, st>>>(EP); break;
-        }
-        cb_status r = check_launch("k_small_step");
-        if (r) return r;
-        if ((mode & EPI_DRIFT) && reads) std::swap(cur, nxt);
-        return CB_OK;
-    };
-    const bool rec0 = energies != nullptr;
-    const bool init = (flags & CB_INIT_ACCEL) != 0;
-    const unsigned mode0 = (init ? EPI_ACCEL : 0u) | (rec0 ? EPI_ENERGY : 0u) | (nsteps > 0 ? EPI_DRIFT : 0u);
-    if (mode0 && (rc = step_launch(0, mode0, 0))) return rc;
-    for (long long k = 1; k <= nsteps; ++k) {
-        const bool rec = rec0 && (k % every == 0);
-        if ((rc = step_launch(k, EPI_KICK | (rec ? EPI_ENERGY : 0u) | (k < nsteps ? EPI_DRIFT : 0u), rec ? k / every : 0)))
-            return rc;
-    }
-    if (cur != bufA)
-        for (int c = 0; c < 3; ++c)
-            if (hipMemcpyAsync(bufA[c], cur[c], sizeof(double) * N, hipMemcpyDeviceToDevice, st) != hipSuccess)
                 return fail(CB_EHIP, "md_run: copy of the final positions failed");
     return ok();
 }

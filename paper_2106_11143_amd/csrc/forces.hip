@@ -103,6 +103,11 @@ static cb_status force_stage(int op, int prec, int64_t n, const double* x, const
     return launch_pair(prec, pr.cfg, true, pot, (int)n, x, y, z, q, eps2, pr.jlen, part, ppot, st);
 }
 
+// Whether an evaluation of n ions takes whole rows per workgroup (rows.hip).
+static bool takes_rows(int op, int64_t n, int prec) {
+    return prec != CB_MIXED_F32D && get_cfg(op, n, prec).rows;
+}
+
 // ------------------------------------------- allocation-free forces
 // coulomb_forces_noalloc keeps its partial sums in this array instead of a
 // caller's workspace.  Each GPU the library runs on holds its own copy (the
@@ -147,12 +152,10 @@ static cb_status md_single(int64_t n, const cb_state* s, const double* q, const 
                            double t0, double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags,
                            double* energies, int64_t every, void* ws, int op, hipStream_t st) {
     const WsLayout L = ws_layout(op, n, 1, 1, prec);
-    // One launch per step (every pair direct, then trap, kick and drift) when
-    // so configured: the default up to kSmallRunMax ions.
     const LaunchCfg sc = get_cfg(op, n, prec);
-    if (sc.algo == ALGO_SMALL && n <= kSmallRunMax && md_small_ws_bytes(n, sc.splits) <= L.ppot - L.part)
-        return md_run_small(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, energies, every, sc.splits,
-                            static_cast<char*>(ws) + L.part, L.ppot - L.part, st);
+    if ((sc.rows || sc.algo == ALGO_SMALL) && n <= kSmallRunMax)
+        return md_run_rows(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, every > 0 ? energies : nullptr, every,
+                           static_cast<char*>(ws) + L.part, L.ppot - L.part, st);
     const PairRun pr = plan(op, n, prec);
     double* part = at(ws, L.part);
     double* ppot = at(ws, L.ppot);
@@ -301,6 +304,11 @@ cb_status coulomb_forces(int64_t n, const double* x, const double* y, const doub
     if (overlaps(fx, fy, n) || overlaps(fx, fz, n) || overlaps(fy, fz, n))
         return fail(CB_EINVAL, "coulomb_forces: outputs overlap");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (takes_rows(CB_OP_FORCES, n, prec)) {
+        rc = rows_forces(prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, EPI_FORCES, fx, fy, fz, nullptr,
+                         nullptr, st);
+        return rc ? rc : ok();
+    }
     int S = 0;
     bool prescaled = false;
     if ((rc = force_stage(CB_OP_FORCES, prec, n, x, y, z, q, eps2, ws, L, st, &S, &prescaled))) return rc;
@@ -336,6 +344,11 @@ cb_status coulomb_forces_noalloc(int64_t n, const double* x, const double* y, co
     if (overlaps(fx, fy, n) || overlaps(fx, fz, n) || overlaps(fy, fz, n))
         return fail(CB_EINVAL, "coulomb_forces_noalloc: outputs overlap");
     cb_status rc = CB_OK;
+    if (takes_rows(CB_OP_FORCES, n, prec)) {  // needs no partial sums
+        rc = rows_forces(prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, EPI_FORCES, fx, fy, fz, nullptr,
+                         nullptr, static_cast<hipStream_t>(stream));
+        return rc ? rc : ok();
+    }
     void* ws = scratch_addr(&rc);
     if (!ws) return rc;
     unsigned* fl = flags_ptr();
@@ -453,6 +466,11 @@ cb_status coulomb_energy(int64_t n, const double* x, const double* y, const doub
     if (prec == CB_MIXED_F32D) return fail(CB_EUNSUPPORTED, "coulomb_energy: CB_MIXED_F32D is for the forces only");
     if (!x || !y || !z || !q || !u_out) return fail(CB_EINVAL, "coulomb_energy: NULL argument");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (takes_rows(CB_OP_ENERGY, n, prec)) {
+        rc = rows_forces(prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, 0u, nullptr, nullptr, nullptr, u_out,
+                         at(ws, L.part), st);
+        return rc ? rc : ok();
+    }
     double* ppot = at(ws, L.ppot);
     double* eblk = at(ws, L.eblk);
     int S = 0;
@@ -509,6 +527,11 @@ cb_status coulomb_trap_grad(int64_t n, const double* x, const double* y, const d
     for (auto o : outs)
         if (u_out && overlaps2(o, n, u_out, 1)) return fail(CB_EINVAL, "coulomb_trap_grad: u_out aliases an output");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (takes_rows(u_out ? CB_OP_ENERGY : CB_OP_FORCES, n, prec)) {
+        rc = rows_forces(prec, n, x, y, z, q, m, m ? trap_k(*trap, t) : TrapK{0.0, 0.0, 0.0}, eps2,
+                         want_g ? EPI_GRAD : 0u, gx, gy, gz, u_out, at(ws, L.part), st);
+        return rc ? rc : ok();
+    }
     EpiParams E{};
     E.n = (int)n;
     E.q = q;

@@ -27,6 +27,8 @@ constexpr int kEpiMinIons = kEpiBlock / 16;  // ions per block of the widest epi
 constexpr int epi_parts(int64_t n, int S) { return n > 8192 ? 1 : (S >= 32 ? 16 : (S >= 16 ? 8 : 1)); }
 constexpr int64_t kMaxIons = int64_t(1) << 28;  // largest n any entry point accepts
 constexpr int64_t kSymMaxN = int64_t(1) << 18;  // largest n for the symmetric kernel (partials grow as n^2)
+constexpr int64_t kRowsMaxN = 6144;        // largest run of the one-launch step by default (rows.hip)
+constexpr int64_t kRowsForcesMaxN = 6144;  // and of the one-launch forces, gradient and energy
 constexpr int kMaxDevices = 64;      // GPUs per process the per-device symbol tables hold
 
 // ALGO_SYM and ALGO_SYM_LDS differ only in how the per-j reactions are summed
@@ -34,7 +36,7 @@ constexpr int kMaxDevices = 64;      // GPUs per process the per-device symbol t
 // ALGO_SYM_LDS with kSymRows consecutive i-blocks per workgroup sharing each
 // j-segment, their reactions added in LDS before one store.
 // ALGO_SMALL (md_step / md_run of one run of at most kSmallRunMax ions):
-// one launch per step, every pair direct (md_run_small).
+// one launch per step, every pair direct (md_run_rows).
 enum : int { ALGO_DIRECT = 0, ALGO_SYM = 1, ALGO_SYM_LDS = 2, ALGO_SMALL = 3, ALGO_SYM_ROWS = 4 };
 
 constexpr bool is_sym(int algo) { return algo == ALGO_SYM || algo == ALGO_SYM_LDS || algo == ALGO_SYM_ROWS; }
@@ -91,6 +93,7 @@ struct LaunchCfg {
     int splits;  // direct: requested j-splits; symmetric: segment length JL
     int tuned;   // 1 if set by tuning or cb_set_config
     int algo;    // ALGO_DIRECT, ALGO_SYM or ALGO_SYM_LDS
+    int rows;    // 1: one launch of whole rows (rows.hip) in the place of the above (untuned or tuned, never forced)
 };
 
 struct WsLayout {
@@ -125,6 +128,11 @@ class HostUpload {
 };
 
 int n_bucket(int64_t n);
+// Whether op at n may take whole rows per workgroup.
+constexpr bool rows_op(int op, int64_t n) {
+    return (op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) ? n <= kRowsMaxN
+                                                       : (op == CB_OP_FORCES || op == CB_OP_ENERGY) && n <= kRowsForcesMaxN;
+}
 LaunchCfg default_cfg(int op, int64_t n, int prec);
 LaunchCfg direct_cfg(int op, int64_t n, int prec);
 LaunchCfg get_cfg(int op, int64_t n, int prec);
@@ -190,17 +198,32 @@ cb_status md_run_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* 
                           int32_t prec, uint32_t flags, double* energies, int64_t every, int P, int JL, void* ws,
                           size_t ws_bytes, hipStream_t st);
 
-// One run of at most kSmallRunMax ions in one launch per step
-// (ensemble.hip), with S j-parts per 64 ions (1..kSmallPartsMax): workspace
-// bytes, the default S and the driver.
-constexpr int64_t kSmallRunMax = 8192;
-constexpr int64_t kSmallRunDefault = 256;  // largest run that takes it by default
+// One run in one launch per step, whole rows per workgroup (rows.hip): every
+// entry of ALGO_SMALL, and the untuned default up to kRowsMaxN ions.
+// Workspace bytes and driver.
+constexpr int64_t kSmallRunMax = 8192;     // largest run an ALGO_SMALL entry may hold
+constexpr int64_t kSmallRunDefault = 256;  // the reported default is ALGO_SMALL up to here
 constexpr int kSmallPartsMax = 32;
-size_t md_small_ws_bytes(int64_t n, int S);
 int small_parts(int64_t n);
-cb_status md_run_small(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap,
-                       double t0, double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags,
-                       double* energies, int64_t every, int S, void* ws, size_t ws_bytes, hipStream_t st);
+constexpr int64_t kRowsSmallN = 1536;  // up to here 4 ions to a workgroup of 8 waves, above 8 to 4 waves
+size_t md_rows_ws_bytes(int64_t n);
+cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,
+                      double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags, double* energies,
+                      int64_t every, void* ws, size_t ws_bytes, hipStream_t st);
+
+// Forces (mode EPI_FORCES) or gradient (EPI_GRAD) of n <= kRowsForcesMaxN
+// ions in one launch, and with u_out the energy U_C (+ U_trap with m) in a
+// second; ws: rows_forces_ws_bytes(n) bytes, used with u_out only.
+struct TrapK;
+size_t rows_forces_ws_bytes(int64_t n);
+cb_status rows_forces(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
+                      const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
+                      double* u_out, void* ws, hipStream_t st);
+// md_run_rows for an ensemble of runs, one launch per step over all of them.
+cb_status md_run_rows_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* s, const double* q,
+                               const double* m, const cb_trap* traps, double t0, double dt, int64_t nsteps,
+                               double eps2, int32_t prec, uint32_t flags, double* energies, int64_t every, void* ws,
+                               size_t ws_bytes, hipStream_t st);
 
 // Batched md_run (batched.hip): picks the persistent kernel or the stepped
 // ensemble path.
