@@ -189,8 +189,8 @@ cb_status coulomb_forces_range(int64_t n, int64_t i0, int64_t i1, const double* 
 /* The first stage of coulomb_forces on its own (everything but the final
  * element-wise pass), for timing the pair loop and for callers that finish
  * the sums themselves.  With algorithm 0 (see cb_get_config) the all-pairs
- * kernel leaves its j-split partial force sums, before the fixed-order sum
- * over splits and the k_C q_i factor, at the start of ws as [splits][3][n]
+ * kernel (at any n whose reported algorithm is 0) leaves its j-split partial
+ * force sums, before the fixed-order sum over splits and the k_C q_i factor, at the start of ws as [splits][3][n]
  * doubles and *splits_out (host) is the number of splits; with algorithms 1,
  * 2 and 4 (the Newton's-third-law stages) the start of ws holds the finished
  * forces [3][n] and *splits_out is 0. */
@@ -338,7 +338,9 @@ cb_status cb_load_tuning(const char* cache_path);
  * While an entry was not set by cb_set_config, a call of at most 6144 ions
  * (forces, energy, gradient, md_step, md_run) evaluates whole rows in one
  * launch (as algorithm 3) in the place of the reported two; a tuned entry
- * does so where that was the faster.
+ * does so where that was the faster.  An untuned entry beyond 2^18 ions runs
+ * algorithm 4's tiles (p = 8, segments of 512) in bands whose partial sums
+ * fit the workspace (forces, energy, gradient, md_step, md_run).
  * CB_EINVAL for a NULL out, n outside [1, 2^28], or an op or prec outside
  * its enum. */
 cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);

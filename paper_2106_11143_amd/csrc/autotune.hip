@@ -87,7 +87,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
     const int ps_force[] = {1, 2, 4}, ps_hvp[] = {1, 2};
     const int wgs[] = {64, 128, 256};
     const int splits[] = {1, 2, 4, 8, 16, 24, 32, 48, 64};
-    LaunchCfg best{0, 0, 0, 1, ALGO_DIRECT, 0};
+    LaunchCfg best{0, 0, 0, 1, ALGO_DIRECT, 0, 0};
     float best_ms = 1e30f;
     cb_status rc = CB_OK;
     const int np = hv ? 2 : 3;
@@ -96,7 +96,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             for (int sp : splits) {
                 const int p = hv ? ps_hvp[ip] : ps_force[ip];
                 if (sp > 1 && n / sp < 64) continue;
-                LaunchCfg c{p, wg, sp, 1, ALGO_DIRECT, 0};
+                LaunchCfg c{p, wg, sp, 1, ALGO_DIRECT, 0, 0};
                 const int jlen = split_len(n, sp);
                 auto launch = [&]() -> cb_status {
                     if (hv)
@@ -138,7 +138,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             for (int jl : kSymJL) {
                 if (rc) break;
                 if (algo == ALGO_SYM_ROWS && !sym_rows_p_ok(p)) continue;
-                LaunchCfg c{p, kSymGroup, jl, 1, algo, 0};
+                LaunchCfg c{p, kSymGroup, jl, 1, algo, 0, 0};
                 auto launch = [&]() {
                     return launch_pair_sym(prec, c, (int)n, x, y, z, q, 0.0, sws.p, static_cast<double*>(F.p), st);
                 };
@@ -222,7 +222,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         const int64_t offs[2] = {0, n};
         std::vector<LaunchCfg> cands{best};
         cands[0].rows = 0;  // the launches of its own shape
-        cands.push_back({1, 64, small_parts(n), 1, ALGO_SMALL, 0});
+        cands.push_back({1, 64, small_parts(n), 1, ALGO_SMALL, 0, 0});
         for (const LaunchCfg& c : cands) {
             if (rc) break;
             put_cfg(CB_OP_MD_RUN, n, prec, c);
@@ -304,7 +304,7 @@ cb_status cb_load_tuning(const char* cache_path) {
         if (arch != a || op < 0 || op > CB_OP_ADJOINT || prec < 0 || prec > CB_MIXED_F32D || n < 1 ||
             n > kMaxIons)
             continue;
-        LaunchCfg c{p, wg, sp, 1, algo, 0};
+        LaunchCfg c{p, wg, sp, 1, algo, 0, 0};
         if (!valid_cfg(op, c)) continue;
         // (a file without the field, or a size the path does not take: 0)
         if (rows == 1 && sym_op(op) && rows_op(op == CB_OP_ENERGY ? CB_OP_ENERGY : CB_OP_FORCES, n)) c.rows = 1;

@@ -91,6 +91,7 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
     // ions 4.0 / 7.6, 1024 5.2 / 9.5, 2048 7.8 / 12.5, 4096 16.5 / 21.4, 6000
     // 31.2 / 35.7, 8192 54.3 / 54.0)
     c.rows = rows_op(op, n);
+    c.bands = sym_op(op) && n > kSymMaxN;
     (void)prec;
     if (op == CB_OP_MD_ENSEMBLE) {
         // Stepped ensemble path (ensemble.hip).  While this entry is untuned,
@@ -139,7 +140,10 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
         c.splits = 128;
         return c;
     }
-    return direct_cfg(op, n, prec);
+    const int bands = c.bands;
+    c = direct_cfg(op, n, prec);
+    c.bands = bands;
+    return c;
 }
 
 // The all-pairs kernel's default shape for op at n.
@@ -148,6 +152,7 @@ LaunchCfg direct_cfg(int op, int64_t n, int prec) {
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
     c.rows = rows_op(op, n);
+    c.bands = 0;
     (void)prec;
     c.wg = 64;
     c.p = 1;
@@ -346,7 +351,7 @@ cb_status cb_set_config(int32_t op, int64_t n, int32_t prec, int32_t algo, int32
         drop_cfg(op, n, prec);
         return ok();
     }
-    LaunchCfg c{p, wg, splits, 1, algo, 0};
+    LaunchCfg c{p, wg, splits, 1, algo, 0, 0};
     const bool hv_op = (op == CB_OP_HVP || op == CB_OP_ADJOINT);
     if (!valid_cfg(op, c) || (is_sym(algo) && op != CB_OP_MD_ENSEMBLE && !hv_op && n > kSymMaxN) ||
         (is_sym(algo) && hv_op && n > hvp_sym_max_n(p)) || (algo == ALGO_SMALL && n > kSmallRunMax))

@@ -75,16 +75,23 @@ static PairRun plan(int op, int64_t n, int prec) {
 
 static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
+// Whether an evaluation of n ions takes the Newton's-third-law stage in bands.
+static bool takes_bands(int op, int64_t n, int prec) {
+    return prec != CB_MIXED_F32D && get_cfg(op, n, prec).bands;
+}
+
 // The pair stage with the configured algorithm: forces, and the potential
 // sums too when pot.  Direct: partial sums [S][3][n] at ws+L.part (to be
 // scaled by k_C q_i) and [S][n] at ws+L.ppot.  Symmetric: the finished forces
 // [3][n] at ws+L.part (S = 1, prescaled), its tiles and partials after them,
 // and the potential sums [n] at ws+L.ppot (S = 1).  tiles_ready: when
 // non-NULL and true, the tile table of the symmetric stage is already in ws (an earlier
-// call of the same md_run); set to true once it is.
+// call of the same md_run); set to true once it is.  bands: the stage may run
+// in bands beyond kSymMaxN ions.
 static cb_status force_stage(int op, int prec, int64_t n, const double* x, const double* y, const double* z,
                              const double* q, double eps2, void* ws, const WsLayout& L, hipStream_t st, int* S_out,
-                             bool* prescaled, bool pot = false, bool* tiles_ready = nullptr) {
+                             bool* prescaled, bool pot = false, bool* tiles_ready = nullptr,
+                             bool bands = true) {
     const LaunchCfg cfg = get_cfg(op, n, prec);
     double* part = at(ws, L.part);
     double* ppot = pot ? at(ws, L.ppot) : nullptr;
@@ -96,6 +103,13 @@ static cb_status force_stage(int op, int prec, int64_t n, const double* x, const
             launch_pair_sym(prec, cfg, (int)n, x, y, z, q, eps2, tiles_ws, part, st, ppot, tiles_ready && *tiles_ready);
         if (tiles_ready && rc == CB_OK) *tiles_ready = true;
         return rc;
+    }
+    if (bands && takes_bands(op, n, prec)) {
+        *S_out = 1;
+        *prescaled = true;
+        const size_t fbytes = al256(sizeof(double) * 3 * (size_t)n);
+        return launch_pair_sym_bands(prec, (int)n, x, y, z, q, eps2, static_cast<char*>(ws) + L.part + fbytes,
+                                     L.ppot - L.part - fbytes, part, st, ppot);
     }
     const PairRun pr = plan(op, n, prec);
     *S_out = pr.S;
@@ -212,7 +226,7 @@ static cb_status md_single(int64_t n, const cb_state* s, const double* q, const 
     // potential alone (an energy record of step 0 without CB_INIT_ACCEL) takes
     // the symmetric stage too when it is configured (its forces unused), else
     // the direct kernel's potential-only pass.
-    const bool sym_stage = is_sym(get_cfg(op, n, prec).algo) && n <= kSymMaxN;
+    const bool sym_stage = (is_sym(get_cfg(op, n, prec).algo) && n <= kSymMaxN) || takes_bands(op, n, prec);
     // the symmetric stage's tile table is the same at every step: built by
     // the first force stage of the run, read by the later ones
     bool plan_ready = false;
@@ -452,7 +466,7 @@ cb_status coulomb_pair_stage(int64_t n, const double* x, const double* y, const 
     int S = 0;
     bool prescaled = false;
     if ((rc = force_stage(CB_OP_FORCES, prec, n, x, y, z, q, eps2, ws, L, static_cast<hipStream_t>(stream), &S,
-                          &prescaled)))
+                          &prescaled, false, nullptr, false)))
         return rc;
     *splits_out = prescaled ? 0 : S;
     return ok();
@@ -476,7 +490,7 @@ cb_status coulomb_energy(int64_t n, const double* x, const double* y, const doub
     int S = 0;
     bool share = false;  // the potential partials hold energy shares (the symmetric stage)
     const LaunchCfg ecfg = get_cfg(CB_OP_ENERGY, n, prec);
-    if (is_sym(ecfg.algo) && n <= kSymMaxN) {
+    if ((is_sym(ecfg.algo) && n <= kSymMaxN) || ecfg.bands) {
         // the Newton's-third-law stage with the potential as a fourth
         // component (its forces are a by-product, left in the workspace)
         bool prescaled = false;

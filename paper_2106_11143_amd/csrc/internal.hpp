@@ -94,6 +94,7 @@ struct LaunchCfg {
     int tuned;   // 1 if set by tuning or cb_set_config
     int algo;    // ALGO_DIRECT, ALGO_SYM or ALGO_SYM_LDS
     int rows;    // 1: one launch of whole rows (rows.hip) in the place of the above (untuned or tuned, never forced)
+    int bands;   // 1: the Newton's-third-law stage in bands (untuned entries beyond kSymMaxN)
 };
 
 struct WsLayout {
@@ -174,6 +175,18 @@ size_t sym_ws_bytes(int64_t n, int p, int jl, bool pot = false, int W = 1);
 cb_status launch_pair_sym(int prec, const LaunchCfg& c, int n, const double* x, const double* y, const double* z,
                           const double* q, double eps2, void* ws, double* F, hipStream_t st, double* phi = nullptr,
                           bool plan_filled = false);
+
+// The same beyond kSymMaxN ions, where the partials of the whole triangle
+// (they grow as n^2) do not fit: row-group tiles of kBandP and kBandJL, the
+// triangle's row groups taken in bands whose partials fit ws_bytes, each band
+// finished and added to F (and phi) before the next.  (ms per evaluation on
+// MI355X, the direct kernel / bands: 262145 ions 36.9 / 23.4, 300001 48.3 /
+// 30.0, 420000 94.6 / 59.5, ions grouped by charge; 50.1 / 32.6 at 300001 in
+// seeded order.  Segments of 1024 or 2048 measured 0-3% slower.)
+constexpr int kBandP = 8, kBandJL = 512;
+cb_status launch_pair_sym_bands(int prec, int n, const double* x, const double* y, const double* z, const double* q,
+                                double eps2, void* ws, size_t ws_bytes, double* F, hipStream_t st,
+                                double* phi = nullptr);
 
 // Launches of the pair kernels (pair.hip).  The _range form evaluates the
 // forces / potentials of the ions i0 .. i0 + ni - 1 only (partials indexed by

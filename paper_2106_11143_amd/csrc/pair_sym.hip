@@ -12,8 +12,9 @@ constexpr int kPlanThreads = 1024;
 
 // Tile table, one workgroup (sym_plan_fill in pair_sym.hpp).
 __global__ void __launch_bounds__(kPlanThreads) k_sym_plan(int n, int IB, int JL, int W, int nI,
-                                                           int* __restrict__ rowstart, int2* __restrict__ tiles) {
-    sym_plan_fill<kPlanThreads>(n, IB, JL, W, nI, rowstart, tiles);
+                                                           int* __restrict__ rowstart, int2* __restrict__ tiles,
+                                                           int G0) {
+    sym_plan_fill<kPlanThreads>(n, IB, JL, W, nI, rowstart, tiles, G0);
 }
 
 static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
@@ -94,16 +95,46 @@ static bool go_sym_rows_p(int P, bool pot, int n, int JL, int64_t T, const doubl
                : go_sym_rows<PREC, false>(P, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
 }
 
-template <int PREC>
+template <int PREC, bool BAND>
 static void go_finish(bool pot, unsigned nb, int n, int IB, int JL, int lgJL, int W, const double* x,
                       const double* y, const double* z, const double* q, double eps2, const int* rowstart,
-                      const double* Pi, const double* R, const double* Et, double* F, double* phi, hipStream_t st) {
+                      const double* Pi, const double* R, const double* Et, double* F, double* phi, int G0, int G1,
+                      hipStream_t st) {
     if (pot)
-        k_sym_finish<PREC, true><<<nb, 64 * kFinishParts, 0, st>>>(n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart,
-                                                                   Pi, R, Et, F, phi);
+        k_sym_finish<PREC, true, BAND><<<nb, 64 * kFinishParts, 0, st>>>(n, IB, JL, lgJL, W, x, y, z, q, eps2,
+                                                                         rowstart, Pi, R, Et, F, phi, G0, G1);
     else
-        k_sym_finish<PREC, false><<<nb, 64 * kFinishParts, 0, st>>>(n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart,
-                                                                    Pi, R, Et, F, phi);
+        k_sym_finish<PREC, false, BAND><<<nb, 64 * kFinishParts, 0, st>>>(n, IB, JL, lgJL, W, x, y, z, q, eps2,
+                                                                          rowstart, Pi, R, Et, F, phi, G0, G1);
+}
+
+// Finish of the whole triangle, or of the band of row groups [G0, G1).
+template <bool BAND>
+static cb_status finish(int prec, bool pot, unsigned nb, int n, int IB, int JL, int W, const double* x,
+                        const double* y, const double* z, const double* q, double eps2, const int* rowstart,
+                        const double* Pi, const double* R, const double* Et, double* F, double* phi, int G0, int G1,
+                        hipStream_t st) {
+    int lgJL = 0;
+    while ((1 << lgJL) < JL) ++lgJL;
+    switch (prec) {
+        case PREC_FP64: go_finish<PREC_FP64, BAND>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, G0, G1, st); break;
+        case PREC_MIXED: go_finish<PREC_MIXED, BAND>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, G0, G1, st); break;
+        case PREC_IEEE: go_finish<PREC_IEEE, BAND>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, G0, G1, st); break;
+        default: go_finish<PREC_FP32, BAND>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, G0, G1, st); break;
+    }
+    return check_launch("k_sym_finish");
+}
+
+static bool go_rows_prec(int prec, int P, bool pot, int n, int JL, int64_t T, const double* x, const double* y,
+                         const double* z, const double* q, double eps2, const int2* tiles, double* Pi, double* R,
+                         double* Et, hipStream_t st) {
+    switch (prec) {
+        case PREC_FP64: return go_sym_rows_p<PREC_FP64>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_MIXED: return go_sym_rows_p<PREC_MIXED>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_IEEE: return go_sym_rows_p<PREC_IEEE>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_FP32: return go_sym_rows_p<PREC_FP32>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        default: return false;
+    }
 }
 
 size_t sym_plan_bytes(int64_t n, int IB, int JL, int W) {
@@ -122,7 +153,7 @@ cb_status sym_plan(int n, int IB, int JL, void* ws, SymPlan* out, hipStream_t st
     out->tiles = reinterpret_cast<int2*>(base);
     out->bytes = sym_plan_bytes(n, IB, JL, W);
     if (filled) return CB_OK;
-    k_sym_plan<<<1, kPlanThreads, 0, st>>>(n, IB, JL, W, nG, out->rowstart, out->tiles);
+    k_sym_plan<<<1, kPlanThreads, 0, st>>>(n, IB, JL, W, nG, out->rowstart, out->tiles, 0);
     return check_launch("k_sym_plan");
 }
 
@@ -147,14 +178,7 @@ cb_status launch_pair_sym(int prec, const LaunchCfg& c, int n, const double* x, 
     base += al256(sizeof(double) * 3 * (size_t)JL * (T + 1));
     double* Et = pot ? reinterpret_cast<double*>(base) : nullptr;
     if (T > 0 && W > 1) {
-        bool okk = false;
-        switch (prec) {
-            case PREC_FP64: okk = go_sym_rows_p<PREC_FP64>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st); break;
-            case PREC_MIXED: okk = go_sym_rows_p<PREC_MIXED>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st); break;
-            case PREC_IEEE: okk = go_sym_rows_p<PREC_IEEE>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st); break;
-            case PREC_FP32: okk = go_sym_rows_p<PREC_FP32>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st); break;
-            default: break;
-        }
+        const bool okk = go_rows_prec(prec, P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
         if (!okk) return fail(CB_EINVAL, "launch_pair_sym: unsupported precision %d / p %d", prec, P);
         if ((rc = check_launch("k_pair_sym_rows"))) return rc;
     } else if (T > 0) {
@@ -169,16 +193,64 @@ cb_status launch_pair_sym(int prec, const LaunchCfg& c, int n, const double* x, 
         if (!okk) return fail(CB_EINVAL, "launch_pair_sym: unsupported precision %d / p %d", prec, P);
         if ((rc = check_launch("k_pair_sym"))) return rc;
     }
-    const unsigned nb = (unsigned)((n + 63) / 64);
-    int lgJL = 0;
-    while ((1 << lgJL) < JL) ++lgJL;
-    switch (prec) {
-        case PREC_FP64: go_finish<PREC_FP64>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, st); break;
-        case PREC_MIXED: go_finish<PREC_MIXED>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, st); break;
-        case PREC_IEEE: go_finish<PREC_IEEE>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, st); break;
-        default: go_finish<PREC_FP32>(pot, nb, n, IB, JL, lgJL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F, phi, st); break;
+    return finish<false>(prec, pot, (unsigned)((n + 63) / 64), n, IB, JL, W, x, y, z, q, eps2, rowstart, Pi, R, Et, F,
+                         phi, 0, 0, st);
+}
+
+// Row groups of the band that starts at group G0 with at most ws_bytes of
+// tables and partials (at least one group): its tiles to *T.
+static int band_groups(int64_t n, int G0, bool pot, size_t ws_bytes, int64_t* T) {
+    constexpr int IB = 64 * kBandP, W = kSymRows;
+    const int nG = sym_groups(n, IB, W);
+    const size_t per_tile = sizeof(int2) + sizeof(double) * (3 * IB * W + 3 * (size_t)kBandJL + (pot ? W : 0));
+    const size_t fixed = 4 * 256 + sizeof(int) * (kPlanMaxRows + 1);  // rowstart and the roundings
+    int G = G0;
+    *T = 0;
+    while (G < nG && G - G0 < kPlanMaxRows) {
+        const int64_t t = sym_nseg((int)n, IB, kBandJL, G * W);
+        if (G > G0 && fixed + per_tile * (size_t)(*T + t) > ws_bytes) break;
+        *T += t;
+        ++G;
     }
-    return check_launch("k_sym_finish");
+    return G - G0;
+}
+
+cb_status launch_pair_sym_bands(int prec, int n, const double* x, const double* y, const double* z, const double* q,
+                                double eps2, void* ws, size_t ws_bytes, double* F, hipStream_t st, double* phi) {
+    constexpr int P = kBandP, JL = kBandJL, IB = 64 * P, W = kSymRows;
+    const int nG = sym_groups(n, IB, W);
+    const bool pot = phi != nullptr;
+    for (int G0 = 0; G0 < nG;) {
+        int64_t T = 0;
+        const int ng = band_groups(n, G0, pot, ws_bytes, &T), G1 = G0 + ng;
+        char* base = static_cast<char*>(ws);
+        auto carve = [&](size_t bytes) {
+            char* p = base;
+            base += al256(bytes);
+            return p;
+        };
+        int* rowstart = reinterpret_cast<int*>(carve(sizeof(int) * (ng + 1)));
+        int2* tiles = reinterpret_cast<int2*>(carve(sizeof(int2) * T));
+        double* Pi = reinterpret_cast<double*>(carve(sizeof(double) * 3 * IB * W * T));
+        double* R = reinterpret_cast<double*>(carve(sizeof(double) * 3 * JL * T));
+        double* Et = pot ? reinterpret_cast<double*>(carve(sizeof(double) * W * T)) : nullptr;
+        if (base > static_cast<char*>(ws) + ws_bytes)
+            return fail(CB_ENOWS, "launch_pair_sym_bands: workspace too small for one row group at n = %d", n);
+        k_sym_plan<<<1, kPlanThreads, 0, st>>>(n, IB, JL, W, ng, rowstart, tiles, G0);
+        cb_status rc = check_launch("k_sym_plan");
+        if (rc) return rc;
+        if (T > 0) {
+            if (!go_rows_prec(prec, P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st))
+                return fail(CB_EINVAL, "launch_pair_sym_bands: unsupported precision %d", prec);
+            if ((rc = check_launch("k_pair_sym_rows"))) return rc;
+        }
+        const int k0 = G0 * W * IB;
+        if ((rc = finish<true>(prec, pot, (unsigned)((n - k0 + 63) / 64), n, IB, JL, W, x, y, z, q, eps2, rowstart, Pi, R,
+                               Et, F, phi, G0, G1, st)))
+            return rc;
+        G0 = G1;
+    }
+    return CB_OK;
 }
 
 }  // namespace cb

@@ -41,19 +41,21 @@ __host__ __device__ __forceinline__ int sym_nseg(int n, int IB, int JL, int I) {
 // segment) of tile t.  Each thread sums the segments of a contiguous share of
 // groups, the shares are scanned in LDS (Hillis-Steele), the group starts are
 // kept in LDS, and each wave then writes whole groups of the table, its lanes
-// taking consecutive segments.
+// taking consecutive segments.  A band of the triangle (launch_pair_sym_bands)
+// plans the nI groups from G0 on: rowstart and the slots count from the band,
+// tiles hold whole-triangle groups.
 constexpr int kPlanMaxRows = 2048;  // n <= 2^18 ions in blocks of >= 128
 
 template <int NT>
 __device__ __forceinline__ void sym_plan_fill(int n, int IB, int JL, int W, int nI, int* __restrict__ rowstart,
-                                              int2* __restrict__ tiles) {
+                                              int2* __restrict__ tiles, int G0 = 0) {
     __shared__ int sh[NT];
     __shared__ int rs[kPlanMaxRows + 1];
     const int t = threadIdx.x;
     const int per = (nI + NT - 1) / NT;
     const int r0 = min(nI, t * per), r1 = min(nI, r0 + per);
     int mine = 0;
-    for (int I = r0; I < r1; ++I) mine += sym_nseg(n, IB, JL, I * W);
+    for (int I = r0; I < r1; ++I) mine += sym_nseg(n, IB, JL, (G0 + I) * W);
     sh[t] = mine;
     __syncthreads();
     for (int w = 1; w < NT; w <<= 1) {
@@ -66,7 +68,7 @@ __device__ __forceinline__ void sym_plan_fill(int n, int IB, int JL, int W, int 
     for (int I = r0; I < r1; ++I) {
         rs[I] = acc;
         rowstart[I] = acc;
-        acc += sym_nseg(n, IB, JL, I * W);
+        acc += sym_nseg(n, IB, JL, (G0 + I) * W);
     }
     if (t == NT - 1) {
         rs[nI] = sh[t];
@@ -76,7 +78,7 @@ __device__ __forceinline__ void sym_plan_fill(int n, int IB, int JL, int W, int 
     const int lane = t & 63;
     for (int I = t >> 6; I < nI; I += NT / 64) {
         const int s0 = rs[I], ns = rs[I + 1] - s0;
-        for (int sg = lane; sg < ns; sg += 64) tiles[s0 + sg] = make_int2(I, sg);
+        for (int sg = lane; sg < ns; sg += 64) tiles[s0 + sg] = make_int2(G0 + I, sg);
     }
 }
 
@@ -510,7 +512,10 @@ __host__ __device__ __forceinline__ void share(int a, int b, int w, int& lo, int
 // k_C sum_k phi[k]: q_k times its pairs with the later ions of its own block
 // (q_j r^-1, j > k), plus the energies of the tiles of its row numbered
 // off, off + IB, ... within the row (each tile's energy goes to one ion).
-template <int PREC, bool POT>
+// BAND: the tiles of the row groups [G0, G1) alone, whose sums are added to F
+// and phi (stored when G0 = 0), for the ions from the first of group G0 on;
+// the ions of those groups take their own block's pairs here.
+template <int PREC, bool POT, bool BAND>
 __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB, int JL, int lgJL, int W,
                                                                   const double* __restrict__ x,
                                                                   const double* __restrict__ y,
@@ -520,17 +525,19 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
                                                                   const double* __restrict__ Pi,
                                                                   const double* __restrict__ R,
                                                                   const double* __restrict__ Et,
-                                                                  double* __restrict__ F, double* __restrict__ phi) {
+                                                                  double* __restrict__ F, double* __restrict__ phi,
+                                                                  int G0, int G1) {
     constexpr int NS = POT ? 10 : 9;  // per lane: direct 3, i sums 3, reactions 3 (+ the energy share)
     __shared__ double red[kFinishParts][NS][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int k0 = blockIdx.x * 64;
+    const int k0 = (BAND ? G0 * W * IB : 0) + blockIdx.x * 64;
     const int k = k0 + lane;
     const int kc = min(k, n - 1);
     const int Ik = k0 / IB;
     const int Gk = Ik / W, wk = Ik - Gk * W;
-    const int b0 = Ik * IB, b1 = min(n, b0 + IB);
+    const bool row = !BAND || Gk < G1;  // the ion's own row is one of the band's
+    const int b0 = Ik * IB, b1 = row ? min(n, b0 + IB) : b0;
     const double xk = x[kc], yk = y[kc], zk = z[kc];
     const SeriesK K;
     int lo, hi;
@@ -551,7 +558,9 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
     }
     const int off = kc - b0;
     double p0 = 0.0, p1 = 0.0, p2 = 0.0;
-    share(rowstart[Gk], rowstart[Gk + 1], w, lo, hi);
+    const int gk = BAND ? (row ? Gk - G0 : 0) : Gk;  // the row's entry of rowstart
+    const int t0 = rowstart[gk], t1 = row ? rowstart[gk + 1] : t0;
+    share(t0, t1, w, lo, hi);
 #pragma unroll 4
     for (int t = lo; t < hi; ++t) {
         const double* Pt = Pi + ((size_t)t * W + wk) * 3 * IB + off;
@@ -562,12 +571,13 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
     double e0 = 0.0, e1 = 0.0, e2 = 0.0;
     // the groups whose segments start at or below k: all above k's group, and
     // k's own group when k is not in its first block
-    share(0, Gk + (wk > 0 ? 1 : 0), w, lo, hi);
+    const int g1 = Gk + (wk > 0 ? 1 : 0);
+    share(BAND ? G0 : 0, BAND ? min(G1, g1) : g1, w, lo, hi);
 #pragma unroll 4
     for (int G = lo; G < hi; ++G) {
         const int rel = kc - (G * W + 1) * IB;
         const int sI = rel >> lgJL;
-        const double* Rt = R + (size_t)(rowstart[G] + sI) * 3 * JL + (rel - (sI << lgJL));
+        const double* Rt = R + (size_t)(rowstart[BAND ? G - G0 : G] + sI) * 3 * JL + (rel - (sI << lgJL));
         e0 += Rt[0];
         e1 += Rt[JL];
         e2 += Rt[2 * JL];
@@ -577,7 +587,7 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
         const double qk = q[kc];
         es = qk * ps;
         if (w == 0)
-            for (int t = rowstart[Gk] + off; t < rowstart[Gk + 1]; t += IB) es += Et[(size_t)t * W + wk];
+            for (int t = t0 + off; t < t1; t += IB) es += Et[(size_t)t * W + wk];
     }
     const double v[10] = {d0, d1, d2, p0, p1, p2, e0, e1, e2, es};
 #pragma unroll
@@ -593,10 +603,14 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
         tot[c] = a;
     }
     const double qk = q[k];
-    F[k] = kCoulomb * (tot[3] + qk * (tot[0] - tot[6]));
-    F[(size_t)n + k] = kCoulomb * (tot[4] + qk * (tot[1] - tot[7]));
-    F[2 * (size_t)n + k] = kCoulomb * (tot[5] + qk * (tot[2] - tot[8]));
-    if (POT) phi[k] = tot[NS - 1];
+    const bool add = BAND && G0 > 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double f = kCoulomb * (tot[3 + c] + qk * (tot[c] - tot[6 + c]));
+        double* Fk = F + (size_t)c * n + k;
+        *Fk = add ? *Fk + f : f;
+    }
+    if (POT) phi[k] = add ? phi[k] + tot[NS - 1] : tot[NS - 1];
 }
 
 }  // namespace cb
