@@ -162,10 +162,10 @@ cb_status coulomb_forces(int64_t n, const double* x, const double* y, const doub
  * process ends, so this call allocates nothing (no hipMalloc, no hipFree, no
  * allocating library routine).  n at most 2796202 (64 MiB over 24 bytes per
  * ion); larger n returns CB_ENOWS.  The configured Newton's-third-law stage
- * runs when its tiles fit in the array (up to about 32768 ions: the result
- * is then bitwise that of coulomb_forces), otherwise the all-pairs kernel
- * with as many j-splits as fit (the same forces up to summation order; small
- * n takes the one-launch evaluation of coulomb_forces and no scratch).
+ * runs when its partial sums fit in the array (up to about 32768 ions: the
+ * result is then bitwise that of coulomb_forces), otherwise the all-pairs
+ * kernel with as many j-splits as fit (the same forces up to summation order;
+ * small n takes the one-launch evaluation of coulomb_forces and no scratch).
  * Every call on one GPU shares that GPU's array: calls that overlap in time
  * on one GPU (other streams, other threads) race and give undefined results;
  * calls ordered on one stream are safe.  Nothing in the array needs to start
@@ -246,8 +246,7 @@ cb_status md_step(int64_t n, const cb_state* s, const double* q, const double* m
  * ..., for each run; every >= 1 then.
  * nrun = 1 runs the multi-workgroup step kernels (any n): one launch per
  * step for small runs, each workgroup evaluating whole rows of the pair sum
- * (algorithm 3 of cb_get_config), else a pair stage and an element-wise
- * launch.  nrun > 1 needs every run to hold at most 4096 ions
+ * (algorithm 3 of cb_get_config), else a pair stage and a finishing launch.  nrun > 1 needs every run to hold at most 4096 ions
  * (CB_EUNSUPPORTED otherwise) and takes, when its entry (configuration key
  * CB_OP_MD_ENSEMBLE) is forced or tuned, one of two ensemble paths:
  *  - algorithm 0: one persistent launch, one workgroup per run at a time,
@@ -307,12 +306,13 @@ const char* cb_last_error(void);
 
 /* Times the candidate launch configurations (i-particles per lane, workgroup
  * size, j-split count) of `op` at n ions and precision prec on the current
- * device (and, for small n, the one-launch evaluation of whole rows), keeps
- * the fastest for all later calls with n in the same power-of-two bucket, and, when cache_path is non-NULL, merges it into that
- * JSON-lines file.  For md_step / md_run at n <= 8192 the force kernel is
+ * device (and the path that an untuned entry takes, see cb_get_config), keeps
+ * the fastest for all later calls with n in the same power-of-two bucket, and,
+ * when cache_path is non-NULL, merges it into that JSON-lines file.  For md_step / md_run at n <= 8192 the force kernel is
  * tuned for coulomb_forces, and the better of its steps and the one-launch
- * step (algorithm 3) is kept for the md calls.  Uses synthetic inputs it allocates itself (this call, and
- * cb_load_tuning, are the only ones that allocate).  Synchronous. */
+ * step (algorithm 3) is kept for the md calls.  Uses synthetic inputs it
+ * allocates itself (this call, and cb_load_tuning, are the only ones that
+ * allocate).  Synchronous. */
 cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_path);
 
 /* Loads tuned configurations written by cb_autotune (missing file: CB_OK). */
@@ -335,12 +335,14 @@ cb_status cb_load_tuning(const char* cache_path);
  *          j-parts (algorithm 3; 1..32 are accepted, the launch's shape
  *          follows n alone),
  * out[4] = 1 if it came from tuning or cb_set_config.
- * While an entry was not set by cb_set_config, a call of at most 6144 ions
- * (forces, energy, gradient, md_step, md_run) evaluates whole rows in one
- * launch (as algorithm 3) in the place of the reported two; a tuned entry
- * does so where that was the faster.  An untuned entry beyond 2^18 ions runs
- * algorithm 4's tiles (p = 8, segments of 512) in bands whose partial sums
- * fit the workspace (forces, energy, gradient, md_step, md_run).
+ * An untuned entry of the forces, energy (and gradient), md_step or md_run
+ * takes, in the place of what is reported here: up to 6144 ions, whole rows of
+ * the pair sum per workgroup in one launch (as algorithm 3); up to 57344
+ * (except where the reported tiles fill the chip evenly), the
+ * Newton's-third-law pairs in equal shares per workgroup; beyond 2^18,
+ * algorithm 4's tiles (p = 8, segments of 512) in bands whose partial sums fit
+ * the workspace.  A tuned entry takes the first two where they were faster;
+ * an entry set by cb_set_config runs as set.
  * CB_EINVAL for a NULL out, n outside [1, 2^28], or an op or prec outside
  * its enum. */
 cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);

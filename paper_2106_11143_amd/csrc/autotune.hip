@@ -87,7 +87,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
     const int ps_force[] = {1, 2, 4}, ps_hvp[] = {1, 2};
     const int wgs[] = {64, 128, 256};
     const int splits[] = {1, 2, 4, 8, 16, 24, 32, 48, 64};
-    LaunchCfg best{0, 0, 0, 1, ALGO_DIRECT, 0, 0};
+    LaunchCfg best{0, 0, 0, 1, ALGO_DIRECT, PATH_CFG};
     float best_ms = 1e30f;
     cb_status rc = CB_OK;
     const int np = hv ? 2 : 3;
@@ -96,7 +96,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             for (int sp : splits) {
                 const int p = hv ? ps_hvp[ip] : ps_force[ip];
                 if (sp > 1 && n / sp < 64) continue;
-                LaunchCfg c{p, wg, sp, 1, ALGO_DIRECT, 0, 0};
+                LaunchCfg c{p, wg, sp, 1, ALGO_DIRECT, PATH_CFG};
                 const int jlen = split_len(n, sp);
                 auto launch = [&]() -> cb_status {
                     if (hv)
@@ -138,7 +138,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             for (int jl : kSymJL) {
                 if (rc) break;
                 if (algo == ALGO_SYM_ROWS && !sym_rows_p_ok(p)) continue;
-                LaunchCfg c{p, kSymGroup, jl, 1, algo, 0, 0};
+                LaunchCfg c{p, kSymGroup, jl, 1, algo, PATH_CFG};
                 auto launch = [&]() {
                     return launch_pair_sym(prec, c, (int)n, x, y, z, q, 0.0, sws.p, static_cast<double*>(F.p), st);
                 };
@@ -161,20 +161,22 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             }
         (void)hipStreamSynchronize(st);
     }
-    // forces and energy of at most kRowsForcesMaxN ions: the whole call with
-    // the best configuration (pair launch and epilogue) against the launch of
-    // whole rows, which the entry then takes if it is faster
-    if (rc == CB_OK && best.p != 0 && !hv && n <= kRowsForcesMaxN) {
+    // forces and energy at sizes that take whole rows or equal shares by
+    // default: the whole call with the best configuration (pair launch and
+    // epilogue) against that path, which the entry then takes if it is faster
+    const int alt = default_path(op, n);
+    if (rc == CB_OK && best.p != 0 && (alt == PATH_ROWS || alt == PATH_SHARES)) {
         DevBuf out, fws;
         const int cop = energy_only ? CB_OP_ENERGY : CB_OP_FORCES;
-        put_cfg(cop, n, prec, best);
+        best.path = alt;
+        put_cfg(cop, n, prec, best);  // (the workspace of either)
         const size_t need = cb_workspace_size(cop, n, 1, 1, prec);
         if (hipMalloc(&out.p, sizeof(double) * 3 * (size_t)n) != hipSuccess || hipMalloc(&fws.p, need) != hipSuccess)
             rc = fail(CB_EHIP, "cb_autotune: allocation failed");
         double* o = static_cast<double*>(out.p);
         float ms2[2] = {0.f, 0.f};
-        for (int rows = 0; rows < 2 && rc == CB_OK; ++rows) {
-            best.rows = rows;
+        for (int a = 0; a < 2 && rc == CB_OK; ++a) {
+            best.path = a ? alt : (int)PATH_CFG;
             put_cfg(cop, n, prec, best);
             auto launch = [&]() {
                 return energy_only ? coulomb_energy(n, x, y, z, q, 0.0, prec, o, fws.p, need, st)
@@ -189,23 +191,21 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
                 if (!rc) rc = fail(CB_EHIP, "cb_autotune: timing failed");
                 break;
             }
-            (void)hipEventElapsedTime(&ms2[rows], e0, e1);
+            (void)hipEventElapsedTime(&ms2[a], e0, e1);
         }
-        best.rows = rc == CB_OK && ms2[1] < ms2[0];
+        best.path = rc == CB_OK && ms2[1] < ms2[0] ? alt : (int)PATH_CFG;
         drop_cfg(cop, n, prec);
         (void)hipStreamSynchronize(st);
     }
     // md_step / md_run of at most kSmallRunMax ions: whole steps (md_run on
-    // the synthetic cloud at rest) of the two-launch step with the best force
-    // configuration and of the one-launch step; the faster is kept for the
-    // md calls.
+    // the synthetic cloud at rest) with the best force configuration, on equal
+    // shares and in one launch; the fastest is kept for the md calls.
     const bool md_op = (op == CB_OP_MD_STEP || op == CB_OP_MD_RUN);
     LaunchCfg md_best = best;
-    md_best.rows = 0;
     float md_ms = 1e30f;
     if (rc == CB_OK && md_op && n <= kSmallRunMax) {
         DevBuf state, mass, mws;
-        const size_t need = cb_workspace_size(CB_OP_MD_RUN, n, 1, 1, prec);
+        const size_t need = std::max(cb_workspace_size(CB_OP_MD_RUN, n, 1, 1, prec), share_ws_bytes(n, true));
         if (hipMalloc(&state.p, sizeof(double) * 9 * (size_t)n) != hipSuccess ||
             hipMalloc(&mass.p, sizeof(double) * (size_t)n) != hipSuccess || hipMalloc(&mws.p, need) != hipSuccess)
             rc = fail(CB_EHIP, "cb_autotune: allocation failed");
@@ -221,8 +221,10 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         tr.wz = 1.2566370614359172e6;
         const int64_t offs[2] = {0, n};
         std::vector<LaunchCfg> cands{best};
-        cands[0].rows = 0;  // the launches of its own shape
-        cands.push_back({1, 64, small_parts(n), 1, ALGO_SMALL, 0, 0});
+        cands[0].path = PATH_CFG;
+        cands.push_back(best);
+        cands[1].path = PATH_SHARES;
+        cands.push_back({1, 64, small_parts(n), 1, ALGO_SMALL, PATH_CFG});
         for (const LaunchCfg& c : cands) {
             if (rc) break;
             put_cfg(CB_OP_MD_RUN, n, prec, c);
@@ -274,8 +276,8 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         auto line = [&](int o, const LaunchCfg& c, float ms) {
             std::fprintf(f,
                          "{\"arch\": \"%s\", \"op\": %d, \"prec\": %d, \"bucket\": %d, \"n\": %lld, \"p\": %d, "
-                         "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"rows\": %d, \"ms\": %.6f}\n",
-                         arch_name().c_str(), o, prec, n_bucket(n), (long long)n, c.p, c.wg, c.splits, c.algo, c.rows,
+                         "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"path\": %d, \"ms\": %.6f}\n",
+                         arch_name().c_str(), o, prec, n_bucket(n), (long long)n, c.p, c.wg, c.splits, c.algo, c.path,
                          ms);
         };
         line(op, best, best_ms);
@@ -294,20 +296,22 @@ cb_status cb_load_tuning(const char* cache_path) {
 
     while (std::fgets(line, sizeof line, f)) {
         char a[64] = {0};
-        int op, prec, bucket, p, wg, sp, algo = 0, rows = 0;
+        int op, prec, bucket, p, wg, sp, algo = 0, path = PATH_CFG;
         long long n;
         if (std::sscanf(line,
                         "{\"arch\": \"%63[^\"]\", \"op\": %d, \"prec\": %d, \"bucket\": %d, \"n\": %lld, \"p\": %d, "
-                        "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"rows\": %d",
-                        a, &op, &prec, &bucket, &n, &p, &wg, &sp, &algo, &rows) < 8)
+                        "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"path\": %d",
+                        a, &op, &prec, &bucket, &n, &p, &wg, &sp, &algo, &path) < 8)
             continue;
         if (arch != a || op < 0 || op > CB_OP_ADJOINT || prec < 0 || prec > CB_MIXED_F32D || n < 1 ||
             n > kMaxIons)
             continue;
-        LaunchCfg c{p, wg, sp, 1, algo, 0, 0};
+        LaunchCfg c{p, wg, sp, 1, algo, PATH_CFG};
         if (!valid_cfg(op, c)) continue;
-        // (a file without the field, or a size the path does not take: 0)
-        if (rows == 1 && sym_op(op) && rows_op(op == CB_OP_ENERGY ? CB_OP_ENERGY : CB_OP_FORCES, n)) c.rows = 1;
+        // (a file without the field, or a path that op does not take at n: the configured launches)
+        if (sym_op(op) && (path == PATH_ROWS || path == PATH_SHARES) &&
+            (path == default_path(op, n) || (path == PATH_SHARES && n <= kSmallRunMax)))
+            c.path = path;
         if (op == CB_OP_FORCES || op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) {
             // as cb_autotune: a forces line also sets the md calls above
             // kSmallRunMax ions; an md line sets the md calls (and forces,
@@ -316,7 +320,7 @@ cb_status cb_load_tuning(const char* cache_path) {
             if (c.algo == ALGO_SMALL && n > kSmallRunMax) continue;
             if (c.algo != ALGO_SMALL) put_cfg(CB_OP_FORCES, n, prec, c);
             if (md_line || n > kSmallRunMax) {
-                c.rows = 0;  // (the forces' choice; the md calls' is ALGO_SMALL)
+                if (c.path == PATH_ROWS) c.path = PATH_CFG;  // (the forces' choice; the md calls' is ALGO_SMALL)
                 put_cfg(CB_OP_MD_STEP, n, prec, c);
                 put_cfg(CB_OP_MD_RUN, n, prec, c);
             }

@@ -86,12 +86,7 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
     LaunchCfg c;
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
-    // small runs and clouds: whole rows in one launch whatever is reported
-    // below (us per md_run step on MI355X, this / the two-launch step: 150
-    // ions 4.0 / 7.6, 1024 5.2 / 9.5, 2048 7.8 / 12.5, 4096 16.5 / 21.4, 6000
-    // 31.2 / 35.7, 8192 54.3 / 54.0)
-    c.rows = rows_op(op, n);
-    c.bands = sym_op(op) && n > kSymMaxN;
+    c.path = default_path(op, n);
     (void)prec;
     if (op == CB_OP_MD_ENSEMBLE) {
         // Stepped ensemble path (ensemble.hip).  While this entry is untuned,
@@ -140,10 +135,7 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
         c.splits = 128;
         return c;
     }
-    const int bands = c.bands;
-    c = direct_cfg(op, n, prec);
-    c.bands = bands;
-    return c;
+    return direct_cfg(op, n, prec);
 }
 
 // The all-pairs kernel's default shape for op at n.
@@ -151,8 +143,7 @@ LaunchCfg direct_cfg(int op, int64_t n, int prec) {
     LaunchCfg c;
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
-    c.rows = rows_op(op, n);
-    c.bands = 0;
+    c.path = default_path(op, n);
     (void)prec;
     c.wg = 64;
     c.p = 1;
@@ -258,8 +249,10 @@ WsLayout ws_layout(int op, int64_t n, int32_t nrun, int32_t nvec, int32_t prec) 
         size_t part = sizeof(double) * (size_t)kMaxSplits * 3 * (hv ? nv : 1) * N;
         const bool force_op = sym_op(op);
         LaunchCfg c = get_cfg(cfg_op, n, prec);
+        bool shares = force_op && c.path == PATH_SHARES;
         if (cfg_op == CB_OP_ENERGY) {  // coulomb_trap_grad: the forces' stage too
             const LaunchCfg f = get_cfg(CB_OP_FORCES, n, prec);
+            shares = shares || f.path == PATH_SHARES;
             if (is_sym(f.algo) && sym_cfg_ok(f.p, f.wg, f.splits) &&
                 (!is_sym(c.algo) || sym_ws_bytes(n, f.p, f.splits, true, sym_rows(f.algo)) >
                                         sym_ws_bytes(n, c.p, c.splits, true, sym_rows(c.algo))))
@@ -268,6 +261,7 @@ WsLayout ws_layout(int op, int64_t n, int32_t nrun, int32_t nvec, int32_t prec) 
         if (force_op && n <= kSymMaxN && is_sym(c.algo) && sym_cfg_ok(c.p, c.wg, c.splits))
             // the configured symmetric stage: finished forces [3][n] then its tiles and partials
             part = std::max(part, al(sizeof(double) * 3 * N) + sym_ws_bytes(n, c.p, c.splits, pot, sym_rows(c.algo)));
+        if (shares) part = std::max(part, share_ws_bytes(n, pot));
         if (hv && is_sym(c.algo) && hvp_sym_cfg_ok(c.p, c.splits))  // (the adjoint's product [3][n] first)
             part = std::max(part, (op == CB_OP_ADJOINT ? al(sizeof(double) * 3 * N) : 0) +
                                       hvp_sym_ws_bytes(n, c.p, c.splits, hvp_sym_passes((int)nv, c.wg)));
@@ -351,7 +345,7 @@ cb_status cb_set_config(int32_t op, int64_t n, int32_t prec, int32_t algo, int32
         drop_cfg(op, n, prec);
         return ok();
     }
-    LaunchCfg c{p, wg, splits, 1, algo, 0, 0};
+    LaunchCfg c{p, wg, splits, 1, algo, PATH_CFG};
     const bool hv_op = (op == CB_OP_HVP || op == CB_OP_ADJOINT);
     if (!valid_cfg(op, c) || (is_sym(algo) && op != CB_OP_MD_ENSEMBLE && !hv_op && n > kSymMaxN) ||
         (is_sym(algo) && hv_op && n > hvp_sym_max_n(p)) || (algo == ALGO_SMALL && n > kSmallRunMax))

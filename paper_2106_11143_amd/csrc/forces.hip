@@ -75,9 +75,9 @@ static PairRun plan(int op, int64_t n, int prec) {
 
 static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Whether an evaluation of n ions takes the Newton's-third-law stage in bands.
-static bool takes_bands(int op, int64_t n, int prec) {
-    return prec != CB_MIXED_F32D && get_cfg(op, n, prec).bands;
+// The path of an evaluation of n ions.
+static int path_of(int op, int64_t n, int prec) {
+    return prec != CB_MIXED_F32D ? get_cfg(op, n, prec).path : (int)PATH_CFG;
 }
 
 // The pair stage with the configured algorithm: forces, and the potential
@@ -104,7 +104,7 @@ static cb_status force_stage(int op, int prec, int64_t n, const double* x, const
         if (tiles_ready && rc == CB_OK) *tiles_ready = true;
         return rc;
     }
-    if (bands && takes_bands(op, n, prec)) {
+    if (bands && path_of(op, n, prec) == PATH_BANDS) {
         *S_out = 1;
         *prescaled = true;
         const size_t fbytes = al256(sizeof(double) * 3 * (size_t)n);
@@ -117,9 +117,22 @@ static cb_status force_stage(int op, int prec, int64_t n, const double* x, const
     return launch_pair(prec, pr.cfg, true, pot, (int)n, x, y, z, q, eps2, pr.jlen, part, ppot, st);
 }
 
-// Whether an evaluation of n ions takes whole rows per workgroup (rows.hip).
-static bool takes_rows(int op, int64_t n, int prec) {
-    return prec != CB_MIXED_F32D && get_cfg(op, n, prec).rows;
+// Whether the evaluation of op (forces, gradient, with u_out the energy) takes
+// whole rows or equal shares: then it is enqueued here, with ws holding what
+// ws_layout gave the call (shares) or 3 doubles per workgroup (rows), and its
+// status goes to *rc.
+static bool evaluated(int op, int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
+                      const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
+                      double* u_out, void* ws, hipStream_t st, cb_status* rc) {
+    const int path = path_of(op, n, prec);
+    if (path == PATH_ROWS)
+        *rc = rows_forces(prec, n, x, y, z, q, m, k, eps2, mode, fx, fy, fz, u_out, ws, st);
+    else if (path == PATH_SHARES)
+        *rc = share_forces(prec, n, x, y, z, q, m, k, eps2, mode, fx, fy, fz, u_out, ws, st);
+    else
+        return false;
+    if (*rc == CB_OK) ok();
+    return true;
 }
 
 // ------------------------------------------- allocation-free forces
@@ -167,9 +180,12 @@ static cb_status md_single(int64_t n, const cb_state* s, const double* q, const 
                            double* energies, int64_t every, void* ws, int op, hipStream_t st) {
     const WsLayout L = ws_layout(op, n, 1, 1, prec);
     const LaunchCfg sc = get_cfg(op, n, prec);
-    if ((sc.rows || sc.algo == ALGO_SMALL) && n <= kSmallRunMax)
+    if (sc.path == PATH_ROWS || (sc.algo == ALGO_SMALL && n <= kSmallRunMax))
         return md_run_rows(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, every > 0 ? energies : nullptr, every,
                            static_cast<char*>(ws) + L.part, L.ppot - L.part, st);
+    if (sc.path == PATH_SHARES)
+        return md_run_shares(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, every > 0 ? energies : nullptr,
+                             every, static_cast<char*>(ws) + L.part, st);
     const PairRun pr = plan(op, n, prec);
     double* part = at(ws, L.part);
     double* ppot = at(ws, L.ppot);
@@ -226,7 +242,7 @@ static cb_status md_single(int64_t n, const cb_state* s, const double* q, const 
     // potential alone (an energy record of step 0 without CB_INIT_ACCEL) takes
     // the symmetric stage too when it is configured (its forces unused), else
     // the direct kernel's potential-only pass.
-    const bool sym_stage = (is_sym(get_cfg(op, n, prec).algo) && n <= kSymMaxN) || takes_bands(op, n, prec);
+    const bool sym_stage = (is_sym(get_cfg(op, n, prec).algo) && n <= kSymMaxN) || sc.path == PATH_BANDS;
     // the symmetric stage's tile table is the same at every step: built by
     // the first force stage of the run, read by the later ones
     bool plan_ready = false;
@@ -318,11 +334,9 @@ cb_status coulomb_forces(int64_t n, const double* x, const double* y, const doub
     if (overlaps(fx, fy, n) || overlaps(fx, fz, n) || overlaps(fy, fz, n))
         return fail(CB_EINVAL, "coulomb_forces: outputs overlap");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (takes_rows(CB_OP_FORCES, n, prec)) {
-        rc = rows_forces(prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, EPI_FORCES, fx, fy, fz, nullptr,
-                         nullptr, st);
-        return rc ? rc : ok();
-    }
+    if (evaluated(CB_OP_FORCES, prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, EPI_FORCES, fx, fy, fz,
+                  nullptr, at(ws, L.part), st, &rc))
+        return rc;
     int S = 0;
     bool prescaled = false;
     if ((rc = force_stage(CB_OP_FORCES, prec, n, x, y, z, q, eps2, ws, L, st, &S, &prescaled))) return rc;
@@ -358,13 +372,13 @@ cb_status coulomb_forces_noalloc(int64_t n, const double* x, const double* y, co
     if (overlaps(fx, fy, n) || overlaps(fx, fz, n) || overlaps(fy, fz, n))
         return fail(CB_EINVAL, "coulomb_forces_noalloc: outputs overlap");
     cb_status rc = CB_OK;
-    if (takes_rows(CB_OP_FORCES, n, prec)) {  // needs no partial sums
-        rc = rows_forces(prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, EPI_FORCES, fx, fy, fz, nullptr,
-                         nullptr, static_cast<hipStream_t>(stream));
-        return rc ? rc : ok();
-    }
-    void* ws = scratch_addr(&rc);
-    if (!ws) return rc;
+    const int path = path_of(CB_OP_FORCES, n, prec);
+    void* ws = nullptr;
+    if (path != PATH_ROWS && !(ws = scratch_addr(&rc))) return rc;  // (whole rows need no partial sums)
+    if ((path == PATH_ROWS || (path == PATH_SHARES && share_ws_bytes(n, false) <= kScratchBytes)) &&
+        evaluated(CB_OP_FORCES, prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, EPI_FORCES, fx, fy, fz, nullptr,
+                  ws, static_cast<hipStream_t>(stream), &rc))
+        return rc;
     unsigned* fl = flags_ptr();
     if (!fl) return fail(CB_EHIP, "coulomb_forces_noalloc: device flag symbol not found");
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -480,17 +494,15 @@ cb_status coulomb_energy(int64_t n, const double* x, const double* y, const doub
     if (prec == CB_MIXED_F32D) return fail(CB_EUNSUPPORTED, "coulomb_energy: CB_MIXED_F32D is for the forces only");
     if (!x || !y || !z || !q || !u_out) return fail(CB_EINVAL, "coulomb_energy: NULL argument");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (takes_rows(CB_OP_ENERGY, n, prec)) {
-        rc = rows_forces(prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, 0u, nullptr, nullptr, nullptr, u_out,
-                         at(ws, L.part), st);
-        return rc ? rc : ok();
-    }
+    if (evaluated(CB_OP_ENERGY, prec, n, x, y, z, q, nullptr, TrapK{0.0, 0.0, 0.0}, eps2, 0u, nullptr, nullptr, nullptr,
+                  u_out, at(ws, L.part), st, &rc))
+        return rc;
     double* ppot = at(ws, L.ppot);
     double* eblk = at(ws, L.eblk);
     int S = 0;
     bool share = false;  // the potential partials hold energy shares (the symmetric stage)
     const LaunchCfg ecfg = get_cfg(CB_OP_ENERGY, n, prec);
-    if ((is_sym(ecfg.algo) && n <= kSymMaxN) || ecfg.bands) {
+    if ((is_sym(ecfg.algo) && n <= kSymMaxN) || ecfg.path == PATH_BANDS) {
         // the Newton's-third-law stage with the potential as a fourth
         // component (its forces are a by-product, left in the workspace)
         bool prescaled = false;
@@ -541,11 +553,10 @@ cb_status coulomb_trap_grad(int64_t n, const double* x, const double* y, const d
     for (auto o : outs)
         if (u_out && overlaps2(o, n, u_out, 1)) return fail(CB_EINVAL, "coulomb_trap_grad: u_out aliases an output");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (takes_rows(u_out ? CB_OP_ENERGY : CB_OP_FORCES, n, prec)) {
-        rc = rows_forces(prec, n, x, y, z, q, m, m ? trap_k(*trap, t) : TrapK{0.0, 0.0, 0.0}, eps2,
-                         want_g ? EPI_GRAD : 0u, gx, gy, gz, u_out, at(ws, L.part), st);
-        return rc ? rc : ok();
-    }
+    if (evaluated(u_out ? CB_OP_ENERGY : CB_OP_FORCES, prec, n, x, y, z, q, m,
+                  m ? trap_k(*trap, t) : TrapK{0.0, 0.0, 0.0}, eps2, want_g ? EPI_GRAD : 0u, gx, gy, gz, u_out,
+                  at(ws, L.part), st, &rc))
+        return rc;
     EpiParams E{};
     E.n = (int)n;
     E.q = q;

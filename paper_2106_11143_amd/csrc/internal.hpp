@@ -10,6 +10,8 @@
 
 namespace cb {
 
+struct TrapK;  // step_common.hpp
+
 constexpr int kMaxSplits = 64;       // j-splits per launch
 constexpr int kMaxVec = 8;           // HVP vectors per call
 constexpr int kMaxBatchIons = 4096;  // ions per run in the batched kernel (LDS bound)
@@ -27,8 +29,8 @@ constexpr int kEpiMinIons = kEpiBlock / 16;  // ions per block of the widest epi
 constexpr int epi_parts(int64_t n, int S) { return n > 8192 ? 1 : (S >= 32 ? 16 : (S >= 16 ? 8 : 1)); }
 constexpr int64_t kMaxIons = int64_t(1) << 28;  // largest n any entry point accepts
 constexpr int64_t kSymMaxN = int64_t(1) << 18;  // largest n for the symmetric kernel (partials grow as n^2)
-constexpr int64_t kRowsMaxN = 6144;        // largest run of the one-launch step by default (rows.hip)
-constexpr int64_t kRowsForcesMaxN = 6144;  // and of the one-launch forces, gradient and energy
+constexpr int64_t kRowsMaxN = 6144;     // largest n that takes whole rows per workgroup by default (rows.hip)
+constexpr int64_t kSharesMaxN = 57344;  // and equal shares of the pairs (shares.hip)
 constexpr int kMaxDevices = 64;      // GPUs per process the per-device symbol tables hold
 
 // ALGO_SYM and ALGO_SYM_LDS differ only in how the per-j reactions are summed
@@ -38,6 +40,11 @@ constexpr int kMaxDevices = 64;      // GPUs per process the per-device symbol t
 // ALGO_SMALL (md_step / md_run of one run of at most kSmallRunMax ions):
 // one launch per step, every pair direct (md_run_rows).
 enum : int { ALGO_DIRECT = 0, ALGO_SYM = 1, ALGO_SYM_LDS = 2, ALGO_SMALL = 3, ALGO_SYM_ROWS = 4 };
+
+// What an entry's calls take: the launches of its algorithm and shape, or
+// whole rows per workgroup (rows.hip), equal shares of the pairs (shares.hip)
+// or the Newton's-third-law stage in bands (pair_sym.hip).
+enum : int { PATH_CFG = 0, PATH_ROWS = 1, PATH_SHARES = 2, PATH_BANDS = 3 };
 
 constexpr bool is_sym(int algo) { return algo == ALGO_SYM || algo == ALGO_SYM_LDS || algo == ALGO_SYM_ROWS; }
 
@@ -93,8 +100,7 @@ struct LaunchCfg {
     int splits;  // direct: requested j-splits; symmetric: segment length JL
     int tuned;   // 1 if set by tuning or cb_set_config
     int algo;    // ALGO_DIRECT, ALGO_SYM or ALGO_SYM_LDS
-    int rows;    // 1: one launch of whole rows (rows.hip) in the place of the above (untuned or tuned, never forced)
-    int bands;   // 1: the Newton's-third-law stage in bands (untuned entries beyond kSymMaxN)
+    int path;    // PATH_CFG, or the path taken in its place (untuned entries, or a tuned one that was faster so)
 };
 
 struct WsLayout {
@@ -129,10 +135,27 @@ class HostUpload {
 };
 
 int n_bucket(int64_t n);
-// Whether op at n may take whole rows per workgroup.
-constexpr bool rows_op(int op, int64_t n) {
-    return (op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) ? n <= kRowsMaxN
-                                                       : (op == CB_OP_FORCES || op == CB_OP_ENERGY) && n <= kRowsForcesMaxN;
+// Whether the one-wave 512 x 512 tiles that are configured from 32768 ions
+// fill the 1024 SIMDs evenly (96% of the waves of their last round): then they
+// beat equal shares, which else win (us per evaluation on MI355X, tiles /
+// shares: 32768 ions, 2016 tiles, 408 / 410; 39900, 3003, 583 / 587; 46592, 4095,
+// 760 / 784; 56832, 6105, 1121 / 1152; but 39424, 2926, 581 / 575; 33500, 2080,
+// 548 / 426; 49152, 4560, 906 / 865).
+constexpr bool tiles_fit(int64_t n) {
+    const int64_t r = (n + 511) / 512, T = r * (r - 1) / 2, rounds = (T + 1023) / 1024;
+    return n >= 32768 && 100 * T >= 96 * 1024 * rounds;
+}
+
+// The path of an untuned entry (us per md_run step on MI355X, rows / pair
+// launch and epilogue: 150 ions 4.0 / 7.6, 1024 5.2 / 9.5, 2048 7.8 / 12.5,
+// 4096 16.5 / 21.4, 6000 31.2 / 35.7, 8192 54.3 / 54.0; us per force
+// evaluation, shares / configured: 7000 ions 37.6 / 39.4 (6144: rows 30.4),
+// 8192 43.4 / 48.5, 12001 71.7 / 104, 16000 114 / 181, 20001 168 / 210, 24577 240 /
+// 243, 27999 307 / 309, 30000 348 / 371, 33500 426 / 548, 40000 588 /
+// 714, 49152 865 / 906, 57344 1161 / 1239, 65536 1490 / 1485).
+constexpr int default_path(int op, int64_t n) {
+    if (op != CB_OP_FORCES && op != CB_OP_ENERGY && op != CB_OP_MD_STEP && op != CB_OP_MD_RUN) return PATH_CFG;
+    return n <= kRowsMaxN ? PATH_ROWS : n <= kSharesMaxN && !tiles_fit(n) ? PATH_SHARES : n > kSymMaxN ? PATH_BANDS : PATH_CFG;
 }
 LaunchCfg default_cfg(int op, int64_t n, int prec);
 LaunchCfg direct_cfg(int op, int64_t n, int prec);
@@ -188,6 +211,17 @@ cb_status launch_pair_sym_bands(int prec, int n, const double* x, const double* 
                                 double eps2, void* ws, size_t ws_bytes, double* F, hipStream_t st,
                                 double* phi = nullptr);
 
+// Forces, gradient (with u_out the energy) and md steps of n ions on equal shares
+// of the pairs (shares.hip); arguments as rows_forces and md_run_rows, ws:
+// share_ws_bytes(n, pot) bytes, pot: with the energy or records.
+size_t share_ws_bytes(int64_t n, bool pot);
+cb_status share_forces(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
+                    const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
+                    double* u_out, void* ws, hipStream_t st);
+cb_status md_run_shares(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,
+                    double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags, double* energies,
+                    int64_t every, void* ws, hipStream_t st);
+
 // Launches of the pair kernels (pair.hip).  The _range form evaluates the
 // forces / potentials of the ions i0 .. i0 + ni - 1 only (partials indexed by
 // i - i0); launch_pair is the whole range.
@@ -224,11 +258,9 @@ cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const doubl
                       double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags, double* energies,
                       int64_t every, void* ws, size_t ws_bytes, hipStream_t st);
 
-// Forces (mode EPI_FORCES) or gradient (EPI_GRAD) of n <= kRowsForcesMaxN
-// ions in one launch, and with u_out the energy U_C (+ U_trap with m) in a
-// second; ws: rows_forces_ws_bytes(n) bytes, used with u_out only.
-struct TrapK;
-size_t rows_forces_ws_bytes(int64_t n);
+// Forces (mode EPI_FORCES) or gradient (EPI_GRAD) of n ions in one launch,
+// and with u_out the energy U_C (+ U_trap with m) in a second; ws (with u_out
+// only): 3 doubles per workgroup of 4 ions or more.
 cb_status rows_forces(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
                       const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
                       double* u_out, void* ws, hipStream_t st);

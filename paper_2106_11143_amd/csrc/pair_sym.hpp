@@ -118,46 +118,33 @@ __device__ __forceinline__ void load_group(JGroupT<WQ>& g, int jg, int last, con
     }
 }
 
-// Minimum and maximum of a and b over the wave (every lane gets them).
-__device__ __forceinline__ void wave_minmax(double& lo, double& hi) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, o));
-        hi = fmax(hi, __shfl_xor(hi, o));
-    }
+// The value of lane 0 (uniform).
+__device__ __forceinline__ double uniform_lane0(double v) {
+    return pack_d(__builtin_amdgcn_readfirstlane(lo_u(v)), __builtin_amdgcn_readfirstlane(hi_u(v)));
 }
 
 // Whether every ion of an i-block (the lane's P charges) and every ion of
-// the j range [j0, j1) carry one charge each, and those charges (qI, qJ):
-// the tile is then one of the paper's single-species N-body sub-problems
-// (section 2), and its pair loop needs no per-pair charge.  Wave-uniform.
-// A non-finite charge anywhere makes the answer false (the general loop then
-// carries it into the forces).
+// the j range [j0, j1), j1 > j0, carry one charge each, and those charges
+// (qI, qJ): the tile is then one of the paper's single-species N-body
+// sub-problems (section 2), and its pair loop needs no per-pair charge.
+// Wave-uniform.  A non-finite charge anywhere makes the answer false (the
+// general loop then carries it into the forces).
 template <int P>
 __device__ __forceinline__ bool tile_charges(const double (&qi)[P], const double* __restrict__ q, int j0, int j1,
                                              double& qI, double& qJ) {
-    double ilo = qi[0], ihi = qi[0];
-    bool fin = __builtin_isfinite(qi[0]);
+    // every charge against the first of its side: one ballot, no reduction
+    // (the first 64 j's charges are requested ahead of the others' wait)
+    const int jl = j0 + (int)__lane_id();
+    const double v = q[min(jl, j1 - 1)];
+    const double q0 = uniform_lane0(qi[0]), q1 = q[j0];
+    bool one = __builtin_isfinite(q0) && __builtin_isfinite(q1);
 #pragma unroll
-    for (int p = 1; p < P; ++p) {
-        ilo = fmin(ilo, qi[p]);
-        ihi = fmax(ihi, qi[p]);
-        fin = fin && __builtin_isfinite(qi[p]);
-    }
-    double jlo = qi[0], jhi = qi[0];  // any finite placeholder: j1 > j0 in every tile
-    if (j1 > j0) jlo = jhi = q[j0];
-    for (int j = j0 + (int)__lane_id(); j < j1; j += 64) {
-        const double v = q[j];
-        jlo = fmin(jlo, v);
-        jhi = fmax(jhi, v);
-        fin = fin && __builtin_isfinite(v);
-    }
-    wave_minmax(ilo, ihi);
-    wave_minmax(jlo, jhi);
-    const bool all_fin = __builtin_amdgcn_ballot_w64(!fin) == 0;
-    qI = ilo;
-    qJ = jlo;
-    return all_fin && ilo == ihi && jlo == jhi;
+    for (int p = 0; p < P; ++p) one &= qi[p] == q0;
+    one &= v == q1;
+    for (int j = jl + 64; j < j1; j += 64) one &= q[j] == q1;
+    qI = q0;
+    qJ = q1;
+    return __builtin_amdgcn_ballot_w64(!one) == 0;
 }
 
 // The pairs of one group (only its first `live` j's when TAIL): i sums into
@@ -169,14 +156,16 @@ __device__ __forceinline__ bool tile_charges(const double (&qi)[P], const double
 // (no charge load, no charge multiply); the i sums are scaled by qI qJ when
 // stored and the reactions by rscale = qI here, so that the partials hold
 // what the general loop stores.
+// DIAG: the j's lie in the lane's own i-block (ion i0 + 64 p + lane of lane's
+// p-th): only the pairs j > i count.
 // POT: the pair energies too, into one sum per lane, pe += q_i q_j r^-1
 // (r^-1 when UNI), from r^-1 = r^2 r^-3: one or two operations per pair and
 // no reaction (each unordered pair's energy is counted once, here).
-template <int PREC, int P, int RED, bool TAIL, bool UNI, bool POT>
+template <int PREC, int P, int RED, bool TAIL, bool UNI, bool POT, bool DIAG = false>
 __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int live, int j0, int JL, double eps2,
                                           const double (&xi)[P], const double (&yi)[P], const double (&zi)[P],
                                           const double (&qi)[P], double (&ia)[P][3], double& pe, const SeriesK& K,
-                                          double rscale, double* __restrict__ Rt, double* __restrict__ red) {
+                                          double rscale, double* __restrict__ Rt, double* __restrict__ red, int i0 = 0) {
     double jv[3 * kGroupJ];  // this lane's share of each reaction: sum over its P ions of q_i d r^-3
 #pragma unroll
     for (int u = 0; u < kGroupJ; ++u) {
@@ -188,6 +177,7 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
             const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
             double s = sym_s<PREC>(r2, UNI ? 1.0 : qi[p], K);  // r^-3 (UNI) or q_i r^-3
             if (TAIL && u >= live) s = 0.0;
+            if (DIAG && jg + u <= i0 + p * 64 + (int)(threadIdx.x & 63)) s = 0.0;
             double sq = s;
             if constexpr (!UNI) sq = s * jd.q[u];  // q_i q_j r^-3
             ia[p][0] = __builtin_fma(dx, sq, ia[p][0]);

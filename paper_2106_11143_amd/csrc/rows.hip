@@ -6,6 +6,7 @@
 #include <numeric>
 #include <vector>
 
+#include "energy_record.hpp"
 #include "internal.hpp"
 #include "rows.hpp"
 #include "step_ion.hpp"
@@ -29,44 +30,6 @@ struct RowParams {
     int nprev;
     unsigned* flags;
 };
-
-// Sums nb workgroups' energy terms [nb][3] in a fixed order (each thread's
-// strided share, a butterfly over each wave, the waves in wave order) into
-// out: with what = REC_ALL, out[0..3] = K, U_C, U_trap, E; with REC_UC, U_C;
-// with REC_UPOT, U_C + U_trap.  Every thread of the workgroup calls it.
-template <int W>
-__device__ __forceinline__ void rows_record(int nb, const double* __restrict__ eblk, double* __restrict__ out,
-                                            int what) {
-    __shared__ double sh[W][3];
-    double e[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nb; b += 64 * W)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) e[c] += eblk[(size_t)b * 3 + c];
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) e[c] += __shfl_xor(e[c], o);
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) sh[threadIdx.x >> 6][c] = e[c];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < W; ++w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) e[c] += sh[w][c];
-        if (what == REC_UC) {
-            out[0] = e[1];
-        } else if (what == REC_UPOT) {
-            out[0] = e[1] + e[2];
-        } else {
-            out[0] = e[0];
-            out[1] = e[1];
-            out[2] = e[2];
-            out[3] = e[0] + e[1] + e[2];
-        }
-    }
-}
 
 // The workgroup's energy sums (the I ions' terms in its first I threads) to
 // eblk[blockIdx.x].
@@ -123,13 +86,7 @@ __global__ void __launch_bounds__(64 * W, (rows_waves<PREC, I, POT>())) k_rows_s
     if (!P.eprev || blockIdx.x != gridDim.x - 1)
         rows_step_block<PREC, I, W, POT>(P);
     else
-        rows_record<W>(P.nprev, P.eprev, P.eprev_out, REC_ALL);
-}
-
-template <int W>
-__global__ void __launch_bounds__(64 * W) k_rows_record(int nb, const double* __restrict__ eblk,
-                                                       double* __restrict__ out, int what) {
-    rows_record<W>(nb, eblk, out, what);
+        energy_record<W>(P.nprev, P.eprev, P.eprev_out, REC_ALL);
 }
 
 // ------------------------------------------------- forces, gradient, energy
@@ -231,7 +188,7 @@ __global__ void __launch_bounds__(64 * W) k_rows_ens_record(const int2* __restri
                                                            const double* __restrict__ eblk, long long nrec,
                                                            long long rec, double* __restrict__ energies) {
     const int2 ru = runs[blockIdx.x];  // its first chunk, its chunks
-    rows_record<W>(ru.y, eblk + (size_t)ru.x * 3, energies + ((size_t)blockIdx.x * nrec + rec) * 4,
+    energy_record<W>(ru.y, eblk + (size_t)ru.x * 3, energies + ((size_t)blockIdx.x * nrec + rec) * 4,
                    REC_ALL);
 }
 
@@ -350,9 +307,10 @@ cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const doubl
     };
     cb_status rc = rows_steps(nsteps, (flags & CB_INIT_ACCEL) != 0, energies != nullptr, every, launch);
     if (rc) return rc;
-    if (pend) {
-        k_rows_record<4><<<1, 256, 0, st>>>(nb, pend, pend_out, REC_ALL);
-        if ((rc = check_launch("k_rows_record"))) return rc;
+    if (pend) {  // the last record, in the order of the launches' extra workgroups
+        if (rows_small(n)) k_energy_record<8><<<1, 512, 0, st>>>(nb, pend, pend_out, REC_ALL);
+        else k_energy_record<4><<<1, 256, 0, st>>>(nb, pend, pend_out, REC_ALL);
+        if ((rc = check_launch("k_energy_record"))) return rc;
     }
     return ok();
 }
@@ -370,8 +328,6 @@ static void go_rows_forces_shape(const RowForceParams& P, unsigned g, hipStream_
     if (rows_small(P.n)) go_rows_forces<PREC, 4, 8>(P, g, st);
     else go_rows_forces<PREC, 8, 4>(P, g, st);
 }
-
-size_t rows_forces_ws_bytes(int64_t n) { return al(sizeof(double) * 3 * (size_t)rows_blocks(n)); }
 
 cb_status rows_forces(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
                       const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
@@ -397,8 +353,8 @@ cb_status rows_forces(int prec, int64_t n, const double* x, const double* y, con
     }
     cb_status rc = check_launch("k_rows_forces");
     if (rc || !u_out) return rc;
-    k_rows_record<4><<<1, 256, 0, st>>>(nb, P.eblk, u_out, REC_UPOT);
-    return check_launch("k_rows_record");
+    k_energy_record<4><<<1, 256, 0, st>>>(nb, P.eblk, u_out, REC_UPOT);
+    return check_launch("k_energy_record");
 }
 
 // Ions per workgroup of an ensemble's launch.

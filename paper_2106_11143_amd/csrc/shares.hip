@@ -1,0 +1,348 @@
+// Forces, gradients and velocity-Verlet steps of one run on equal shares of
+// its Newton's-third-law pairs (shares.hpp): a pair launch and a launch that
+// finishes each ion.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "energy_record.hpp"
+#include "internal.hpp"
+#include "shares.hpp"
+#include "step_ion.hpp"
+
+namespace cb {
+
+struct ShareStep {
+    int n;
+    ShareCut cut;  // k_share_pairs'
+    const double *Pi, *R, *Et;
+    double *x, *y, *z;     // positions (a drift moves them in place)
+    double *xn, *yn, *zn;  // = x, y, z
+    const double *q, *m;   // m NULL: no trap term (EPI_GRAD)
+    double *vx, *vy, *vz, *ax, *ay, *az;
+    double *fx, *fy, *fz;  // EPI_FORCES, EPI_GRAD
+    TrapK k;
+    double gamma, dt;
+    unsigned mode;
+    double* eblk;  // [workgroups][3] energy sums (EPI_ENERGY)
+    const double* eprev;  // an earlier record's sums, added by one extra workgroup into eprev_out
+    double* eprev_out;
+    int nprev;
+    unsigned* flags;
+};
+
+// 64 ions of one block per workgroup: wave w adds the w-th part of the ions'
+// i sums (the shares of their row) and of their reactions (the rows above and its own),
+// wave 0 the waves' parts in order; then forces, gradient, or trap, kick and
+// drift as the mode says.  The partials were just written by other CUs:
+// several are in flight per wave.
+constexpr int kFinWaves = 8, kFinPi = 3, kFinR = 6;
+
+template <bool POT>
+__global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
+    __shared__ double red[kFinWaves][6][64];
+    if (S.eprev && blockIdx.x == gridDim.x - 1) {
+        energy_record<kFinWaves>(S.nprev, S.eprev, S.eprev_out, REC_ALL);
+        return;
+    }
+    const ShareCut& cut = S.cut;
+    const int IB = cut.IB;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k0 = blockIdx.x * 64, k = k0 + lane, kc = min(k, S.n - 1);
+    const int B = k0 / IB, off = kc - B * IB;
+    const unsigned mode = S.mode;
+    const bool own = w == 0 && k < S.n;
+    const bool step =
+        (mode & (EPI_ACCEL | EPI_KICK | EPI_DRIFT)) || ((mode & EPI_ENERGY) && !(mode & (EPI_GRAD | EPI_UPOT)));
+    // the row's slots: its shares, each at slot share + row
+    const int u0 = row_unit(cut, B);
+    const int s0 = unit_share(cut, u0) + B, s1 = unit_share(cut, u0 + row_units(cut, B) - 1) + B + 1;
+    IonState s{};
+    double x = 0.0, y = 0.0, z = 0.0, qk = 0.0;
+    if (own) {
+        qk = S.q[k];
+        if (step || S.m) {
+            x = S.x[k];
+            y = S.y[k];
+            z = S.z[k];
+        }
+        if (step) s = load_ion(S, k);
+        else if (S.m) s.m = S.m[k];
+    }
+    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (mode & (EPI_ACCEL | EPI_KICK | EPI_FORCES | EPI_GRAD)) {
+        // part w of the row's slots [s0, s1) and of the rows 0 .. B, kFinPi and
+        // kFinR of them requested together
+        auto part = [&](int a, int b, int& lo, int& hi) {
+            const int len = (b - a + kFinWaves - 1) / kFinWaves;
+            lo = min(b, a + w * len);
+            hi = min(b, lo + len);
+        };
+        int tp, tpe, tr, tre;
+        part(s0, s1, tp, tpe);
+        part(0, B + 1, tr, tre);
+        for (; tp < tpe || tr < tre; tp += kFinPi, tr += kFinR) {
+            double d[kFinPi][3], e[kFinR][3];
+#pragma unroll
+            for (int i = 0; i < kFinPi; ++i) {
+                const double* p = S.Pi + (size_t)max(s0, min(tp + i, tpe - 1)) * 3 * IB + off;
+                d[i][0] = p[0];
+                d[i][1] = p[IB];
+                d[i][2] = p[2 * IB];
+            }
+#pragma unroll
+            for (int i = 0; i < kFinR; ++i) {
+                const int I = max(0, min(tr + i, tre - 1)), stride = row_units(cut, I) * kShareJ;
+                const double* p = S.R + (size_t)3 * row_unit(cut, I) * kShareJ + (kc - I * IB);
+                e[i][0] = p[0];
+                e[i][1] = p[stride];
+                e[i][2] = p[2 * (size_t)stride];
+            }
+#pragma unroll
+            for (int i = 0; i < kFinPi; ++i)
+                if (tp + i < tpe)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) v[c] += d[i][c];
+#pragma unroll
+            for (int i = 0; i < kFinR; ++i)
+                if (tr + i < tre)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) v[3 + c] += e[i][c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) red[w][c][lane] = v[c];
+    __syncthreads();
+    if (w != 0) return;
+#pragma unroll
+    for (int u = 1; u < kFinWaves; ++u)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[c] += red[u][c][lane];
+    double eK = 0.0, eC = 0.0, eT = 0.0;
+    if (own) {
+        const double Fx = kCoulomb * (v[0] - qk * v[3]);
+        const double Fy = kCoulomb * (v[1] - qk * v[4]);
+        const double Fz = kCoulomb * (v[2] - qk * v[5]);
+        bool ok = true;
+        if (mode & EPI_FORCES) {
+            S.fx[k] = Fx;
+            S.fy[k] = Fy;
+            S.fz[k] = Fz;
+            ok = finite3(Fx, Fy, Fz);
+        } else if (step) {
+            step_ion(S, S.k, S.gamma, k, s, x, y, z, qk, Fx, Fy, Fz, 0.0, eK, eC, eT);
+        } else {
+            if (mode & EPI_GRAD) {
+                const double gx = __builtin_fma(s.m * S.k.kx, x, -Fx);
+                const double gy = __builtin_fma(s.m * S.k.ky, y, -Fy);
+                const double gz = __builtin_fma(s.m * S.k.kz, z, -Fz);
+                S.fx[k] = gx;
+                S.fy[k] = gy;
+                S.fz[k] = gz;
+                ok = finite3(gx, gy, gz);
+            }
+            if (POT) eT = 0.5 * s.m * (S.k.kx * x * x + S.k.ky * y * y + S.k.kz * z * z);
+        }
+        if (POT) {
+            // each share of the block's row gives its pair energy to one ion
+            eC = 0.0;
+            for (int t = s0 + off; t < s1; t += IB) eC += S.Et[t];
+            eC *= kCoulomb;
+            ok = ok && __builtin_isfinite(eC) && __builtin_isfinite(eT);
+        }
+        if (!ok) atomicOr(S.flags, 1u);
+    }
+    if (POT) {
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            eK += __shfl_xor(eK, d);
+            eC += __shfl_xor(eC, d);
+            eT += __shfl_xor(eT, d);
+        }
+        if (lane == 0) {
+            S.eblk[(size_t)blockIdx.x * 3 + 0] = eK;
+            S.eblk[(size_t)blockIdx.x * 3 + 1] = eC;
+            S.eblk[(size_t)blockIdx.x * 3 + 2] = eT;
+        }
+    }
+}
+
+// ----------------------------------------------------------------- host
+
+static size_t al(size_t b) { return (b + 255) / 256 * 256; }
+
+// Shape at n ions.  Four ions per lane and 1024 shares, all resident at once
+// (4 waves on each of the 1024 SIMDs); 2048 from 18000 ions, where a second
+// round costs less than the uneven end of longer shares; eight ions per lane
+// from 28000, where half the reaction sums per pair count more, in 2 rounds of
+// the 768 workgroups that then fit at once, or 3 (us per evaluation on
+// MI355X, P 4 with 1024 / 2048 shares: 8192 ions 42.7 / 46.7, 12001 70.8 / 71.5,
+// 20001 173 / 168, 24576 248 / 242, 32768 427 / 417; P 8 with 768 / 1536 / 2304:
+// 32768 ions 415 / 404 / 407, 40000 607 / 588 / 585, 49152 906 / 884 / 865).  With
+// the energy, P = 8 does not fit its registers (49152 ions: 1180 against 1007
+// with P = 4).
+struct ShareShape {
+    int P, N;
+};
+
+static ShareShape share_shape(int64_t n, bool pot) {
+    if (n >= 28000 && !pot) return {8, n < 45056 ? 1536 : 2304};
+    return {4, n < 18000 ? 1024 : 2048};
+}
+
+struct ShareWs {
+    double *Pi, *R, *Et, *eblk[2];
+    size_t bytes;
+};
+
+// Two sets of energy sums (at the same place for either shape) | Pi | R | Et.
+// ws NULL: the size alone.
+static ShareWs share_carve(int64_t n, bool pot, void* ws) {
+    const ShareShape h = share_shape(n, pot);
+    const ShareCut c = share_cut((int)n, h.P, h.N);
+    const size_t slots = (size_t)c.N + c.nI, nb = (size_t)((n + 63) / 64);
+    size_t at = 0;
+    auto carve = [&](size_t doubles) {
+        const size_t p = at;
+        at += al(sizeof(double) * doubles);
+        return ws ? reinterpret_cast<double*>(static_cast<char*>(ws) + p) : nullptr;
+    };
+    ShareWs w;
+    w.eblk[0] = carve(3 * nb);
+    w.eblk[1] = carve(3 * nb);
+    w.Pi = carve(3 * slots * c.IB);
+    w.R = carve(3 * (size_t)c.U * kShareJ);
+    w.Et = carve(slots);
+    w.bytes = at;
+    return w;
+}
+
+size_t share_ws_bytes(int64_t n, bool pot) {
+    const size_t f = share_carve(n, false, nullptr).bytes;
+    return pot ? std::max(f, share_carve(n, true, nullptr).bytes) : f;
+}
+
+template <int PREC, int P, bool POT>
+static void go_share(int n, int N, const double* x, const double* y, const double* z, const double* q, double eps2,
+                     const ShareWs& W, hipStream_t st) {
+    const ShareCut c = share_cut(n, P, N);
+    k_share_pairs<PREC, P, POT><<<(unsigned)c.N, 64 * kShareWaves, 0, st>>>(c, x, y, z, q, eps2, W.Pi, W.R, W.Et);
+}
+
+template <int PREC>
+static void go_share_p(bool pot, int n, const double* x, const double* y, const double* z, const double* q,
+                       double eps2, const ShareWs& W, hipStream_t st) {
+    const ShareShape h = share_shape(n, pot);
+    switch (h.P) {
+        case 4: pot ? go_share<PREC, 4, true>(n, h.N, x, y, z, q, eps2, W, st) : go_share<PREC, 4, false>(n, h.N, x, y, z, q, eps2, W, st); break;
+        default: go_share<PREC, 8, false>(n, h.N, x, y, z, q, eps2, W, st); break;
+    }
+}
+
+static cb_status share_pairs(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
+                             double eps2, bool pot, const ShareWs& W, hipStream_t st) {
+    switch (prec) {
+        case CB_FP64: go_share_p<PREC_FP64>(pot, (int)n, x, y, z, q, eps2, W, st); break;
+        case CB_MIXED: go_share_p<PREC_MIXED>(pot, (int)n, x, y, z, q, eps2, W, st); break;
+        case CB_FP64_IEEE: go_share_p<PREC_IEEE>(pot, (int)n, x, y, z, q, eps2, W, st); break;
+        default: go_share_p<PREC_FP32>(pot, (int)n, x, y, z, q, eps2, W, st); break;
+    }
+    return check_launch("k_share_pairs");
+}
+
+static cb_status share_finish(const ShareStep& S, hipStream_t st) {
+    const unsigned g = (unsigned)((S.n + 63) / 64) + (S.eprev ? 1u : 0u);
+    if (S.mode & EPI_ENERGY) k_share_finish<true><<<g, 64 * kFinWaves, 0, st>>>(S);
+    else k_share_finish<false><<<g, 64 * kFinWaves, 0, st>>>(S);
+    return check_launch("k_share_finish");
+}
+
+// The partials that S reads, as share_pairs left them.
+static void share_use(ShareStep& S, int64_t n, bool pot, const ShareWs& W) {
+    const ShareShape h = share_shape(n, pot);
+    S.n = (int)n;
+    S.cut = share_cut((int)n, h.P, h.N);
+    S.Pi = W.Pi;
+    S.R = W.R;
+    S.Et = W.Et;
+}
+
+cb_status share_forces(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
+                       const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
+                       double* u_out, void* ws, hipStream_t st) {
+    const bool pot = u_out != nullptr;
+    const ShareWs W = share_carve(n, pot, ws);
+    ShareStep S{};
+    share_use(S, n, pot, W);
+    S.eblk = W.eblk[0];
+    S.x = const_cast<double*>(x);  // read only in these modes
+    S.y = const_cast<double*>(y);
+    S.z = const_cast<double*>(z);
+    S.q = q;
+    S.m = m;
+    S.k = k;
+    S.fx = fx; S.fy = fy; S.fz = fz;
+    S.mode = mode | (u_out ? EPI_ENERGY | EPI_UPOT : 0u);
+    S.flags = flags_ptr();
+    if (!S.flags) return fail(CB_EHIP, "share_forces: device flag symbol not found");
+    cb_status rc = share_pairs(prec, n, x, y, z, q, eps2, pot, W, st);
+    if (rc || (rc = share_finish(S, st)) || !u_out) return rc;
+    k_energy_record<kFinWaves><<<1, 64 * kFinWaves, 0, st>>>((int)((n + 63) / 64), S.eblk, u_out, REC_UPOT);
+    return check_launch("k_energy_record");
+}
+
+cb_status md_run_shares(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,
+                        double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags, double* energies,
+                        int64_t every, void* ws, hipStream_t st) {
+    const ShareWs W[2] = {share_carve(n, false, ws), share_carve(n, true, ws)};  // a plain step's, a record's
+    ShareStep S{};
+    S.x = S.xn = s->x;
+    S.y = S.yn = s->y;
+    S.z = S.zn = s->z;
+    S.vx = s->vx; S.vy = s->vy; S.vz = s->vz;
+    S.ax = s->ax; S.ay = s->ay; S.az = s->az;
+    S.q = q;
+    S.m = m;
+    S.gamma = trap->gamma;
+    S.dt = dt;
+    S.flags = flags_ptr();
+    if (!S.flags) return fail(CB_EHIP, "md_run: device flag symbol not found");
+    const int nb = (int)((n + 63) / 64);
+    int parity = 0;
+    auto step = [&](int64_t k, unsigned mode, double* rec) -> cb_status {
+        cb_status r;
+        if ((mode & (EPI_ACCEL | EPI_KICK | EPI_ENERGY)) &&
+            (r = share_pairs(prec, n, s->x, s->y, s->z, q, eps2, rec != nullptr, W[rec != nullptr], st)))
+            return r;
+        share_use(S, n, rec != nullptr, W[rec != nullptr]);
+        S.k = trap_k(*trap, t0 + (double)k * dt);
+        S.mode = mode;
+        S.eblk = W[0].eblk[parity];
+        if ((r = share_finish(S, st))) return r;
+        // a record's sums are added by the next finish launch
+        S.eprev = rec ? W[0].eblk[parity] : nullptr;
+        S.eprev_out = rec;
+        S.nprev = nb;
+        if (rec) parity ^= 1;
+        return CB_OK;
+    };
+    const bool rec0 = energies != nullptr;
+    const bool init = (flags & CB_INIT_ACCEL) != 0;
+    const unsigned mode0 = (init ? EPI_ACCEL : 0u) | (rec0 ? EPI_ENERGY : 0u) | (nsteps > 0 ? EPI_DRIFT : 0u);
+    cb_status rc;
+    if (mode0 && (rc = step(0, mode0, rec0 ? energies : nullptr))) return rc;
+    for (int64_t k = 1; k <= nsteps; ++k) {
+        const bool rec = rec0 && k % every == 0;
+        if ((rc = step(k, EPI_KICK | (rec ? EPI_ENERGY : 0u) | (k < nsteps ? EPI_DRIFT : 0u),
+                       rec ? energies + 4 * (k / every) : nullptr)))
+            return rc;
+    }
+    if (S.eprev) {
+        k_energy_record<kFinWaves><<<1, 64 * kFinWaves, 0, st>>>(nb, S.eprev, S.eprev_out, REC_ALL);
+        if ((rc = check_launch("k_energy_record"))) return rc;
+    }
+    return ok();
+}
+
+}  // namespace cb

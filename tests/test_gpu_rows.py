@@ -145,3 +145,19 @@ def test_ensemble(api, sizes, prec):
             assert np.abs(a[0][blk] - b[0][blk]).max() <= 1e-11 * np.abs(b[0][blk]).max(), (nsteps, every, init)
         assert np.abs(a[1] - b[1]).max() <= 1e-11 * max(np.abs(b[1]).max(), 1e-300), (nsteps, every, init)
     assert api.poll_flags() == 0
+
+
+@pytest.mark.parametrize("n", [900, 2500, 9000])
+def test_resumed_records_are_bitwise(api, n):
+    """A record is summed by the next step's launch, or after the last step by
+    one of its own: both in the same order, so a run resumed after a record
+    agrees bitwise, state and records."""
+    from _gpu_util import dev, state_host, state_tensors
+    st, q, m, trap = _cloud(n, 11)
+    q, m = dev(q), dev(m)
+    a, b = state_tensors(st), state_tensors(st)
+    ea = api.md_run(a, q, m, trap, 0.0, 1e-9, 6, every=2).cpu().numpy()
+    eb = api.md_run(b, q, m, trap, 0.0, 1e-9, 4, every=2).cpu().numpy()
+    ec = api.md_run(b, q, m, trap, 4e-9, 1e-9, 2, every=2, init_accel=False).cpu().numpy()
+    assert np.array_equal(state_host(a), state_host(b))
+    assert np.array_equal(ea[0, :3], eb[0]) and np.array_equal(ea[0, 2:], ec[0])
