@@ -57,6 +57,12 @@ __global__ void __launch_bounds__(256) k_hvp_pack(int n, int nv, const double* _
 template <int NV>
 struct HvpJRec {
     double x, y, z, q, v[NV][3];
+    // An empty asm that reads the record: its loads are waited for before it.
+    __device__ __forceinline__ void arrived() {
+        asm volatile("" : "+s"(x), "+s"(y), "+s"(z), "+s"(q));
+#pragma unroll
+        for (int b = 0; b < NV; ++b) asm volatile("" : "+s"(v[b][0]), "+s"(v[b][1]), "+s"(v[b][2]));
+    }
 };
 
 template <int NV>
@@ -151,6 +157,8 @@ constexpr int hvp_sym_waves() {
     return P == 1 ? (NV == 4 ? 3 : 4) : (P == 2 ? (NV == 4 ? 2 : (NV == 2 ? 3 : 4)) : (NV == 1 ? 3 : 2));
 }
 
+constexpr int kWaitLgkm0 = 0xc07f;  // s_waitcnt lgkmcnt(0), the other counters unwaited
+
 // The j loop of tile t over [j0, j1) and the stores of its partials:
 // Pi[t][NV][3][IB] and R[t][NV][3][JL].
 template <int PREC, int P, int NV, bool UNI>
@@ -182,36 +190,64 @@ __device__ __forceinline__ void hvp_sym_body(const double* __restrict__ J, doubl
             if (g < lv) Rt[(size_t)(b * 3 + c) * JL + (jgs - j0) + g] = UNI ? o * qI : o;
         }
     };
-    HvpJRec<NV> cur = load_hvp_j<NV>(J, j0);
-    for (int jg = j0; jg < j1; jg += GJ) {
-        const int live = min(GJ, j1 - jg);
-        double sh[GJ][NV][3];
+    // Two records of j data in turn, each requested again (two j's further on)
+    // as soon as its j is evaluated.  Scalar loads return out of order and
+    // count with the LDS reads, so a wait for one is a wait for all: the wait
+    // stands between a j's evaluation, during which the other record and the
+    // last group's LDS loads arrive, and the next request.  A request ahead of
+    // the wait would be waited for at once, as it was with one record copied
+    // to the next (one vector at 8192 ions 63 -> 61 us, eight 288 -> 286).
+    HvpJRec<NV> rec[2] = {load_hvp_j<NV>(J, j0), load_hvp_j<NV>(J, min(j0 + 1, j1 - 1))};
+    // (everything requested so far is waited for here: a load still pending on
+    // the way in would be waited for inside the loop, each time round, and with
+    // it the loop's own stores and requests)
+    rec[0].arrived();
+    rec[1].arrived();
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int UJ = GJ < 2 ? 2 : GJ;  // j's per iteration
+    for (int jb = j0; jb < j1; jb += UJ) {
 #pragma unroll
-        for (int g = 0; g < GJ; ++g) {
-            // the next j's record is requested before this j is evaluated
-            const HvpJRec<NV> nxt = load_hvp_j<NV>(J, min(jg + g + 1, j1 - 1));
-            __builtin_amdgcn_sched_barrier(0);
-            if (g < live) {
-                hvp_sym_pair<PREC, P, NV, UNI>(cur, eps2, xi, yi, zi, qi, vi, ia, sh[g], K);
-            } else {
+        for (int r = 0; r < UJ / GJ; ++r) {
+            const int jg = jb + r * GJ;
+            // (a group beyond the range is a sum of zeros that store() leaves
+            // out: a branch past it would bring the pending loads of its start
+            // back to the loop's head)
+            const int live = min(GJ, j1 - jg);
+            double sh[GJ][NV][3];
 #pragma unroll
-                for (int b = 0; b < NV; ++b) sh[g][b][0] = sh[g][b][1] = sh[g][b][2] = 0.0;
+            for (int g = 0; g < GJ; ++g) {
+                HvpJRec<NV>& cur = rec[(r * GJ + g) & 1];
+                if ((r == 0 && g == 0) || g < live) {
+                    hvp_sym_pair<PREC, P, NV, UNI>(cur, eps2, xi, yi, zi, qi, vi, ia, sh[g], K);
+                } else {
+#pragma unroll
+                    for (int b = 0; b < NV; ++b) sh[g][b][0] = sh[g][b][1] = sh[g][b][2] = 0.0;
+                }
+                // the empty asm keeps the sums' updates ahead of the wait and
+                // the reduction (as in the force tiles: otherwise their
+                // operands stay live through it)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int b = 0; b < NV; ++b)
+                        asm volatile("" : "+v"(ia[p][b][0]), "+v"(ia[p][b][1]), "+v"(ia[p][b][2]));
+#pragma unroll
+                for (int b = 0; b < NV; ++b) asm volatile("" : "+v"(sh[g][b][0]), "+v"(sh[g][b][1]), "+v"(sh[g][b][2]));
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                __builtin_amdgcn_sched_barrier(0);
+                cur = load_hvp_j<NV>(J, min(jg + g + 2, j1 - 1));
+                __builtin_amdgcn_sched_barrier(0);
             }
-            cur = nxt;
+            if (pjg >= 0) store(pjg, plive);
+            double v12[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k) v12[k] = sh[k / (3 * NV)][(k / 3) % NV][k % 3];
+            lds_put12(v12, red, a);
+            pjg = jg;
+            plive = live;
         }
-        // the empty asm keeps the i sums' updates ahead of the reduction (as in
-        // the force tiles: otherwise their operands stay live through it)
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-#pragma unroll
-            for (int b = 0; b < NV; ++b) asm volatile("" : "+v"(ia[p][b][0]), "+v"(ia[p][b][1]), "+v"(ia[p][b][2]));
-        if (pjg >= 0) store(pjg, plive);
-        double v12[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) v12[k] = sh[k / (3 * NV)][(k / 3) % NV][k % 3];
-        lds_put12(v12, red, a);
-        pjg = jg;
-        plive = live;
     }
     if (pjg >= 0) store(pjg, plive);
     const double sc = UNI ? qI * qJ : 1.0;
