@@ -246,7 +246,9 @@ cb_status md_step(int64_t n, const cb_state* s, const double* q, const double* m
  * ..., for each run; every >= 1 then.
  * nrun = 1 runs the multi-workgroup step kernels (any n): one launch per
  * step for small runs, each workgroup evaluating whole rows of the pair sum
- * (algorithm 3 of cb_get_config), else a pair stage and a finishing launch.  nrun > 1 needs every run to hold at most 4096 ions
+ * (algorithm 3 of cb_get_config; up to 1280 ions and from 6 + n / 256 steps
+ * on, one launch for up to 128 steps, bitwise the same), else a pair stage and
+ * a finishing launch.  nrun > 1 needs every run to hold at most 4096 ions
  * (CB_EUNSUPPORTED otherwise) and takes, when its entry (configuration key
  * CB_OP_MD_ENSEMBLE) is forced or tuned, one of two ensemble paths:
  *  - algorithm 0: one persistent launch, one workgroup per run at a time,
@@ -327,8 +329,9 @@ cb_status cb_load_tuning(const char* cache_path);
  *          j-segment and sum their reactions in LDS before one write, which
  *          cuts the partial sums written and read back by four;
  *          3: md_step / md_run of one run of at most 8192 ions in one launch
- *          per step, every ordered pair evaluated, a workgroup taking 4 or 8
- *          ions against all j and then applying trap, kick and drift),
+ *          per step (or, up to 1280 ions, for many steps), every ordered pair
+ *          evaluated, a workgroup taking 4 or 8 ions against all j and then
+ *          applying trap, kick and drift),
  * out[1] = i-particles per lane, out[2] = workgroup size (algorithm 0) or
  *          j's per reduction group (algorithms 1, 2, 4),
  * out[3] = j-splits (algorithm 0), j-segment length (algorithms 1, 2, 4) or

@@ -182,7 +182,7 @@ static cb_status md_single(int64_t n, const cb_state* s, const double* q, const 
     const LaunchCfg sc = get_cfg(op, n, prec);
     if (sc.path == PATH_ROWS || (sc.algo == ALGO_SMALL && n <= kSmallRunMax))
         return md_run_rows(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, every > 0 ? energies : nullptr, every,
-                           static_cast<char*>(ws) + L.part, L.ppot - L.part, st);
+                           static_cast<char*>(ws) + L.part, L.ppot - L.part, kRunSpins, st);
     if (sc.path == PATH_SHARES)
         return md_run_shares(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, every > 0 ? energies : nullptr,
                              every, static_cast<char*>(ws) + L.part, st);

@@ -38,7 +38,8 @@ constexpr int kMaxDevices = 64;      // GPUs per process the per-device symbol t
 // ALGO_SYM_LDS with kSymRows consecutive i-blocks per workgroup sharing each
 // j-segment, their reactions added in LDS before one store.
 // ALGO_SMALL (md_step / md_run of one run of at most kSmallRunMax ions):
-// one launch per step, every pair direct (md_run_rows).
+// one launch per step, every pair direct (md_run_rows; up to kRowsRunMaxN ions
+// and from some steps on, one launch for many steps).
 enum : int { ALGO_DIRECT = 0, ALGO_SYM = 1, ALGO_SYM_LDS = 2, ALGO_SMALL = 3, ALGO_SYM_ROWS = 4 };
 
 // What an entry's calls take: the launches of its algorithm and shape, or
@@ -256,7 +257,19 @@ constexpr int64_t kRowsSmallN = 1536;  // up to here 4 ions to a workgroup of 8 
 size_t md_rows_ws_bytes(int64_t n);
 cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,
                       double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags, double* energies,
-                      int64_t every, void* ws, size_t ws_bytes, hipStream_t st);
+                      int64_t every, void* ws, size_t ws_bytes, int spins, hipStream_t st);
+
+// Its steps by workgroups that stay resident (rows_run.hpp): whether a run
+// takes them, and the steps themselves, from accelerations at t0 on; spins:
+// polls of one wait for a position before the launch gives up (its end then
+// takes the steps by one workgroup).
+constexpr int64_t kRowsRunMaxN = 1280;
+constexpr int kRunSpins = 1 << 18;
+size_t rows_run_ws_bytes(int64_t n);
+bool rows_run_fits(int64_t n, int64_t nsteps, size_t ws_bytes);
+cb_status rows_run(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,
+                   double dt, int64_t nsteps, double eps2, int32_t prec, double* energies, int64_t every, int spins,
+                   void* ws, hipStream_t st);
 
 // Forces (mode EPI_FORCES) or gradient (EPI_GRAD) of n ions in one launch,
 // and with u_out the energy U_C (+ U_trap with m) in a second; ws (with u_out

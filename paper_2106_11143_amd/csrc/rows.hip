@@ -251,7 +251,7 @@ static void go_rows_shape(const RowParams& P, unsigned g, hipStream_t st) {
 
 cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,
                       double dt, int64_t nsteps, double eps2, int32_t prec, uint32_t flags, double* energies,
-                      int64_t every, void* ws, size_t ws_bytes, hipStream_t st) {
+                      int64_t every, void* ws, size_t ws_bytes, int spins, hipStream_t st) {
     if (ws_bytes < md_rows_ws_bytes(n)) return fail(CB_ENOWS, "md_run: workspace too small for the one-launch step");
     unsigned* fl = flags_ptr();
     if (!fl) return fail(CB_EHIP, "md_run: device flag symbol not found");
@@ -305,13 +305,17 @@ cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const doubl
         if (swap) std::swap(cur, nxt);
         return CB_OK;
     };
-    cb_status rc = rows_steps(nsteps, (flags & CB_INIT_ACCEL) != 0, energies != nullptr, every, launch);
+    const bool init = (flags & CB_INIT_ACCEL) != 0;
+    const bool resident = rows_run_fits(n, nsteps, ws_bytes);
+    cb_status rc = rows_steps(resident ? 0 : nsteps, init, energies != nullptr, every, launch);
     if (rc) return rc;
     if (pend) {  // the last record, in the order of the launches' extra workgroups
         if (rows_small(n)) k_energy_record<8><<<1, 512, 0, st>>>(nb, pend, pend_out, REC_ALL);
         else k_energy_record<4><<<1, 256, 0, st>>>(nb, pend, pend_out, REC_ALL);
         if ((rc = check_launch("k_energy_record"))) return rc;
     }
+    if (resident && (rc = rows_run(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, energies, every, spins, ws, st)))
+        return rc;
     return ok();
 }
 

@@ -68,6 +68,17 @@ __device__ __forceinline__ void reduce_scatter12(const double (&v)[12], double (
     }
 }
 
+// Likewise for four values: every lane of group g = lane >> 4 returns the sum
+// over all 64 lanes of v[g].
+__device__ __forceinline__ double reduce_scatter4(const double (&v)[4]) {
+    double x = swap16_add(swap32_add(v[0], v[2]), swap32_add(v[1], v[3]));
+    x += dpp_d<kDppRowRor8>(x);
+    x += dpp_d<kDppRowHalfMirror>(x);
+    x += dpp_d<kDppQuadXor2>(x);
+    x += dpp_d<kDppQuadXor1>(x);
+    return x;
+}
+
 // The same sums through LDS, for a workgroup of one wave.  Every lane writes
 // its NV (12 or 16) values value-major into red: row k of kRedStride doubles
 // holds value k of lanes 0-63, each run of 16 lanes followed by 2 doubles of
