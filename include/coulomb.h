@@ -257,8 +257,9 @@ cb_status md_step(int64_t n, const cb_state* s, const double* q, const double* m
  *    of every run and one launch that finishes the forces and applies the
  *    kick and drift (p i-particles per lane, j-segment length JL).
  * Without a forced or tuned entry, ensembles of small runs take one launch
- * per step over the whole rows of every run, the others the stepped path
- * (the smaller estimated step time decides) with p = 4 and JL = 256, or
+ * per step over the whole rows of every run, middle ones two launches per step
+ * over equal shares of all runs' pairs, large ones the stepped path (the
+ * smallest estimated step time decides) with p = 4 and JL = 256, or
  * JL = 512 for ensembles of at least 2^30 ordered pairs.  All paths give the
  * same trajectories up to rounding (different summation orders); each is
  * deterministic.

@@ -452,15 +452,21 @@ cb_status md_run_batched(int32_t nrun, const int64_t* offsets, const cb_state* s
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return fail(CB_EHIP, "md_run: device query failed");
     // Path.  A forced or tuned entry decides.  Otherwise estimate the time of
-    // one step on each path from rates measured on MI355X.  Whole rows per
-    // workgroup (rows.hip): one launch of about 5 us and every ordered pair
-    // at 1.25e12/s.  Newton's-third-law tiles (ensemble.hip): two launches,
-    // whose longest tile bounds a small ensemble (about 45 us in all), and
-    // the pairs at 2.3e12/s.  us per step, rows / tiles: 4 runs of 30-100
-    // ions 4.8 / 51 (the persistent kernel of this file 25.4); 8 of 64-600
-    // 6.3 / 49; 64 of 64-1024 (2.2e7 pairs) 26.3 / 67.5; 512 of 64-512
-    // (5.0e7) 57 / 89; 512 of 64-1024 (1.9e8) 166 / 159; 16 of 2048-4096
-    // (1.4e8) 114 / 88.
+    // one step on each path from rates measured on MI355X, in ordered pairs and
+    // in units of 256 ions by 16 j's (which count what short blocks leave
+    // idle).  Whole rows per workgroup (rows.hip): one launch of about 5 us and
+    // every ordered pair at 1.25e12/s.  Equal shares of the Newton's-third-law
+    // pairs (shares.hip): two launches of about 15 us in all and 3.3 ns a
+    // unit.  Tiles (ensemble.hip): two launches, whose longest tile bounds a
+    // small ensemble (about 40 us in all), and 3.0 ns a unit.  us per step,
+    // rows / shares / tiles: 4 runs of 30-100 ions 4.8 / 10.9 / 51 (the
+    // persistent kernel of this file 25.4); 8 of 64-600 6.3 / 13.2 / 49; 64 of
+    // 64-1024 (2.2e7 pairs, 4.0e3 units) 26.3 / 33 / 67; 512 of 64-512 (5.0e7,
+    // 1.2e4) 57 / 68 / 89; 16 of 2048-4096 (1.4e8, 1.9e4) 114 / 79 / 87; 128 of
+    // 64-2048 (1.9e8, 2.8e4) - / 118 / 134; 512 of 64-1024 (1.9e8, 3.3e4) 166 /
+    // 124 / 157; 256 of 64-2048 (3.5e8, 5.2e4) - / 182 / 203; 512 of 64-2048
+    // (7.2e8, 1.06e5) - / 352 / 328; 512 of 64-4096 (2.8e9, 3.8e5) - / 1180 /
+    // 1130.
     // The tiles use 256-ion i-blocks, with 512-ion j-segments when the
     // ensemble holds 2^30 or more ordered pairs (4096 or more tiles) and
     // 256-ion ones below (measured on MI355X, ms per step with JL 256 / 512:
@@ -473,11 +479,15 @@ cb_status md_run_batched(int32_t nrun, const int64_t* offsets, const cb_state* s
         double pairs = 0.0;
         for (int r = 0; r < nrun; ++r)
             pairs += (double)(offsets[r + 1] - offsets[r]) * (double)(offsets[r + 1] - offsets[r]);
-        if (5e-6 + pairs / 1.25e12 < 45e-6 + pairs / 2.3e12) {
-            const WsLayout LE = ws_layout(CB_OP_MD_RUN, offsets[nrun], nrun, 1, prec);
+        const WsLayout LE = ws_layout(CB_OP_MD_RUN, offsets[nrun], nrun, 1, prec);
+        const double units = share_ens_units(nrun, offsets);
+        const double shares = 15e-6 + units * 3.3e-9, tiles = 40e-6 + units * 3.0e-9;
+        if (5e-6 + pairs / 1.25e12 < std::min(shares, tiles))
             return md_run_rows_ensemble(nrun, offsets, s, q, m, traps, t0, dt, nsteps, eps2, prec, flags, energies,
                                         every, static_cast<char*>(ws) + LE.aux, ws_bytes - LE.aux, st);
-        }
+        if (shares < tiles && share_ens_fits(nrun, offsets, ws_bytes - LE.aux))
+            return md_run_shares_ensemble(nrun, offsets, s, q, m, traps, t0, dt, nsteps, eps2, prec, flags, energies,
+                                          every, static_cast<char*>(ws) + LE.aux, ws_bytes - LE.aux, st);
         ec.algo = ALGO_SYM_LDS;
         ec.p = 4;
         ec.splits = pairs >= 1073741824.0 ? 512 : 256;

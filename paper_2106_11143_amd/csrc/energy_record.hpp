@@ -50,4 +50,14 @@ __global__ void __launch_bounds__(64 * W) k_energy_record(int nb, const double* 
     energy_record<W>(nb, eblk, out, what);
 }
 
+// Records of the runs of an ensemble, run r = blockIdx.x: runs[r] = its first
+// block and its blocks.
+template <int W>
+__global__ void __launch_bounds__(64 * W) k_ens_record(const int2* __restrict__ runs,
+                                                      const double* __restrict__ eblk, long long nrec, long long rec,
+                                                      double* __restrict__ energies) {
+    const int2 ru = runs[blockIdx.x];
+    energy_record<W>(ru.y, eblk + (size_t)ru.x * 3, energies + ((size_t)blockIdx.x * nrec + rec) * 4, REC_ALL);
+}
+
 }  // namespace cb

@@ -157,7 +157,8 @@ __device__ __forceinline__ bool tile_charges(const double (&qi)[P], const double
 // stored and the reactions by rscale = qI here, so that the partials hold
 // what the general loop stores.
 // DIAG: the j's lie in the lane's own i-block (ion i0 + 64 p + lane of lane's
-// p-th): only the pairs j > i count.
+// p-th): only the pairs j > i count, so the lane's ions are taken up to the
+// group's own sub-block of 64 (groups start at multiples of 4 from i0).
 // POT: the pair energies too, into one sum per lane, pe += q_i q_j r^-1
 // (r^-1 when UNI), from r^-1 = r^2 r^-3: one or two operations per pair and
 // no reaction (each unordered pair's energy is counted once, here).
@@ -167,8 +168,34 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
                                           const double (&qi)[P], double (&ia)[P][3], double& pe, const SeriesK& K,
                                           double rscale, double* __restrict__ Rt, double* __restrict__ red, int i0 = 0) {
     double jv[3 * kGroupJ];  // this lane's share of each reaction: sum over its P ions of q_i d r^-3
+    if constexpr (DIAG) {
 #pragma unroll
-    for (int u = 0; u < kGroupJ; ++u) {
+        for (int k = 0; k < 3 * kGroupJ; ++k) jv[k] = 0.0;
+        const int own = (jg - i0) / 64;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (p > own) break;
+#pragma unroll
+            for (int u = 0; u < kGroupJ; ++u) {
+                const double dx = xi[p] - jd.x[u], dy = yi[p] - jd.y[u], dz = zi[p] - jd.z[u];
+                const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
+                double s = sym_s<PREC>(r2, UNI ? 1.0 : qi[p], K);
+                if ((TAIL && u >= live) || jg + u <= i0 + p * 64 + (int)(threadIdx.x & 63)) s = 0.0;
+                double sq = s;
+                if constexpr (!UNI) sq = s * jd.q[u];
+                ia[p][0] = __builtin_fma(dx, sq, ia[p][0]);
+                ia[p][1] = __builtin_fma(dy, sq, ia[p][1]);
+                ia[p][2] = __builtin_fma(dz, sq, ia[p][2]);
+                jv[3 * u + 0] = __builtin_fma(dx, s, jv[3 * u + 0]);
+                jv[3 * u + 1] = __builtin_fma(dy, s, jv[3 * u + 1]);
+                jv[3 * u + 2] = __builtin_fma(dz, s, jv[3 * u + 2]);
+                if constexpr (POT) pe = __builtin_fma(r2, sq, pe);
+            }
+            asm volatile("" : "+v"(ia[p][0]), "+v"(ia[p][1]), "+v"(ia[p][2]));
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < (DIAG ? 0 : kGroupJ); ++u) {
         const double xj = jd.x[u], yj = jd.y[u], zj = jd.z[u];
         double a0 = 0.0, a1 = 0.0, a2 = 0.0;
 #pragma unroll
@@ -177,7 +204,6 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
             const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
             double s = sym_s<PREC>(r2, UNI ? 1.0 : qi[p], K);  // r^-3 (UNI) or q_i r^-3
             if (TAIL && u >= live) s = 0.0;
-            if (DIAG && jg + u <= i0 + p * 64 + (int)(threadIdx.x & 63)) s = 0.0;
             double sq = s;
             if constexpr (!UNI) sq = s * jd.q[u];  // q_i q_j r^-3
             ia[p][0] = __builtin_fma(dx, sq, ia[p][0]);

@@ -182,16 +182,6 @@ __global__ void __launch_bounds__(64 * W, (rows_waves<PREC, I, POT>())) k_rows_e
     if (POT) rows_energy<I>(eK, eC, eT, P.eblk);
 }
 
-// Record of run r = blockIdx.x from its chunks' energy sums.
-template <int W>
-__global__ void __launch_bounds__(64 * W) k_rows_ens_record(const int2* __restrict__ runs,
-                                                           const double* __restrict__ eblk, long long nrec,
-                                                           long long rec, double* __restrict__ energies) {
-    const int2 ru = runs[blockIdx.x];  // its first chunk, its chunks
-    energy_record<W>(ru.y, eblk + (size_t)ru.x * 3, energies + ((size_t)blockIdx.x * nrec + rec) * 4,
-                   REC_ALL);
-}
-
 // ----------------------------------------------------------------- host
 
 static size_t al(size_t b) { return (b + 255) / 256 * 256; }
@@ -459,8 +449,8 @@ cb_status md_run_rows_ensemble(int32_t nrun, const int64_t* offsets, const cb_st
         if (r) return r;
         if (swap) std::swap(cur, nxt);
         if (rec < 0) return CB_OK;
-        k_rows_ens_record<4><<<nrun, 256, 0, st>>>(d_runs, eblk, nrec, rec, energies);
-        return check_launch("k_rows_ens_record");
+        k_ens_record<4><<<nrun, 256, 0, st>>>(d_runs, eblk, nrec, rec, energies);
+        return check_launch("k_ens_record");
     };
     const cb_status rc = rows_steps(nsteps, (flags & CB_INIT_ACCEL) != 0, energies != nullptr, every, launch);
     return rc ? rc : ok();

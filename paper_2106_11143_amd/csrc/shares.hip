@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <vector>
 
 #include "energy_record.hpp"
 #include "internal.hpp"
@@ -38,26 +39,31 @@ struct ShareStep {
 // several are in flight per wave.
 constexpr int kFinWaves = 8, kFinPi = 3, kFinR = 6;
 
-template <bool POT>
-__global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
-    __shared__ double red[kFinWaves][6][64];
-    if (S.eprev && blockIdx.x == gridDim.x - 1) {
-        energy_record<kFinWaves>(S.nprev, S.eprev, S.eprev_out, REC_ALL);
-        return;
-    }
-    const ShareCut& cut = S.cut;
+// A run among several (a single one is at zero): its first ion, row and unit,
+// and its trap.
+struct ShareRun {
+    int o, row, unit;
+    TrapK k;
+    double gamma;
+};
+
+// The 64 ions from k0 on of a run of cut.n ions, by FW waves; their energy
+// sums (POT) to eblk.
+template <bool POT, int FW>
+__device__ __forceinline__ void share_finish_ions(const ShareStep& S, const ShareCut& cut, const ShareRun& run, int k0,
+                                                  double (&red)[FW][6][64], double* __restrict__ eblk) {
     const int IB = cut.IB;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int k0 = blockIdx.x * 64, k = k0 + lane, kc = min(k, S.n - 1);
+    const int kl = k0 + lane, kc = min(kl, cut.n - 1), k = run.o + kl;
     const int B = k0 / IB, off = kc - B * IB;
     const unsigned mode = S.mode;
-    const bool own = w == 0 && k < S.n;
+    const bool own = w == 0 && kl < cut.n;
     const bool step =
         (mode & (EPI_ACCEL | EPI_KICK | EPI_DRIFT)) || ((mode & EPI_ENERGY) && !(mode & (EPI_GRAD | EPI_UPOT)));
     // the row's slots: its shares, each at slot share + row
-    const int u0 = row_unit(cut, B);
-    const int s0 = unit_share(cut, u0) + B, s1 = unit_share(cut, u0 + row_units(cut, B) - 1) + B + 1;
+    const int u0 = run.unit + row_unit(cut, B), row = run.row + B;
+    const int s0 = unit_share(cut, u0) + row, s1 = unit_share(cut, u0 + row_units(cut, B) - 1) + row + 1;
     IonState s{};
     double x = 0.0, y = 0.0, z = 0.0, qk = 0.0;
     if (own) {
@@ -75,7 +81,7 @@ __global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
         // part w of the row's slots [s0, s1) and of the rows 0 .. B, kFinPi and
         // kFinR of them requested together
         auto part = [&](int a, int b, int& lo, int& hi) {
-            const int len = (b - a + kFinWaves - 1) / kFinWaves;
+            const int len = (b - a + FW - 1) / FW;
             lo = min(b, a + w * len);
             hi = min(b, lo + len);
         };
@@ -94,7 +100,7 @@ __global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
 #pragma unroll
             for (int i = 0; i < kFinR; ++i) {
                 const int I = max(0, min(tr + i, tre - 1)), stride = row_units(cut, I) * kShareJ;
-                const double* p = S.R + (size_t)3 * row_unit(cut, I) * kShareJ + (kc - I * IB);
+                const double* p = S.R + (size_t)3 * (run.unit + row_unit(cut, I)) * kShareJ + (kc - I * IB);
                 e[i][0] = p[0];
                 e[i][1] = p[stride];
                 e[i][2] = p[2 * (size_t)stride];
@@ -116,7 +122,7 @@ __global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
     __syncthreads();
     if (w != 0) return;
 #pragma unroll
-    for (int u = 1; u < kFinWaves; ++u)
+    for (int u = 1; u < FW; ++u)
 #pragma unroll
         for (int c = 0; c < 6; ++c) v[c] += red[u][c][lane];
     double eK = 0.0, eC = 0.0, eT = 0.0;
@@ -131,18 +137,18 @@ __global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
             S.fz[k] = Fz;
             ok = finite3(Fx, Fy, Fz);
         } else if (step) {
-            step_ion(S, S.k, S.gamma, k, s, x, y, z, qk, Fx, Fy, Fz, 0.0, eK, eC, eT);
+            step_ion(S, run.k, run.gamma, k, s, x, y, z, qk, Fx, Fy, Fz, 0.0, eK, eC, eT);
         } else {
             if (mode & EPI_GRAD) {
-                const double gx = __builtin_fma(s.m * S.k.kx, x, -Fx);
-                const double gy = __builtin_fma(s.m * S.k.ky, y, -Fy);
-                const double gz = __builtin_fma(s.m * S.k.kz, z, -Fz);
+                const double gx = __builtin_fma(s.m * run.k.kx, x, -Fx);
+                const double gy = __builtin_fma(s.m * run.k.ky, y, -Fy);
+                const double gz = __builtin_fma(s.m * run.k.kz, z, -Fz);
                 S.fx[k] = gx;
                 S.fy[k] = gy;
                 S.fz[k] = gz;
                 ok = finite3(gx, gy, gz);
             }
-            if (POT) eT = 0.5 * s.m * (S.k.kx * x * x + S.k.ky * y * y + S.k.kz * z * z);
+            if (POT) eT = 0.5 * s.m * (run.k.kx * x * x + run.k.ky * y * y + run.k.kz * z * z);
         }
         if (POT) {
             // each share of the block's row gives its pair energy to one ion
@@ -161,11 +167,39 @@ __global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
             eT += __shfl_xor(eT, d);
         }
         if (lane == 0) {
-            S.eblk[(size_t)blockIdx.x * 3 + 0] = eK;
-            S.eblk[(size_t)blockIdx.x * 3 + 1] = eC;
-            S.eblk[(size_t)blockIdx.x * 3 + 2] = eT;
+            eblk[0] = eK;
+            eblk[1] = eC;
+            eblk[2] = eT;
         }
     }
+}
+
+template <bool POT>
+__global__ void __launch_bounds__(64 * kFinWaves) k_share_finish(ShareStep S) {
+    __shared__ double red[kFinWaves][6][64];
+    if (S.eprev && blockIdx.x == gridDim.x - 1)
+        energy_record<kFinWaves>(S.nprev, S.eprev, S.eprev_out, REC_ALL);
+    else
+        share_finish_ions<POT, kFinWaves>(S, S.cut, ShareRun{0, 0, 0, S.k, S.gamma}, blockIdx.x * 64, red,
+                                          POT ? S.eblk + (size_t)blockIdx.x * 3 : nullptr);
+}
+
+// The same for the runs of k_share_pairs_ens.  chunks[blockIdx.x]: run and
+// first ion (of the run) of the workgroup's 64.
+template <bool POT, int FW>
+__global__ void __launch_bounds__(64 * FW) k_share_finish_ens(ShareStep S, const int4* __restrict__ runs,
+                                                             const int2* __restrict__ chunks,
+                                                             const cb_trap* __restrict__ traps, double t0,
+                                                             long long step) {
+    __shared__ double red[FW][6][64];
+    const int2 ch = chunks[blockIdx.x];
+    const int4 ru = runs[ch.x];
+    ShareCut cut = share_rows(ru.y, S.cut.IB / 64);
+    cut.len = S.cut.len;
+    cut.more = S.cut.more;
+    const cb_trap& tr = traps[ch.x];
+    share_finish_ions<POT, FW>(S, cut, ShareRun{ru.x, ru.z, ru.w, trap_k(tr, step_time(t0, S.dt, step)), tr.gamma},
+                               ch.y, red, POT ? S.eblk + (size_t)blockIdx.x * 3 : nullptr);
 }
 
 // ----------------------------------------------------------------- host
@@ -341,6 +375,165 @@ cb_status md_run_shares(int64_t n, const cb_state* s, const double* q, const dou
     if (S.eprev) {
         k_energy_record<kFinWaves><<<1, 64 * kFinWaves, 0, st>>>(nb, S.eprev, S.eprev_out, REC_ALL);
         if ((rc = check_launch("k_energy_record"))) return rc;
+    }
+    return ok();
+}
+
+// ------------------------------------------------------------- ensembles
+constexpr int kEnsP = 4;  // ions per lane
+// Shares, in two rounds of the 1024 workgroups that fit at once (us per step
+// with 1024 / 2048 / 4096: 16 runs of 2048-4096 ions 81.8 / 79.6 / 87.2, 512 of
+// 64-1024 128.6 / 124.8 / 125.8, 256 of 64-2048 188 / 183 / 182; a share per
+// wave instead of per workgroup, 4096 and 8192: 89 / 90, 135 / 132, 192 / 190;
+// 2 ions per lane and 1024 workgroups 86, 128, 200).
+constexpr int kEnsShares = 2048;
+constexpr size_t kEnsFinishFew = 4096;  // up to here 8 waves finish 64 ions, above 2
+
+struct ShareEns {
+    std::vector<int4> runs;    // k_share_pairs_ens'
+    std::vector<int2> first, chunks, recs;
+    ShareCut all{};
+    size_t rows = 0, bytes = 0;
+};
+
+// Whether nrun runs can take equal shares, and their tables.
+static bool share_ens(int32_t nrun, const int64_t* offsets, ShareEns& E) {
+    if (share_ens_units(nrun, offsets) > 1e9) return false;  // (unit numbers are 32 bits)
+    E.runs.resize(nrun);
+    E.recs.resize(nrun);
+    int u = 0;
+    for (int r = 0; r < nrun; ++r) {
+        const int n = (int)(offsets[r + 1] - offsets[r]);
+        const ShareCut c = share_rows(n, kEnsP);
+        E.runs[r] = make_int4((int)offsets[r], n, (int)E.rows, u);
+        E.recs[r] = make_int2((int)E.chunks.size(), (n + 63) / 64);
+        for (int k0 = 0; k0 < n; k0 += 64) E.chunks.push_back(make_int2(r, k0));
+        E.rows += (size_t)c.nI;
+        u += c.U;
+    }
+    E.all.IB = 64 * kEnsP;
+    share_units(E.all, u, kEnsShares);
+    E.first.reserve((size_t)E.all.N);
+    int r = 0, I = 0;
+    ShareCut c = share_rows(E.runs[0].y, kEnsP);
+    for (int g = 0; g < E.all.N; ++g) {
+        const int at = share_unit(E.all, g);
+        while (at >= E.runs[r].w + c.U) {
+            c = share_rows(E.runs[++r].y, kEnsP);
+            I = 0;
+        }
+        while (at >= E.runs[r].w + row_unit(c, I) + row_units(c, I)) ++I;
+        E.first.push_back(make_int2(r, I));
+    }
+    const size_t slots = (size_t)E.all.N + E.rows, nch = E.chunks.size();
+    E.bytes = al(sizeof(int4) * nrun) + al(sizeof(int2) * E.first.size()) + al(sizeof(int2) * nch) +
+              al(sizeof(int2) * nrun) + al(sizeof(cb_trap) * nrun) + al(sizeof(double) * 3 * slots * 64 * kEnsP) +
+              al(sizeof(double) * 3 * (size_t)u * kShareJ) + al(sizeof(double) * slots) + al(sizeof(double) * 3 * nch);
+    return true;
+}
+
+double share_ens_units(int32_t nrun, const int64_t* offsets) {
+    double units = 0.0;
+    for (int r = 0; r < nrun; ++r) units += share_rows((int)(offsets[r + 1] - offsets[r]), kEnsP).U;
+    return units;
+}
+
+bool share_ens_fits(int32_t nrun, const int64_t* offsets, size_t ws_bytes) {
+    ShareEns E;
+    return share_ens(nrun, offsets, E) && E.bytes <= ws_bytes;
+}
+
+template <int PREC>
+static void go_share_ens(bool pot, const ShareEns& E, const int4* runs, const int2* first, const cb_state* s,
+                         const double* q, double eps2, double* Pi, double* R, double* Et, hipStream_t st) {
+    const unsigned g = (unsigned)E.all.N;
+    if (pot)
+        k_share_pairs_ens<PREC, kEnsP, true><<<g, 64 * kShareWaves, 0, st>>>(E.all, runs, first, s->x, s->y, s->z, q, eps2, Pi, R, Et);
+    else
+        k_share_pairs_ens<PREC, kEnsP, false><<<g, 64 * kShareWaves, 0, st>>>(E.all, runs, first, s->x, s->y, s->z, q, eps2, Pi, R, Et);
+}
+
+template <int FW>
+static void go_finish_ens(const ShareStep& S, unsigned g, const int4* runs, const int2* chunks, const cb_trap* traps,
+                          double t0, long long step, hipStream_t st) {
+    if (S.mode & EPI_ENERGY) k_share_finish_ens<true, FW><<<g, 64 * FW, 0, st>>>(S, runs, chunks, traps, t0, step);
+    else k_share_finish_ens<false, FW><<<g, 64 * FW, 0, st>>>(S, runs, chunks, traps, t0, step);
+}
+
+cb_status md_run_shares_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* s, const double* q,
+                                 const double* m, const cb_trap* traps, double t0, double dt, int64_t nsteps,
+                                 double eps2, int32_t prec, uint32_t flags, double* energies, int64_t every, void* ws,
+                                 size_t ws_bytes, hipStream_t st) {
+    ShareEns E;
+    if (!share_ens(nrun, offsets, E) || ws_bytes < E.bytes)
+        return fail(CB_ENOWS, "md_run: the ensemble path needs %zu workspace bytes, has %zu", E.bytes, ws_bytes);
+    const size_t slots = (size_t)E.all.N + E.rows, nch = E.chunks.size();
+    char* base = static_cast<char*>(ws);
+    auto carve = [&](size_t bytes) {
+        char* p = base;
+        base += al(bytes);
+        return p;
+    };
+    int4* d_runs = reinterpret_cast<int4*>(carve(sizeof(int4) * nrun));
+    int2* d_first = reinterpret_cast<int2*>(carve(sizeof(int2) * E.first.size()));
+    int2* d_chunks = reinterpret_cast<int2*>(carve(sizeof(int2) * nch));
+    int2* d_recs = reinterpret_cast<int2*>(carve(sizeof(int2) * nrun));
+    cb_trap* d_traps = reinterpret_cast<cb_trap*>(carve(sizeof(cb_trap) * nrun));
+    double* Pi = reinterpret_cast<double*>(carve(sizeof(double) * 3 * slots * 64 * kEnsP));
+    double* R = reinterpret_cast<double*>(carve(sizeof(double) * 3 * (size_t)E.all.U * kShareJ));
+    double* Et = reinterpret_cast<double*>(carve(sizeof(double) * slots));
+    double* eblk = reinterpret_cast<double*>(carve(sizeof(double) * 3 * nch));
+    HostUpload up;
+    up.add(d_runs, E.runs.data(), sizeof(int4) * nrun);
+    up.add(d_first, E.first.data(), sizeof(int2) * E.first.size());
+    up.add(d_chunks, E.chunks.data(), sizeof(int2) * nch);
+    up.add(d_recs, E.recs.data(), sizeof(int2) * nrun);
+    up.add(d_traps, traps, sizeof(cb_trap) * nrun);
+    if (cb_status urc = up.run(st, "md_run")) return urc;
+    ShareStep S{};
+    S.cut = E.all;
+    S.Pi = Pi;
+    S.R = R;
+    S.Et = Et;
+    S.x = S.xn = s->x;
+    S.y = S.yn = s->y;
+    S.z = S.zn = s->z;
+    S.vx = s->vx; S.vy = s->vy; S.vz = s->vz;
+    S.ax = s->ax; S.ay = s->ay; S.az = s->az;
+    S.q = q;
+    S.m = m;
+    S.dt = dt;
+    S.eblk = eblk;
+    S.flags = flags_ptr();
+    if (!S.flags) return fail(CB_EHIP, "md_run: device flag symbol not found");
+    const long long nrec = energies ? nsteps / every + 1 : 0;
+    auto step = [&](int64_t k, unsigned mode, int64_t rec) -> cb_status {
+        cb_status r;
+        const bool pot = rec >= 0;
+        if (mode & (EPI_ACCEL | EPI_KICK | EPI_ENERGY)) {
+            switch (prec) {
+                case CB_FP64: go_share_ens<PREC_FP64>(pot, E, d_runs, d_first, s, q, eps2, Pi, R, Et, st); break;
+                case CB_MIXED: go_share_ens<PREC_MIXED>(pot, E, d_runs, d_first, s, q, eps2, Pi, R, Et, st); break;
+                case CB_FP64_IEEE: go_share_ens<PREC_IEEE>(pot, E, d_runs, d_first, s, q, eps2, Pi, R, Et, st); break;
+                default: go_share_ens<PREC_FP32>(pot, E, d_runs, d_first, s, q, eps2, Pi, R, Et, st); break;
+            }
+            if ((r = check_launch("k_share_pairs_ens"))) return r;
+        }
+        S.mode = mode;
+        if (nch < kEnsFinishFew) go_finish_ens<8>(S, (unsigned)nch, d_runs, d_chunks, d_traps, t0, k, st);
+        else go_finish_ens<2>(S, (unsigned)nch, d_runs, d_chunks, d_traps, t0, k, st);
+        if ((r = check_launch("k_share_finish_ens")) || rec < 0) return r;
+        k_ens_record<4><<<nrun, 256, 0, st>>>(d_recs, eblk, nrec, rec, energies);
+        return check_launch("k_ens_record");
+    };
+    const unsigned mode0 = ((flags & CB_INIT_ACCEL) ? EPI_ACCEL : 0u) | (energies ? EPI_ENERGY : 0u) |
+                           (nsteps > 0 ? EPI_DRIFT : 0u);
+    cb_status rc;
+    if (mode0 && (rc = step(0, mode0, energies ? 0 : -1))) return rc;
+    for (int64_t k = 1; k <= nsteps; ++k) {
+        const bool rec = energies && k % every == 0;
+        if ((rc = step(k, EPI_KICK | (rec ? EPI_ENERGY : 0u) | (k < nsteps ? EPI_DRIFT : 0u), rec ? k / every : -1)))
+            return rc;
     }
     return ok();
 }

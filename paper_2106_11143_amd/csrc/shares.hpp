@@ -1,5 +1,6 @@
-// Newton's third law for one run of some thousand ions (device code): the
-// triangle of pairs cut into equal shares, one per workgroup.
+// Newton's third law for one run of some thousand ions, or an ensemble of runs
+// (device code): the triangles of pairs cut into equal shares, one per
+// workgroup.
 //
 // Ions are cut into i-blocks of IB = 64 P; row I is block I against the ions
 // j >= I IB, its own block (the diagonal, of which the pairs j > i count)
@@ -39,16 +40,28 @@ struct ShareCut {
     int len, more;
 };
 
-__host__ __device__ __forceinline__ ShareCut share_cut(int n, int P, int maxN) {
-    ShareCut c;
+// The rows alone (N, len and more unset).
+__host__ __device__ __forceinline__ ShareCut share_rows(int n, int P) {
+    ShareCut c{};
     c.n = n;
     c.IB = 64 * P;
     c.C = (n + kShareJ - 1) / kShareJ;
     c.nI = (n + c.IB - 1) / c.IB;
     c.U = c.nI * c.C - c.IB / kShareJ * (c.nI * (c.nI - 1) / 2);
+    return c;
+}
+
+// U units into at most maxN shares.
+__host__ __device__ __forceinline__ void share_units(ShareCut& c, int U, int maxN) {
+    c.U = U;
     c.N = maxN < c.U ? maxN : c.U;
     c.len = (int)((unsigned)c.U / (unsigned)c.N);
     c.more = c.U - c.len * c.N;
+}
+
+__host__ __device__ __forceinline__ ShareCut share_cut(int n, int P, int maxN) {
+    ShareCut c = share_rows(n, P);
+    share_units(c, c.U, maxN);
     return c;
 }
 
@@ -68,7 +81,7 @@ __host__ __device__ __forceinline__ int unit_share(const ShareCut& c, int u) {
 
 // Pairs of one wave: j's [j0, j1) against the lane's P ions of the block at
 // jb, reactions to Rt[c * stride + j - jb], i sums into ia, pair energy into
-// pe.  DIAG: j's of the block itself.
+// pe.  DIAG: j's of the block itself (see sym_group).
 template <int PREC, int P, bool UNI, bool POT, bool DIAG>
 __device__ __forceinline__ void share_wave(const double* __restrict__ x, const double* __restrict__ y,
                                            const double* __restrict__ z, const double* __restrict__ q, double eps2,
@@ -116,6 +129,66 @@ union ShareLds {
     double sum[kShareWaves][3 * 64 * P];
 };
 
+// Units [ua, ub) of the nu of row I of a run of n ions, by the workgroup: i
+// sums to Pt[3][IB], reactions to Rt[c nu kShareJ + j - I IB], the pair energy
+// (POT) to Et[0].
+template <int PREC, int P, bool POT>
+__device__ __forceinline__ void share_row(int n, const double* __restrict__ x, const double* __restrict__ y,
+                                          const double* __restrict__ z, const double* __restrict__ q, double eps2,
+                                          int I, int nu, int ua, int ub, ShareLds<P>& lds, double (&esum)[kShareWaves],
+                                          double* __restrict__ Pt, double* __restrict__ Rt, double* __restrict__ Et) {
+    constexpr int IB = 64 * P;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ib = I * IB;
+    double xi[P], yi[P], zi[P], qi[P], ia[P][3], pe = 0.0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int i = min(ib + p * 64 + lane, n - 1);
+        xi[p] = x[i];
+        yi[p] = y[i];
+        zi[p] = z[i];
+        qi[p] = q[i];
+        ia[p][0] = ia[p][1] = ia[p][2] = 0.0;
+    }
+    // the wave's j's: the w-th quarter, a whole group per unit
+    const int j0 = min(n, ib + ua * kShareJ + w * (ub - ua) * kGroupJ);
+    const int j1 = min(n, j0 + (ub - ua) * kGroupJ);
+    const int jd = ib + IB;  // the block's own ions end here
+    const int stride = nu * kShareJ;
+    const int jo = max(j0, jd);
+    if (j1 > jo) {
+        double qI, qJ;
+        if (tile_charges<P>(qi, q, jo, j1, qI, qJ))
+            share_wave<PREC, P, true, POT, false>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, qI, qJ, ia, pe,
+                                                  lds.red[w], Rt);
+        else
+            share_wave<PREC, P, false, POT, false>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, 1.0, 1.0, ia,
+                                                   pe, lds.red[w], Rt);
+    }
+    if (j0 < min(j1, jd))
+        share_wave<PREC, P, false, POT, true>(x, y, z, q, eps2, j0, min(j1, jd), ib, stride, xi, yi, zi, qi, 1.0, 1.0,
+                                              ia, pe, lds.red[w], Rt);
+    if constexpr (POT) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) pe += __shfl_xor(pe, o);
+        if (lane == 0) esum[w] = pe;
+    }
+    __syncthreads();  // the reduction buffers become the waves' sums
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int p = 0; p < P; ++p) lds.sum[w][c * IB + p * 64 + lane] = ia[p][c];
+    __syncthreads();
+    for (int k = threadIdx.x; k < 3 * IB; k += 64 * kShareWaves) {
+        double a = lds.sum[0][k];
+#pragma unroll
+        for (int v = 1; v < kShareWaves; ++v) a += lds.sum[v][k];
+        Pt[k] = a;
+    }
+    if (POT && threadIdx.x == 0) Et[0] = (esum[0] + esum[1]) + (esum[2] + esum[3]);
+}
+
 // Share blockIdx.x of the cut.  i sums of row I to Pi[blockIdx.x + I][3][IB],
 // reactions of row I on its j's to R[3 row_unit(I) kShareJ + c row_units(I)
 // kShareJ + j - I IB], pair energies (POT) to Et[blockIdx.x + I].  cut: the
@@ -127,10 +200,6 @@ __global__ void __launch_bounds__(64 * kShareWaves, (sym_waves<PREC, P, POT>()))
                   double* __restrict__ R, double* __restrict__ Et) {
     __shared__ __align__(16) ShareLds<P> lds;
     __shared__ double esum[kShareWaves];
-    constexpr int IB = 64 * P;
-    const int n = cut.n;
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = blockIdx.x;
     int u = share_unit(cut, g);
     const int uend = share_unit(cut, g + 1);
@@ -146,57 +215,46 @@ __global__ void __launch_bounds__(64 * kShareWaves, (sym_waves<PREC, P, POT>()))
     for (; u < uend; ++I) {
         const int u0 = row_unit(cut, I), nu = row_units(cut, I);
         const int ue = min(uend, u0 + nu);  // this share's units of the row: [u, ue)
-        const int ib = I * IB;
-        double xi[P], yi[P], zi[P], qi[P], ia[P][3], pe = 0.0;
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const int i = min(ib + p * 64 + lane, n - 1);
-            xi[p] = x[i];
-            yi[p] = y[i];
-            zi[p] = z[i];
-            qi[p] = q[i];
-            ia[p][0] = ia[p][1] = ia[p][2] = 0.0;
-        }
-        // the wave's j's: the w-th quarter, a whole group per unit
-        const int j0 = min(n, ib + (u - u0) * kShareJ + w * (ue - u) * kGroupJ);
-        const int j1 = min(n, j0 + (ue - u) * kGroupJ);
-        const int jd = ib + IB;  // the block's own ions end here
-        const int stride = nu * kShareJ;
-        double* Rt = R + (size_t)3 * u0 * kShareJ;
-        const int jo = max(j0, jd);
-        if (j1 > jo) {
-            double qI, qJ;
-            if (tile_charges<P>(qi, q, jo, j1, qI, qJ))
-                share_wave<PREC, P, true, POT, false>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, qI, qJ, ia,
-                                                      pe, lds.red[w], Rt);
-            else
-                share_wave<PREC, P, false, POT, false>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, 1.0, 1.0,
-                                                       ia, pe, lds.red[w], Rt);
-        }
-        if (j0 < min(j1, jd))
-            share_wave<PREC, P, false, POT, true>(x, y, z, q, eps2, j0, min(j1, jd), ib, stride, xi, yi, zi, qi, 1.0,
-                                                  1.0, ia, pe, lds.red[w], Rt);
-        if constexpr (POT) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) pe += __shfl_xor(pe, o);
-            if (lane == 0) esum[w] = pe;
-        }
-        __syncthreads();  // the reduction buffers become the waves' sums
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-            for (int p = 0; p < P; ++p) lds.sum[w][c * IB + p * 64 + lane] = ia[p][c];
-        __syncthreads();
         const size_t slot = (size_t)(g + I);
-        for (int k = threadIdx.x; k < 3 * IB; k += 64 * kShareWaves) {
-            double a = lds.sum[0][k];
-#pragma unroll
-            for (int v = 1; v < kShareWaves; ++v) a += lds.sum[v][k];
-            Pi[slot * 3 * IB + k] = a;
-        }
-        if (POT && threadIdx.x == 0) Et[slot] = (esum[0] + esum[1]) + (esum[2] + esum[3]);
+        share_row<PREC, P, POT>(cut.n, x, y, z, q, eps2, I, nu, u - u0, ue - u0, lds, esum, Pi + slot * 3 * 64 * P,
+                                R + (size_t)3 * u0 * kShareJ, Et + slot);
         u = ue;
         if (u < uend) __syncthreads();  // the next row rewrites the buffers
+    }
+}
+
+// The rows of many runs, one run after the other, in equal shares.  runs[r]:
+// its first ion, its ions, its first row and first unit among all rows and
+// units; first[g]: the run and the row (of the run) where share g starts.
+// cut: N, len and more of all units.  i sums, reactions and pair energies as
+// above, with rows and units counted over all runs.
+template <int PREC, int P, bool POT>
+__global__ void __launch_bounds__(64 * kShareWaves, (sym_waves<PREC, P, POT>()))
+    k_share_pairs_ens(ShareCut all, const int4* __restrict__ runs, const int2* __restrict__ first,
+                      const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+                      const double* __restrict__ q, double eps2, double* __restrict__ Pi, double* __restrict__ R,
+                      double* __restrict__ Et) {
+    __shared__ __align__(16) ShareLds<P> lds;
+    __shared__ double esum[kShareWaves];
+    const int g = blockIdx.x;
+    int u = share_unit(all, g);
+    const int uend = share_unit(all, g + 1);
+    const int2 at = first[g];
+    int r = at.x, I = at.y;
+    while (u < uend) {
+        const int4 ru = runs[r];
+        const ShareCut cut = share_rows(ru.y, P);
+        for (; I < cut.nI && u < uend; ++I) {
+            const int u0 = ru.w + row_unit(cut, I), nu = row_units(cut, I);
+            const int ue = min(uend, u0 + nu);
+            const size_t slot = (size_t)(g + ru.z + I);
+            share_row<PREC, P, POT>(ru.y, x + ru.x, y + ru.x, z + ru.x, q + ru.x, eps2, I, nu, u - u0, ue - u0, lds,
+                                    esum, Pi + slot * 3 * 64 * P, R + (size_t)3 * u0 * kShareJ, Et + slot);
+            u = ue;
+            if (u < uend) __syncthreads();
+        }
+        ++r;
+        I = 0;
     }
 }
 
