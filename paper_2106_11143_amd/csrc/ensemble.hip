@@ -6,8 +6,8 @@
 //      run, one wave per tile, longest tiles first.  A tile entry holds its
 //      run's first ion and size, the slot of its partials, and its row and
 //      segment.
-//      Each row's first tiles are its diagonal block (the ordered pairs
-//      inside the i-block, evaluated directly) cut into j-ranges of 128.
+//      Each row's first tiles are its diagonal block (the pairs inside the
+//      i-block), in small launches the ordered ones, cut into j-ranges of 128.
 //   2. k_ens_step: per 64 ions of one run, the finish of the force (the i
 //      sums of its row and the reactions from the rows above, each summed in
 //      a fixed order) fused with the trap, the kick and the next drift.  The drift writes the other of two
@@ -48,9 +48,9 @@ constexpr int kDiagSeg = 0xffff;     // segment field of diagonal sub-tile d: kD
 constexpr int kDiagMax = 8;          // sub-tiles per block at most (IB <= 1024)
 
 template <int PREC, int P>
-__device__ __forceinline__ void diag_tile(int n, const double* __restrict__ x, const double* __restrict__ y,
-                                          const double* __restrict__ z, const double* __restrict__ q, double eps2,
-                                          int I, int d, int DL, int t, double* __restrict__ Pi) {
+__device__ __forceinline__ void diag_direct(int n, const double* __restrict__ x, const double* __restrict__ y,
+                                            const double* __restrict__ z, const double* __restrict__ q, double eps2,
+                                            int I, int d, int DL, int t, double* __restrict__ Pi) {
     constexpr int IB = 64 * P;
     constexpr int H = P < 4 ? P : 4;  // i rows held per pass: the block in P / H passes over its j's
     const int lane = threadIdx.x;
@@ -117,6 +117,66 @@ __device__ __forceinline__ void diag_tile(int n, const double* __restrict__ x, c
     }
 }
 
+// The whole diagonal of row I by Newton's third law, as the row's other tiles:
+// i sums to Pi[t], reactions on the j's to R[t][3][JL].  Of the block's lanes
+// of 64 only those up to the j's own are taken, 5/8 of the pairs of i and j (512
+// runs of 64-4096 ions: 1056 us per launch, 1119 with the ordered pairs).
+// Lanes beyond a short block hold its last ion again; no j is past them.  For
+// launches whose diagonals are not split, with 4 ions per lane: in a small
+// launch the waves wait for the longest tile (16 runs of 2048-4096 ions 87 us
+// per step with the ordered pairs in halves, 93 with halves of this, 112 with
+// this), and 8 ions per lane need more registers than there are (256 runs of
+// 64-2048 ions 241 against 287).
+constexpr bool diag_is_sym(int P, int DL) { return P == 4 && DL == 64 * P; }
+
+template <int PREC, int P>
+__device__ __forceinline__ void diag_sym(int n, const double* __restrict__ x, const double* __restrict__ y,
+                                         const double* __restrict__ z, const double* __restrict__ q, double eps2,
+                                         int JL, int I, int t, double* __restrict__ red, double* __restrict__ Pi,
+                                         double* __restrict__ R) {
+    constexpr int IB = 64 * P;
+    const int lane = threadIdx.x;
+    const int j0 = I * IB, j1 = min(n, j0 + IB);
+    double xi[P], yi[P], zi[P], qi[P], ia[P][3], pe = 0.0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int i = min(j0 + p * 64 + lane, n - 1);
+        xi[p] = x[i];
+        yi[p] = y[i];
+        zi[p] = z[i];
+        qi[p] = q[i];
+        ia[p][0] = ia[p][1] = ia[p][2] = 0.0;
+    }
+    double* Rt = R + (size_t)t * 3 * JL;
+    const SeriesK K;
+    const int full = j0 + (j1 - j0) / kGroupJ * kGroupJ;
+    int jg = j0;
+    if (jg < full) {
+        JGroup cur;
+        load_group<false>(cur, jg, 0, x, y, z, q);
+        for (; jg < full; jg += kGroupJ) {
+            JGroup nxt;
+            const int jn = jg + kGroupJ;
+            load_group<false>(nxt, jn < full ? jn : jg, 0, x, y, z, q);
+            __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the arithmetic
+            sym_group<PREC, P, 1, false, false, false, true>(cur, jg, kGroupJ, j0, JL, eps2, xi, yi, zi, qi, ia, pe, K,
+                                                             1.0, Rt, red, j0);
+            cur = nxt;
+        }
+    }
+    if (jg < j1) {
+        JGroup tail;
+        load_group<true>(tail, jg, j1 - jg - 1, x, y, z, q);
+        sym_group<PREC, P, 1, true, false, false, true>(tail, jg, j1 - jg, j0, JL, eps2, xi, yi, zi, qi, ia, pe, K, 1.0,
+                                                        Rt, red, j0);
+    }
+    double* Pt = Pi + (size_t)t * 3 * IB;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) Pt[(size_t)c * IB + p * 64 + lane] = ia[p][c];
+}
+
 template <int PREC, int P>
 __global__ void __launch_bounds__(64, (sym_waves<PREC, P>())) k_pair_sym_ens(const double* __restrict__ x,
                                                                      const double* __restrict__ y,
@@ -129,11 +189,17 @@ __global__ void __launch_bounds__(64, (sym_waves<PREC, P>())) k_pair_sym_ens(con
     const int4 tl = tiles[blockIdx.x];  // first ion, ions, slot, row << 16 | segment
     const int o = tl.x;
     const int sg = tl.w & 0xffff;
-    if (sg > kDiagSeg - kDiagMax)
-        diag_tile<PREC, P>(tl.y, x + o, y + o, z + o, q + o, eps2, tl.w >> 16, kDiagSeg - sg, DL, tl.z, Pi);
-    else
+    if (sg > kDiagSeg - kDiagMax) {
+        if constexpr (diag_is_sym(P, 64 * P))
+            if (diag_is_sym(P, DL)) {
+                diag_sym<PREC, P>(tl.y, x + o, y + o, z + o, q + o, eps2, JL, tl.w >> 16, tl.z, red_buf, Pi, R);
+                return;
+            }
+        diag_direct<PREC, P>(tl.y, x + o, y + o, z + o, q + o, eps2, tl.w >> 16, kDiagSeg - sg, DL, tl.z, Pi);
+    } else {
         sym_tile<PREC, P, 1>(tl.y, x + o, y + o, z + o, q + o, eps2, JL, tl.w >> 16, sg, tl.z, red_buf,
                              Pi, R);
+    }
 }
 
 struct EnsParams {
@@ -149,6 +215,7 @@ struct EnsParams {
     const double* m;
     double *vx, *vy, *vz, *ax, *ay, *az;
     int IB, JL, lgJL;
+    bool diag_sym;  // the rows' diagonals leave reactions
     int ndiag;  // diagonal sub-tiles (slots) at the head of every full row, 0 without tiles
     double eps2, t0, dt;
     long long step;     // the trap is taken at step_time(t0, dt, step)
@@ -294,7 +361,7 @@ __global__ void __launch_bounds__(64 * PARTS) k_ens_step(EnsParams P) {
         else if (need_f) direct_range<PREC, true, false>(lo, hi, kc, xk, yk, zk, X, Y, Z, Q, P.eps2, K, f, u);
         else if (need_p) direct_range<PREC, false, true>(lo, hi, kc, xk, yk, zk, X, Y, Z, Q, P.eps2, K, f, u);
     } else {
-        // (the pairs inside the ion's own i-block come from the row's diagonal sub-tiles)
+        // (the pairs inside the ion's own i-block: the row's diagonal sub-tiles)
         if (need_p) {  // potential over the whole run
             int lo, hi;
             part_of<PARTS>(0, n, w, lo, hi);
@@ -329,6 +396,12 @@ __global__ void __launch_bounds__(64 * PARTS) k_ens_step(EnsParams P) {
                     v[4] += a[u][1];
                     v[5] += a[u][2];
                 }
+        }
+        if (P.diag_sym && w == PARTS - 1) {  // the reactions inside the ion's own block
+            const double* Rt = P.R + (size_t)rowstart[Ik] * 3 * JL + off;
+            v[kVals - 4] += Rt[0];
+            v[kVals - 3] += Rt[JL];
+            v[kVals - 2] += Rt[2 * JL];
         }
         part_of<PARTS>(0, Ik, w, lo, hi);
         for (int I = lo; I < hi; I += U) {
@@ -573,6 +646,7 @@ cb_status md_run_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* 
     int lgJL = 0;
     while ((1 << lgJL) < JL) ++lgJL;
     EP.lgJL = lgJL;
+    EP.diag_sym = diag_is_sym(P, E.dl);
     EP.ndiag = E.ndiag;
     EP.eps2 = eps2;
     EP.t0 = t0;
