@@ -18,13 +18,19 @@ from . import api
 trap_k = api.trap_k
 
 
+def _rows(r):
+    """x, y and z of a (3, n) tensor, contiguous."""
+    if r.dim() != 2 or r.shape[0] != 3:
+        return r[0].contiguous(), r[1].contiguous(), r[2].contiguous()
+    return r.contiguous().unbind(0)
+
+
 class CoulombTrapGrad(torch.autograd.Function):
     """G(r) = dU/dr = -F_C(r) + m k r; backward: H(r) w."""
 
     @staticmethod
     def forward(ctx, r, q, m, trap, t, eps2, prec):
-        G, _ = api.coulomb_trap_grad(r[0].contiguous(), r[1].contiguous(), r[2].contiguous(), q, m, trap, t, eps2,
-                                     prec)
+        G, _ = api.coulomb_trap_grad(*_rows(r), q, m, trap, t, eps2, prec)
         ctx.save_for_backward(r, q, m if m is not None else torch.empty(0))
         ctx.trap, ctx.t, ctx.eps2, ctx.prec, ctx.has_m = trap, t, eps2, prec, m is not None
         return G
@@ -32,8 +38,8 @@ class CoulombTrapGrad(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gG):
         r, q, m = ctx.saved_tensors
-        hv = api.coulomb_hvp(r[0].contiguous(), r[1].contiguous(), r[2].contiguous(), q, gG.contiguous(),
-                             m if ctx.has_m else None, ctx.trap, ctx.t, ctx.eps2, ctx.prec)
+        hv = api.coulomb_hvp(*_rows(r), q, gG.contiguous(), m if ctx.has_m else None, ctx.trap, ctx.t, ctx.eps2,
+                             ctx.prec)
         return hv, None, None, None, None, None, None
 
 
@@ -43,8 +49,7 @@ class CoulombTrapEnergy(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, r, q, m, trap, t, eps2, prec):
-        _, u = api.coulomb_trap_grad(r[0].contiguous(), r[1].contiguous(), r[2].contiguous(), q, m, trap, t, eps2,
-                                     prec, grad=False, energy=True)
+        _, u = api.coulomb_trap_grad(*_rows(r), q, m, trap, t, eps2, prec, grad=False, energy=True)
         u = u[0]
         ctx.save_for_backward(r, q, m if m is not None else torch.empty(0))
         ctx.args = (trap, t, eps2, prec, m is not None)
