@@ -99,7 +99,11 @@ struct RunLds {
 
 // rows_sums' wave sums over the positions X = [3][n] of one step, as they
 // arrive.  False in every thread (the sums are then void) if a wait ran out.
-template <int PREC, int W, bool POT>
+// ALONE: a workgroup that reads what it has published itself; should that not
+// arrive, the flag is set for what follows from it.
+constexpr int kAloneSpins = 1 << 20;
+
+template <int PREC, int W, bool POT, bool ALONE>
 __device__ __forceinline__ bool run_sums(const RowRunParams& P, const double* X, int i0,
                                          const double (&xs)[3][kRunI], RowsLds<kRunI, W, POT>& lds, int& dead) {
     constexpr int C = POT ? 4 : 3, I = kRunI;
@@ -126,8 +130,13 @@ __device__ __forceinline__ bool run_sums(const RowRunParams& P, const double* X,
         for (; jb < n; jb += 64 * W) {
             for (int s = 0; __any(unset(xj) || unset(yj) || unset(zj)); ++s) {
                 const bool look = (s & 15) == 15;
-                if (s >= P.spins ||
-                    (look && __hip_atomic_load(P.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                if (ALONE) {
+                    if (s >= kAloneSpins) {
+                        if (lane == 0) atomicOr(P.flags, 1u);
+                        break;
+                    }
+                } else if (s >= P.spins ||
+                           (look && __hip_atomic_load(P.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                     if (lane == 0) {
                         dead = 1;
                         __hip_atomic_store(P.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -173,7 +182,7 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
     constexpr int I = kRunI;
     const int n = P.n, t = threadIdx.x;
     const int g0 = ONE ? (int)blockIdx.x : 0, g1 = ONE ? g0 + 1 : (n + I - 1) / I;
-    if (t == 0) lds.dead = 0;
+    if (t == 0) lds.dead = ONE && __hip_atomic_load(P.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (t < P.nk) {
         lds.k[t][0] = P.k[t].kx;
         lds.k[t][1] = P.k[t].ky;
@@ -218,6 +227,7 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
     // (what the ring holds of a run that gave up is overwritten before it is read)
     if (!ONE) __threadfence();
     __syncthreads();
+    if (lds.dead) return;  // (given up before this workgroup started, or not admitted)
     int rec = 0, due = REC ? P.phase : 0;
     for (int s = 1; s <= P.nk; ++s) {
         const bool record = REC && ++due == P.every;
@@ -232,10 +242,10 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
             }
             bool live;
             if constexpr (REC) {
-                if (record) live = run_sums<PREC, W, true>(P, X, i0, lds.x, lds.p, lds.dead);
-                else live = run_sums<PREC, W, false>(P, X, i0, lds.x, lds.f, lds.dead);
+                if (record) live = run_sums<PREC, W, true, !ONE>(P, X, i0, lds.x, lds.p, lds.dead);
+                else live = run_sums<PREC, W, false, !ONE>(P, X, i0, lds.x, lds.f, lds.dead);
             } else {
-                live = run_sums<PREC, W, false>(P, X, i0, lds.x, lds.f, lds.dead);
+                live = run_sums<PREC, W, false, !ONE>(P, X, i0, lds.x, lds.f, lds.dead);
             }
             if (!live) return;
             double pot = 0.0;
