@@ -262,9 +262,13 @@ cb_status md_run_rows(int64_t n, const cb_state* s, const double* q, const doubl
 // Its steps by workgroups that stay resident (rows_run.hpp): whether a run
 // takes them, and the steps themselves, from accelerations at t0 on; spins:
 // polls of one wait for a position before the launch gives up (its end then
-// takes the steps by one workgroup).
+// takes the steps, in an order that waits for no workgroup without a place).
+// Some ms, several times what a run of another process may hold the places,
+// since only the wait for a place can be long (us per step of two processes
+// with runs of 1280 ions, alone 4.4: 8.4 while each waits for the other's runs,
+// 25 with 2^11 polls, which give up on them).
 constexpr int64_t kRowsRunMaxN = 1280;
-constexpr int kRunSpins = 1 << 18;
+constexpr int kRunSpins = 1 << 13;
 size_t rows_run_ws_bytes(int64_t n);
 bool rows_run_fits(int64_t n, int64_t nsteps, size_t ws_bytes);
 cb_status rows_run(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap, double t0,

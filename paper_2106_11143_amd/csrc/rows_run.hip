@@ -62,9 +62,10 @@ static void go_run(const RowRunParams& P, hipStream_t st) {
     const unsigned most = (unsigned)(kRunWavesPerCu * cu_count());
     std::lock_guard<std::mutex> lock(run_mutex);
     k_rows_run_begin<<<(unsigned)std::min(256, (len + 1023) / 1024), 256, 0, st>>>(
-        reinterpret_cast<unsigned long long*>(P.pub), len, P.abort, (unsigned)(quads * W), most, kRunAdmitPolls);
+        reinterpret_cast<unsigned long long*>(P.pub), len, P.abort, (unsigned)(quads * W), most,
+        P.spins < 0 ? 0 : kRunAdmitPolls, P.spins == 0);
     k_rows_run<PREC, W, REC><<<(unsigned)quads, 64 * W, 0, st>>>(P);
-    k_rows_run_end<PREC, W, REC><<<1, 64 * W, 0, st>>>(P);
+    k_rows_run_end<PREC, W, REC><<<(unsigned)quads, 64 * W, 0, st>>>(P);
 }
 
 template <int PREC>
@@ -119,9 +120,8 @@ cb_status rows_run(int64_t n, const cb_state* s, const double* q, const double* 
 
 }  // namespace cb
 
-// rows_run with the bound on its waits given (0: it gives up at once, and one
-// workgroup takes the steps), for the test of that path; the accelerations are
-// the state's.
+// rows_run with the bound on its waits given (0: it gives up at once, -1: it is
+// not admitted), for the test of those paths; the accelerations are the state's.
 extern "C" cb_status cb_rows_run_spins(int64_t n, const cb_state* s, const double* q, const double* m,
                                        const cb_trap* trap, double t0, double dt, int64_t nsteps, double eps2,
                                        int32_t prec, double* energies, int64_t every, int32_t spins, void* ws,

@@ -32,8 +32,14 @@
 // graph's launches between another stream's) is caught by a bound on every
 // wait: a workgroup whose wait runs out raises `abort`, on which all of them
 // end.  Nothing of the caller's is written meanwhile: k_rows_run_end commits
-// the results, or if `abort` is up first takes the same steps itself, by one
-// workgroup that waits for nobody.
+// the results, or if `abort` is up takes the same steps itself, in an order
+// that needs no workgroup but those that have a place.  Its workgroups take the
+// groups of four ions of step after step by a running number (a ticket) and
+// wait for the steps before their own alone, whose tickets were taken earlier,
+// by workgroups that run: the lowest ticket not yet done never waits, so every
+// wait ends, with any number of them on the chip (us per step of a run that
+// gave up, by one workgroup / so / a launch per step: 150 ions 56 / 4.7 / 5.9,
+// 1024 603 / 8.7 / 6.0, 1280 815 / 12.1 / 6.9).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -44,6 +50,7 @@ namespace cb {
 
 constexpr int kRunSteps = 128;  // steps per launch: its kernel arguments hold their trap's spring constants
 constexpr int kRunRing = 8;
+constexpr int kTaken = 16, kDone = 32;  // (words, each in a line of its own)
 constexpr unsigned long long kUnset = 0x7ff4'5a5a'7ff4'5a5aull;
 
 struct RowRunParams {
@@ -53,7 +60,7 @@ struct RowRunParams {
     double* pub;               // [kRunRing][3][n] positions after the last drifts
     double* out;               // [9][n] state after the last step: x y z vx vy vz ax ay az
     double* eblk;              // [records][nquads(n)][3] energy sums of four ions each
-    unsigned* abort;           // [2] give up; the waves this run was admitted with
+    unsigned* abort;           // give up; the waves this run was admitted with; at kTaken and kDone, tickets
     double gamma, dt, eps2;
     int every, phase;          // a record after step k (1 .. nk) where phase + k is a multiple of every (0: none)
     int spins;                 // polls of one wait for a position
@@ -95,15 +102,13 @@ struct RunLds {
     double x[3][kRunI], v[3][kRunI], a[3][kRunI], m[kRunI], q[kRunI], r[3][kRunI];
     double k[kRunSteps][3];  // the trap's spring constants (an indexed kernel argument is a load from memory)
     int dead;
+    unsigned ticket;
 };
 
 // rows_sums' wave sums over the positions X = [3][n] of one step, as they
 // arrive.  False in every thread (the sums are then void) if a wait ran out.
-// ALONE: a workgroup that reads what it has published itself; should that not
-// arrive, the flag is set for what follows from it.
-constexpr int kAloneSpins = 1 << 20;
-
-template <int PREC, int W, bool POT, bool ALONE>
+// THERE: they have all arrived.
+template <int PREC, int W, bool POT, bool THERE>
 __device__ __forceinline__ bool run_sums(const RowRunParams& P, const double* X, int i0,
                                          const double (&xs)[3][kRunI], RowsLds<kRunI, W, POT>& lds, int& dead) {
     constexpr int C = POT ? 4 : 3, I = kRunI;
@@ -128,15 +133,10 @@ __device__ __forceinline__ bool run_sums(const RowRunParams& P, const double* X,
         int jc = min(jb + lane, n - 1);
         double qj = P.q[jc], xj = poll(X + jc), yj = poll(X + n + jc), zj = poll(X + 2 * n + jc);
         for (; jb < n; jb += 64 * W) {
-            for (int s = 0; __any(unset(xj) || unset(yj) || unset(zj)); ++s) {
+            for (int s = 0; !THERE && __any(unset(xj) || unset(yj) || unset(zj)); ++s) {
                 const bool look = (s & 15) == 15;
-                if (ALONE) {
-                    if (s >= kAloneSpins) {
-                        if (lane == 0) atomicOr(P.flags, 1u);
-                        break;
-                    }
-                } else if (s >= P.spins ||
-                           (look && __hip_atomic_load(P.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                if (s >= P.spins ||
+                    (look && __hip_atomic_load(P.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                     if (lane == 0) {
                         dead = 1;
                         __hip_atomic_store(P.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -173,15 +173,18 @@ __device__ __forceinline__ bool run_sums(const RowRunParams& P, const double* X,
     return dead == 0;
 }
 
-// Steps 1 .. nk of the run: the ions' groups of kRunI by the workgroups, group
-// blockIdx.x each (ONE), or all by this workgroup.  Results to P.out.  Thread
-// t < 3 kRunI updates component t / kRunI of ion t % kRunI (as step_update
-// does): one division in the chain from sums to positions instead of three.
+// ONE: steps 1 .. nk of the ions' group blockIdx.x of kRunI, results to P.out.
+// Else step ts (0: the first drift) of group tg, whose state is in P.out
+// meanwhile, the last step's results to the run's state.  Thread t < 3 kRunI
+// updates component t / kRunI of ion t % kRunI (as step_update does): one
+// division in the chain from sums to positions instead of three.
 template <int PREC, int W, bool REC, bool ONE>
-__device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& lds) {
+__device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& lds, int ts = 0, int tg = 0) {
     constexpr int I = kRunI;
     const int n = P.n, t = threadIdx.x;
-    const int g0 = ONE ? (int)blockIdx.x : 0, g1 = ONE ? g0 + 1 : (n + I - 1) / I;
+    // (one group, in loops of one turn: written without them the compiler spills
+    // two registers in the chain, 1024 ions with records 3.4 -> 3.5 us per step)
+    const int g0 = ONE ? (int)blockIdx.x : tg, g1 = g0 + 1;
     if (t == 0) lds.dead = ONE && __hip_atomic_load(P.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (t < P.nk) {
         lds.k[t][0] = P.k[t].kx;
@@ -203,6 +206,13 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
         P.out[(size_t)(3 + c) * n + k] = lds.v[c][u];
         P.out[(size_t)(6 + c) * n + k] = lds.a[c][u];
     };
+    // (a step's results for other workgroups; nobody reads the run's state any
+    // more when the last step's get there)
+    auto pass = [&](int k, bool last) {
+        publish(last ? (c == 0 ? P.x : (c == 1 ? P.y : P.z)) + k : P.out + (size_t)c * n + k, lds.x[c][u]);
+        publish(last ? (c == 0 ? P.vx : (c == 1 ? P.vy : P.vz)) + k : P.out + (size_t)(3 + c) * n + k, lds.v[c][u]);
+        publish(last ? (c == 0 ? P.ax : (c == 1 ? P.ay : P.az)) + k : P.out + (size_t)(6 + c) * n + k, lds.a[c][u]);
+    };
     auto drift = [&](double* X, int k, bool own, double x, double v, double a, double m) {
         if (P.gamma == 0.0) {
             x = x + v * P.dt + h2 * a;
@@ -214,22 +224,26 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
         lds.x[c][u] = x;
         if (own && !__builtin_isfinite(x)) atomicOr(P.flags, 1u);
     };
-    for (int g = g0; g < g1; ++g) {  // the first drift
+    for (int g = g0; (ONE || ts == 0) && g < g1; ++g) {  // the first drift
         const int k = min(g * I + u, n - 1);
         if (mine) {
             load(k, c == 0 ? P.x : (c == 1 ? P.y : P.z), c == 0 ? P.vx : (c == 1 ? P.vy : P.vz),
                  c == 0 ? P.ax : (c == 1 ? P.ay : P.az));
             drift(P.pub + (size_t)(1 % kRunRing) * 3 * n, k, g * I + u < n, lds.x[c][u], lds.v[c][u], lds.a[c][u],
                   lds.m[u]);
-            if (!ONE && g * I + u < n) save(k);
+            if (!ONE && g * I + u < n) pass(k, false);
         }
     }
-    // (what the ring holds of a run that gave up is overwritten before it is read)
-    if (!ONE) __threadfence();
+    if (!ONE && ts == 0) return;
     __syncthreads();
     if (lds.dead) return;  // (given up before this workgroup started, or not admitted)
     int rec = 0, due = REC ? P.phase : 0;
-    for (int s = 1; s <= P.nk; ++s) {
+    if (REC && !ONE) {
+        due += ts - 1;
+        rec = due / P.every;
+        due -= rec * P.every;
+    }
+    for (int s = ONE ? 1 : ts; s <= (ONE ? P.nk : ts); ++s) {
         const bool record = REC && ++due == P.every;
         auto ring = [&](int step) { return P.pub + (size_t)(step % kRunRing) * 3 * n; };
         const double* X = ring(s);
@@ -237,7 +251,13 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
             const int i0 = g * I, k = min(i0 + u, n - 1);
             const bool own = i0 + u < n;
             if (!ONE) {
-                if (mine) load(k, P.out + (size_t)c * n, P.out + (size_t)(3 + c) * n, P.out + (size_t)(6 + c) * n);
+                if (mine) {
+                    lds.x[c][u] = poll(P.out + (size_t)c * n + k);
+                    lds.v[c][u] = poll(P.out + (size_t)(3 + c) * n + k);
+                    lds.a[c][u] = poll(P.out + (size_t)(6 + c) * n + k);
+                    lds.m[u] = P.m[k];
+                    lds.q[u] = P.q[k];
+                }
                 __syncthreads();
             }
             bool live;
@@ -272,7 +292,7 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
                 if (REC && record) lds.r[c][u] = x;
                 if (ONE && own) mark(ring(s - 1) + (size_t)c * n + k);
                 if (own && !(__builtin_isfinite(an) && __builtin_isfinite(v))) atomicOr(P.flags, 1u);
-                if (!ONE && own) save(k);
+                if (!ONE && own) pass(k, s == P.nk);
             }
             __syncthreads();  // x is the next step's, the sums' LDS free
             if (REC && record && t < I) {  // the four ions' energies, while their positions travel
@@ -292,16 +312,56 @@ __device__ __forceinline__ void rows_run(const RowRunParams& P, RunLds<W, REC>& 
                 }
             }
         }
-        if (!ONE) {
-            __threadfence();
-            __syncthreads();
-        }
         if (record) {
             ++rec;
             due = 0;
         }
     }
     if (ONE && mine && g0 * I + u < n) save(g0 * I + u);
+}
+
+// Waits until `before` tickets are done; the wait ends by itself (see above), its
+// bound, of half a second, sets the flag.
+constexpr int kTicketSpins = 1 << 20;
+
+__device__ __forceinline__ void wait_tickets(const RowRunParams& P, unsigned before) {
+    const unsigned* done = P.abort + kDone;
+    for (int spin = 0; __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < before; ++spin) {
+        if (spin >= kTicketSpins) {
+            atomicOr(P.flags, 1u);
+            break;
+        }
+        __builtin_amdgcn_s_sleep(2);
+    }
+}
+
+// Waits for the wave's stores.  What workgroups exchange here they write and
+// read past the L2s (agent-scope atomics), so nothing is to be written back or
+// dropped, as a fence would: by every wave that took 0.15 us a ticket, one
+// after the other (1024 ions 40 us per step; by one thread 14, and so 7.5).
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The run's steps after giving up, by as many workgroups as run: ticket s G + g
+// is step s of group g of G.  The positions of step s + 2 are written when all
+// tickets of step s are done, so never over positions that are still read.
+template <int PREC, int W, bool REC>
+__device__ __forceinline__ void rows_run_tickets(const RowRunParams& P, RunLds<W, REC>& lds) {
+    const unsigned groups = (unsigned)run_quads(P.n), all = groups * (unsigned)(P.nk + 1);
+    for (;;) {
+        if (threadIdx.x == 0) lds.ticket = atomicAdd(P.abort + kTaken, 1u);
+        __syncthreads();
+        const unsigned ticket = __builtin_amdgcn_readfirstlane(lds.ticket);
+        if (ticket >= all) return;
+        const unsigned s = ticket / groups;
+        if (threadIdx.x == 0 && s > 0) wait_tickets(P, s * groups);
+        __syncthreads();
+        rows_run<PREC, W, REC, false>(P, lds, (int)s, (int)(ticket - s * groups));
+        if (threadIdx.x == 0) {
+            stores_done();  // (all of them are this wave's)
+            atomicAdd(P.abort + kDone, 1u);
+        }
+        __syncthreads();
+    }
 }
 
 // Two workgroups of 8 waves (four of 4) on each CU.
@@ -315,10 +375,11 @@ __global__ void __launch_bounds__(64 * W, 4) k_rows_run(RowRunParams P) {
 static __device__ unsigned g_run_waves;
 
 // pub (len words) is marked as not yet written, and the run of `waves` waves
-// admitted beside others up to `most` in all, or (after `polls` tries) given up.
+// admitted beside others up to `most` in all, or (after `polls` tries) given
+// up; give_up: also when admitted.
 static __global__ void __launch_bounds__(256) k_rows_run_begin(unsigned long long* __restrict__ pub, int len,
                                                                unsigned* __restrict__ abort, unsigned waves,
-                                                               unsigned most, int polls) {
+                                                               unsigned most, int polls, bool give_up) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     for (int k = i; k < len; k += gridDim.x * 256) pub[k] = kUnset;
     if (i != 0) return;
@@ -328,8 +389,9 @@ static __global__ void __launch_bounds__(256) k_rows_run_begin(unsigned long lon
         if (now + waves <= most && atomicCAS(&g_run_waves, now, now + waves) == now) got = waves;
         else __builtin_amdgcn_s_sleep(8);
     }
-    abort[0] = got == 0;
+    abort[0] = got == 0 || give_up;
     abort[1] = got;
+    abort[kTaken] = abort[kDone] = 0;
 }
 
 // The results of k_rows_run into the run's state, after its steps were taken
@@ -337,13 +399,13 @@ static __global__ void __launch_bounds__(256) k_rows_run_begin(unsigned long lon
 template <int PREC, int W, bool REC>
 __global__ void __launch_bounds__(64 * W, 4) k_rows_run_end(RowRunParams P) {
     __shared__ __align__(16) RunLds<W, REC> lds;
-    if (threadIdx.x == 0 && P.abort[1]) atomicSub(&g_run_waves, P.abort[1]);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && P.abort[1]) atomicSub(&g_run_waves, P.abort[1]);
     if (P.abort[0]) {
-        rows_run<PREC, W, REC, false>(P, lds);
-        __syncthreads();
+        rows_run_tickets<PREC, W, REC>(P, lds);
+        return;
     }
     double* const s[9] = {P.x, P.y, P.z, P.vx, P.vy, P.vz, P.ax, P.ay, P.az};
-    for (int k = threadIdx.x; k < P.n; k += 64 * W)
+    for (int k = blockIdx.x * 64 * W + threadIdx.x; k < P.n; k += gridDim.x * 64 * W)
 #pragma unroll
         for (int c = 0; c < 9; ++c) s[c][k] = P.out[(size_t)c * P.n + k];
 }
