@@ -505,7 +505,7 @@ def bench_md_single(args, which):
     E = en[0, :, 3].cpu().numpy()
     cfg = api.get_config("md_run", n, "fp64")
     extra = {"energy_rel_range": float((E.max() - E.min()) / abs(E[0])), "nsteps_per_run": nsteps,
-             "launch": cfg,
+             "launch": cfg, "path": api.get_path("md_run", n, "fp64"),
              "roofline": _roof(force_eval_flops(n, cfg["algo"]) * nsteps, ms * 1e-3,
                                "whole md_run (force stage + fused epilogue per step, energies as recorded)",
                                _force_convention(cfg["algo"]))}
@@ -787,10 +787,9 @@ def bench_rsqrt_sweep(args):
             ms = e0.elapsed_time(e1) / reps
             Fh = np.stack([t.cpu().numpy() for t in F])[:, idx]
             err = np.linalg.norm(Fh - ref, axis=0) / np.linalg.norm(ref, axis=0)
-            cfg = api.get_config("forces", n, prec)
             rows.append({"n": n, "variant": prec, "ms": ms, "pairs_per_s": float(n) * n / (ms * 1e-3),
                          "max_rel_err": float(err.max()), "rms_rel_err": float(np.sqrt(np.mean(err ** 2))),
-                         "algo": cfg["algo"]})
+                         "path": api.get_path("forces", n, prec), "algo": api.get_config("forces", n, prec)["algo"]})
             print(f"n={n:6d} {prec:5s} {ms:9.4f} ms {float(n) * n / (ms * 1e-3):.3e} pairs/s "
                   f"max_err {err.max():.2e}", file=sys.stderr, flush=True)
     top = [r for r in rows if r["n"] == sizes[-1]]

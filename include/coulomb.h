@@ -186,14 +186,16 @@ cb_status coulomb_forces_range(int64_t n, int64_t i0, int64_t i1, const double* 
                                const double* q, double eps2, int32_t prec, double* fx, double* fy, double* fz,
                                void* ws, size_t ws_bytes, void* stream);
 
-/* The first stage of coulomb_forces on its own (everything but the final
- * element-wise pass), for timing the pair loop and for callers that finish
- * the sums themselves.  With algorithm 0 (see cb_get_config) the all-pairs
- * kernel (at any n whose reported algorithm is 0) leaves its j-split partial
- * force sums, before the fixed-order sum over splits and the k_C q_i factor, at the start of ws as [splits][3][n]
- * doubles and *splits_out (host) is the number of splits; with algorithms 1,
- * 2 and 4 (the Newton's-third-law stages) the start of ws holds the finished
- * forces [3][n] and *splits_out is 0. */
+/* The force stage that cb_get_config reports for CB_OP_FORCES on its own
+ * (everything but the final element-wise pass), for timing its pair loop and
+ * for callers that finish the sums themselves.  Where cb_get_path is 0 it is
+ * the first stage of coulomb_forces; elsewhere coulomb_forces takes other
+ * launches, with nothing to hand out between them.  With algorithm 0 the
+ * all-pairs kernel leaves its j-split partial force sums, before the
+ * fixed-order sum over splits and the k_C q_i factor, at the start of ws as
+ * [splits][3][n] doubles and *splits_out (host) is the number of splits; with
+ * algorithms 1, 2 and 4 (the Newton's-third-law stages) the start of ws holds
+ * the finished forces [3][n] and *splits_out is 0. */
 cb_status coulomb_pair_stage(int64_t n, const double* x, const double* y, const double* z, const double* q,
                              double eps2, int32_t prec, int32_t* splits_out, void* ws, size_t ws_bytes,
                              void* stream);
@@ -309,7 +311,7 @@ const char* cb_last_error(void);
 
 /* Times the candidate launch configurations (i-particles per lane, workgroup
  * size, j-split count) of `op` at n ions and precision prec on the current
- * device (and the path that an untuned entry takes, see cb_get_config), keeps
+ * device (and the path that an untuned entry takes, see cb_get_path), keeps
  * the fastest for all later calls with n in the same power-of-two bucket, and,
  * when cache_path is non-NULL, merges it into that JSON-lines file.  For md_step / md_run at n <= 8192 the force kernel is
  * tuned for coulomb_forces, and the better of its steps and the one-launch
@@ -321,7 +323,8 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
 /* Loads tuned configurations written by cb_autotune (missing file: CB_OK). */
 cb_status cb_load_tuning(const char* cache_path);
 
-/* The launch configuration the next call of `op` at (n, prec) will use:
+/* The launch configuration of `op` at (n, prec), which its next call will use
+ * unless cb_get_path says otherwise:
  * out[0] = algorithm (0: every ordered pair evaluated, j-split partial sums;
  *          1: each unordered pair evaluated once and applied to both ions by
  *          Newton's third law, forces only, n <= 2^18, the reactions summed
@@ -339,17 +342,26 @@ cb_status cb_load_tuning(const char* cache_path);
  *          j-parts (algorithm 3; 1..32 are accepted, the launch's shape
  *          follows n alone),
  * out[4] = 1 if it came from tuning or cb_set_config.
- * An untuned entry of the forces, energy (and gradient), md_step or md_run
- * takes, in the place of what is reported here: up to 6144 ions, whole rows of
- * the pair sum per workgroup in one launch (as algorithm 3); up to 57344
- * (except where the reported tiles fill the chip evenly), the
- * Newton's-third-law pairs in equal shares per workgroup; beyond 2^18,
- * algorithm 4's tiles (p = 8, segments of 512) in bands whose partial sums fit
- * the workspace.  A tuned entry takes the first two where they were faster;
- * an entry set by cb_set_config runs as set.
  * CB_EINVAL for a NULL out, n outside [1, 2^28], or an op or prec outside
  * its enum. */
 cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);
+
+/* The path of the next call of `op` (forces, energy, md_step, md_run of one
+ * run, HVP, adjoint; coulomb_trap_grad takes that of the forces, or with the
+ * energy that of the energy) at (n, prec), to *path_out:
+ * 0 = the launches that cb_get_config reports;
+ * 1 = whole rows of the pair sum per workgroup in one launch (as algorithm 3);
+ * 2 = the Newton's-third-law pairs in equal shares per workgroup;
+ * 3 = algorithm 4's tiles (p = 8, segments of 512) in bands whose partial sums
+ *     fit the workspace.
+ * An untuned entry of the forces, energy, md_step or md_run takes 1 up to 6144
+ * ions, 2 up to 57344 (except where the reported tiles fill the chip evenly), 3
+ * beyond 2^18.  A tuned entry takes them where they were faster, an entry set
+ * by cb_set_config runs as set, and CB_MIXED_F32D always runs as reported.
+ * CB_EINVAL for a NULL path_out, n outside [1, 2^28], an op that is none of
+ * these (an ensemble's path follows the sizes of its runs, see md_run) or a
+ * prec outside its enum. */
+cb_status cb_get_path(int32_t op, int64_t n, int32_t prec, int32_t* path_out);
 
 /* Forces the launch configuration for (op, n power-of-two bucket, prec), with
  * the fields of cb_get_config.  Algorithm 0: p in {1,2,4} ({1,2} for the HVP

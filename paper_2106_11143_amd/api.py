@@ -24,12 +24,13 @@ CB_OK, CB_EINVAL, CB_EHIP, CB_ENOWS, CB_ENONFINITE, CB_EUNSUPPORTED = range(6)
 STATUS_NAMES = {0: "CB_OK", 1: "CB_EINVAL", 2: "CB_EHIP", 3: "CB_ENOWS", 4: "CB_ENONFINITE", 5: "CB_EUNSUPPORTED"}
 PRECISIONS = {"fp64": 0, "mixed": 1, "ieee": 2, "fp32": 3, "mixed_f32d": 4}
 OPS = {"forces": 0, "energy": 1, "md_step": 2, "md_run": 3, "hvp": 4, "adjoint": 5, "md_ensemble": 6, "grad": 7}
+PATHS = ("config", "rows", "shares", "bands")
 CB_INIT_ACCEL = 1
 CB_ADJ_FINAL = 1
 
 EXPORTS = ("cb_workspace_size", "coulomb_forces", "coulomb_forces_range", "coulomb_pair_stage", "coulomb_energy",
            "coulomb_trap_grad", "cb_trap_k", "coulomb_forces_noalloc", "md_step", "md_run", "coulomb_hvp", "md_adjoint_step", "cb_poll_flags",
-           "cb_last_error", "cb_autotune", "cb_load_tuning", "cb_get_config", "cb_set_config")
+           "cb_last_error", "cb_autotune", "cb_load_tuning", "cb_get_config", "cb_get_path", "cb_set_config")
 
 
 class CoulombError(RuntimeError):
@@ -95,6 +96,7 @@ def lib() -> C.CDLL:
                 L.cb_autotune.argtypes = [i32, i64, i32, C.c_char_p]
                 L.cb_load_tuning.argtypes = [C.c_char_p]
                 L.cb_get_config.argtypes = [i32, i64, i32, C.POINTER(C.c_int32)]
+                L.cb_get_path.argtypes = [i32, i64, i32, C.POINTER(C.c_int32)]
                 L.cb_set_config.argtypes = [i32, i64, i32, i32, i32, i32, i32]
                 for name in EXPORTS:
                     if name not in ("cb_workspace_size", "cb_last_error"):
@@ -398,6 +400,14 @@ def get_config(op, n: int, prec="fp64") -> dict:
     out = (C.c_int32 * 5)()
     _check(lib().cb_get_config(_op(op), int(n), _prec(prec), out), "cb_get_config")
     return dict(algo=out[0], p=out[1], wg=out[2], splits=out[3], tuned=bool(out[4]))
+
+
+def get_path(op, n: int, prec="fp64") -> str:
+    """What the next call of op takes: "config" (the launches that get_config
+    reports), "rows", "shares" or "bands"."""
+    out = C.c_int32()
+    _check(lib().cb_get_path(_op(op), int(n), _prec(prec), C.byref(out)), "cb_get_path")
+    return PATHS[out.value]
 
 
 def set_config(op, n: int, prec="fp64", p: int = 1, wg: int = 256, splits: int = 1, algo: int = 0) -> None:

@@ -195,6 +195,10 @@ void drop_cfg(int op, int64_t n, int prec) {
     g_cfg.erase(cfg_key(op, prec, n));
 }
 
+int path_of(int op, int64_t n, int prec) {
+    return prec != CB_MIXED_F32D ? get_cfg(op, n, prec).path : (int)PATH_CFG;
+}
+
 bool valid_cfg(int op, const LaunchCfg& c) {
     if (c.algo == ALGO_SMALL)
         return (op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) && c.p == 1 && c.wg == 64 && c.splits >= 1 &&
@@ -339,6 +343,13 @@ cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]) {
     out[2] = c.wg;
     out[3] = c.splits;
     out[4] = c.tuned;
+    return ok();
+}
+
+cb_status cb_get_path(int32_t op, int64_t n, int32_t prec, int32_t* path_out) {
+    if (!path_out || n < 1 || n > kMaxIons || op < 0 || op > CB_OP_ADJOINT || prec < 0 || prec > CB_MIXED_F32D)
+        return fail(CB_EINVAL, "cb_get_path: bad argument");
+    *path_out = path_of(op, n, prec);
     return ok();
 }
 

@@ -75,11 +75,6 @@ static PairRun plan(int op, int64_t n, int prec) {
 
 static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
-// The path of an evaluation of n ions.
-static int path_of(int op, int64_t n, int prec) {
-    return prec != CB_MIXED_F32D ? get_cfg(op, n, prec).path : (int)PATH_CFG;
-}
-
 // The pair stage with the configured algorithm: forces, and the potential
 // sums too when pot.  Direct: partial sums [S][3][n] at ws+L.part (to be
 // scaled by k_C q_i) and [S][n] at ws+L.ppot.  Symmetric: the finished forces

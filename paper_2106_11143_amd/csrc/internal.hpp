@@ -161,6 +161,7 @@ constexpr int default_path(int op, int64_t n) {
 LaunchCfg default_cfg(int op, int64_t n, int prec);
 LaunchCfg direct_cfg(int op, int64_t n, int prec);
 LaunchCfg get_cfg(int op, int64_t n, int prec);
+int path_of(int op, int64_t n, int prec);  // the path of a call (CB_MIXED_F32D runs as configured)
 void put_cfg(int op, int64_t n, int prec, LaunchCfg c);
 void drop_cfg(int op, int64_t n, int prec);
 bool valid_cfg(int op, const LaunchCfg& c);
