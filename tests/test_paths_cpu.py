@@ -15,6 +15,7 @@ FORCE_OPS = ("forces", "energy", "md_step", "md_run")
 def test_untuned(api, n, path):  # noqa: F811
     for op in FORCE_OPS:
         for prec in ("fp64", "mixed", "ieee", "fp32"):
+            api.reset_config(op, n, prec)  # (an entry that another test left)
             assert api.get_path(op, n, prec) == path
     assert api.get_path("forces", n, "mixed_f32d") == "config"
     assert api.get_path("hvp", n) == api.get_path("adjoint", n) == "config"
@@ -24,6 +25,8 @@ def test_forced_entries_run_as_set(api):  # noqa: F811
     for n, cfg in ((5000, dict(p=1, wg=64, splits=8, algo=0)), (12000, dict(p=4, wg=4, splits=256, algo=2)),
                    (300000, dict(p=1, wg=64, splits=64, algo=0))):
         for op in FORCE_OPS:
+            api.reset_config(op, n, "fp64")
+            api.reset_config(op, n, "mixed")
             untuned = api.get_path(op, n)
             assert untuned != "config"
             api.set_config(op, n, "fp64", **cfg)
