@@ -313,14 +313,17 @@ const char* cb_last_error(void);
  * size, j-split count) of `op` at n ions and precision prec on the current
  * device (and the path that an untuned entry takes, see cb_get_path), keeps
  * the fastest for all later calls with n in the same power-of-two bucket, and,
- * when cache_path is non-NULL, merges it into that JSON-lines file.  For md_step / md_run at n <= 8192 the force kernel is
- * tuned for coulomb_forces, and the better of its steps and the one-launch
- * step (algorithm 3) is kept for the md calls.  Uses synthetic inputs it
- * allocates itself (this call, and cb_load_tuning, are the only ones that
- * allocate).  Synchronous. */
+ * when cache_path is non-NULL, merges it into that JSON-lines file.  A bucket's
+ * sizes whose untuned calls take another path than at n keep that path.  For
+ * md_step / md_run at n <= 8192 the force kernel is tuned for coulomb_forces,
+ * and the better of its steps and the one-launch step (algorithm 3) is kept
+ * for the md calls.  Uses synthetic inputs it allocates itself (this call, and
+ * cb_load_tuning, are the only ones that allocate).  Synchronous. */
 cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_path);
 
-/* Loads tuned configurations written by cb_autotune (missing file: CB_OK). */
+/* Loads tuned configurations written by cb_autotune (missing file: CB_OK).
+ * Lines of a file from before paths were timed set a configuration, and the
+ * calls take the path of untuned ones. */
 cb_status cb_load_tuning(const char* cache_path);
 
 /* The launch configuration of `op` at (n, prec), which its next call will use

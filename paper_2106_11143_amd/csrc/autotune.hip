@@ -161,11 +161,11 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
             }
         (void)hipStreamSynchronize(st);
     }
-    // forces and energy at sizes that take whole rows or equal shares by
-    // default: the whole call with the best configuration (pair launch and
-    // epilogue) against that path, which the entry then takes if it is faster
+    // forces and energy at sizes that take another path by default: the whole
+    // call with the best configuration (pair launch and epilogue) against that
+    // path, which the entry then takes if it is faster
     const int alt = default_path(op, n);
-    if (rc == CB_OK && best.p != 0 && (alt == PATH_ROWS || alt == PATH_SHARES)) {
+    if (rc == CB_OK && best.p != 0 && alt != PATH_CFG) {
         DevBuf out, fws;
         const int cop = energy_only ? CB_OP_ENERGY : CB_OP_FORCES;
         best.path = alt;
@@ -201,6 +201,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
     // the synthetic cloud at rest) with the best force configuration, on equal
     // shares and in one launch; the fastest is kept for the md calls.
     const bool md_op = (op == CB_OP_MD_STEP || op == CB_OP_MD_RUN);
+    if (!hv) best.base = alt;
     LaunchCfg md_best = best;
     float md_ms = 1e30f;
     if (rc == CB_OK && md_op && n <= kSmallRunMax) {
@@ -222,7 +223,8 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         const int64_t offs[2] = {0, n};
         std::vector<LaunchCfg> cands{best};
         cands[0].path = PATH_CFG;
-        cands.push_back(best);
+        cands[0].base = -1;
+        cands.push_back(cands[0]);
         cands[1].path = PATH_SHARES;
         cands.push_back({1, 64, small_parts(n), 1, ALGO_SMALL, PATH_CFG});
         for (const LaunchCfg& c : cands) {
@@ -247,6 +249,8 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
                 md_best = c;
             }
         }
+        md_best.base = alt;
+        if (md_best.algo == ALGO_SMALL) md_best.path = PATH_ROWS;
         drop_cfg(CB_OP_MD_RUN, n, prec);
         (void)hipStreamSynchronize(st);
     }
@@ -276,9 +280,9 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
         auto line = [&](int o, const LaunchCfg& c, float ms) {
             std::fprintf(f,
                          "{\"arch\": \"%s\", \"op\": %d, \"prec\": %d, \"bucket\": %d, \"n\": %lld, \"p\": %d, "
-                         "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"path\": %d, \"ms\": %.6f}\n",
+                         "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"path\": %d, \"base\": %d, \"ms\": %.6f}\n",
                          arch_name().c_str(), o, prec, n_bucket(n), (long long)n, c.p, c.wg, c.splits, c.algo, c.path,
-                         ms);
+                         c.base, ms);
         };
         line(op, best, best_ms);
         if (md_op && n <= kSmallRunMax) line(CB_OP_MD_RUN, md_best, md_ms);
@@ -296,22 +300,29 @@ cb_status cb_load_tuning(const char* cache_path) {
 
     while (std::fgets(line, sizeof line, f)) {
         char a[64] = {0};
-        int op, prec, bucket, p, wg, sp, algo = 0, path = PATH_CFG;
+        int op, prec, bucket, p, wg, sp, algo = 0, path = -1, base = -1;
         long long n;
         if (std::sscanf(line,
                         "{\"arch\": \"%63[^\"]\", \"op\": %d, \"prec\": %d, \"bucket\": %d, \"n\": %lld, \"p\": %d, "
-                        "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"path\": %d",
-                        a, &op, &prec, &bucket, &n, &p, &wg, &sp, &algo, &path) < 8)
+                        "\"wg\": %d, \"splits\": %d, \"algo\": %d, \"path\": %d, \"base\": %d",
+                        a, &op, &prec, &bucket, &n, &p, &wg, &sp, &algo, &path, &base) < 8)
             continue;
         if (arch != a || op < 0 || op > CB_OP_ADJOINT || prec < 0 || prec > CB_MIXED_F32D || n < 1 ||
             n > kMaxIons)
             continue;
         LaunchCfg c{p, wg, sp, 1, algo, PATH_CFG};
         if (!valid_cfg(op, c)) continue;
-        // (a file without the field, or a path that op does not take at n: the configured launches)
-        if (sym_op(op) && (path == PATH_ROWS || path == PATH_SHARES) &&
-            (path == default_path(op, n) || (path == PATH_SHARES && n <= kSmallRunMax)))
+        if (sym_op(op)) {
+            // The line's path counts where it was timed against what an untuned
+            // call takes at n.  Lines without the fields were not; those without
+            // the second alone were, except against bands.
+            c.base = default_path(op, n);
+            const bool timed = base >= 0 ? base == c.base : path >= 0 && c.base != PATH_BANDS;
+            if (timed && c.algo == ALGO_SMALL) path = PATH_ROWS;
+            else if (!timed || (path != PATH_CFG && path != c.base && !(path == PATH_SHARES && n <= kSmallRunMax)))
+                path = c.base;
             c.path = path;
+        }
         if (op == CB_OP_FORCES || op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) {
             // as cb_autotune: a forces line also sets the md calls above
             // kSmallRunMax ions; an md line sets the md calls (and forces,
@@ -320,7 +331,6 @@ cb_status cb_load_tuning(const char* cache_path) {
             if (c.algo == ALGO_SMALL && n > kSmallRunMax) continue;
             if (c.algo != ALGO_SMALL) put_cfg(CB_OP_FORCES, n, prec, c);
             if (md_line || n > kSmallRunMax) {
-                if (c.path == PATH_ROWS) c.path = PATH_CFG;  // (the forces' choice; the md calls' is ALGO_SMALL)
                 put_cfg(CB_OP_MD_STEP, n, prec, c);
                 put_cfg(CB_OP_MD_RUN, n, prec, c);
             }

@@ -181,8 +181,14 @@ LaunchCfg direct_cfg(int op, int64_t n, int prec) {
 LaunchCfg get_cfg(int op, int64_t n, int prec) {
     std::lock_guard<std::mutex> lk(g_cfg_mu);
     auto it = g_cfg.find(cfg_key(op, prec, n));
-    if (it != g_cfg.end()) return it->second;
-    return default_cfg(op, n, prec);
+    if (it == g_cfg.end()) return default_cfg(op, n, prec);
+    LaunchCfg c = it->second;
+    // A bucket spans sizes with different default paths (32768 to 65536 ions:
+    // tiles, or equal shares, 33500 ions 548 / 426 us): what was timed at one
+    // size decides for those alone that have the same.
+    const int path = default_path(op, n);
+    if (c.base >= 0 && c.base != path) c.path = path;
+    return c;
 }
 
 void put_cfg(int op, int64_t n, int prec, LaunchCfg c) {

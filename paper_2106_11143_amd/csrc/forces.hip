@@ -175,7 +175,7 @@ static cb_status md_single(int64_t n, const cb_state* s, const double* q, const 
                            double* energies, int64_t every, void* ws, int op, hipStream_t st) {
     const WsLayout L = ws_layout(op, n, 1, 1, prec);
     const LaunchCfg sc = get_cfg(op, n, prec);
-    if (sc.path == PATH_ROWS || (sc.algo == ALGO_SMALL && n <= kSmallRunMax))
+    if (sc.path == PATH_ROWS || (sc.path == PATH_CFG && sc.algo == ALGO_SMALL && n <= kSmallRunMax))
         return md_run_rows(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, flags, every > 0 ? energies : nullptr, every,
                            static_cast<char*>(ws) + L.part, L.ppot - L.part, kRunSpins, st);
     if (sc.path == PATH_SHARES)

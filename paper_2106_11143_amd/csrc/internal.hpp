@@ -102,6 +102,10 @@ struct LaunchCfg {
     int tuned;   // 1 if set by tuning or cb_set_config
     int algo;    // ALGO_DIRECT, ALGO_SYM or ALGO_SYM_LDS
     int path;    // PATH_CFG, or the path taken in its place (untuned entries, or a tuned one that was faster so)
+    // A tuned entry's: the default path it was timed against.  At the sizes of
+    // its bucket that have another, that one is taken (get_cfg).  -1: path holds
+    // at every size.
+    int base = -1;
 };
 
 struct WsLayout {

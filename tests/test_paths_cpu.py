@@ -46,3 +46,68 @@ def test_bad_arguments(api):  # noqa: F811
     for op, n, prec in ((-1, 100, 0), (6, 100, 0), (7, 100, 0), (0, 0, 0), (0, (1 << 28) + 1, 0), (0, 100, 5), (0, 100, -1)):
         assert L.cb_get_path(op, n, prec, C.byref(out)) == api.CB_EINVAL
     assert out.value == -1
+
+
+OP = {"forces": 0, "energy": 1, "md_step": 2, "md_run": 3, "hvp": 4}
+PATH = {"config": 0, "rows": 1, "shares": 2, "bands": 3}
+
+
+def _load(api, tmp_path, *lines):
+    """A tuning file of these (op, n, algo, path, base) lines: path and base
+    None where the file was written without them."""
+    f = tmp_path / "tune.jsonl"
+    out = []
+    for op, n, algo, path, base in lines:
+        shape = {0: (1, 64, 8), 2: (4, 4, 256), 3: (1, 64, 4), 4: (8, 4, 512)}[algo]
+        t = '"op": %d, "prec": 0, "bucket": 0, "n": %d, "p": %d, "wg": %d, "splits": %d, "algo": %d' % (
+            OP[op], n, *shape, algo)
+        t += "" if path is None else ', "path": %d' % PATH[path]
+        t += "" if base is None else ', "base": %d' % PATH[base]
+        # (the architecture's name where there is no GPU, and where there is)
+        out += ['{"arch": "%s", %s, "ms": 1.0}' % (arch, t) for arch in ("unknown", "gfx950")]
+    f.write_text("\n".join(out) + "\n")
+    api.load_tuning(str(f))
+
+
+@pytest.fixture
+def clean(api):  # noqa: F811
+    def drop():
+        for op in FORCE_OPS:
+            for b in range(12, 20):
+                api.reset_config(op, 1 << b)
+    drop()
+    yield
+    drop()
+
+
+# (line, {n: path}): the line's path at the sizes of its bucket that have the
+# default it was timed against, their default at the others; a line that does
+# not say what it was timed against takes the default everywhere, except that
+# rows and shares were always timed when a path was written at all.
+@pytest.mark.parametrize("line,want", [
+    (("forces", 300001, 0, None, None), {262145: "bands", 300001: "bands"}),
+    (("forces", 300001, 0, "config", None), {262145: "bands", 300001: "bands"}),
+    (("forces", 300001, 0, "config", "bands"), {262145: "config", 300001: "config"}),
+    (("energy", 300001, 0, "bands", "bands"), {262145: "bands"}),
+    (("md_run", 300001, 0, "bands", "bands"), {262145: "bands"}),
+    (("forces", 65536, 2, "config", "config"), {33500: "shares", 39900: "config", 57344: "shares", 60000: "config"}),
+    (("md_step", 39900, 2, "config", "config"), {33500: "shares", 39900: "config", 57344: "shares", 65536: "config"}),
+    (("energy", 12000, 2, "config", None), {9000: "config", 12000: "config"}),
+    (("energy", 12000, 2, "shares", "shares"), {9000: "shares", 16384: "shares"}),
+    (("energy", 12000, 2, None, None), {9000: "shares", 12000: "shares"}),
+    (("forces", 7000, 0, "config", "shares"), {5000: "rows", 7000: "config"}),
+    (("forces", 5000, 0, "config", "rows"), {5000: "config", 7000: "shares"}),
+    (("forces", 5000, 0, "shares", "rows"), {5000: "shares", 7000: "shares"}),
+    (("forces", 5000, 0, "bands", "rows"), {5000: "rows"}),
+    (("md_run", 5000, 3, "rows", "rows"), {5000: "rows", 7000: "shares"}),
+    (("md_run", 7000, 3, "rows", "shares"), {5000: "rows", 7000: "rows"}),
+    (("md_run", 7000, 3, "config", None), {5000: "rows", 7000: "rows"})])
+def test_tuned_at_one_size(api, clean, tmp_path, line, want):  # noqa: F811
+    _load(api, tmp_path, line)
+    op = line[0]
+    for n, path in want.items():
+        assert api.get_config(op, n)["tuned"]
+        assert api.get_path(op, n) == path, n
+    if op.startswith("md") or line[1] > 8192 and op == "forces":
+        for n, path in want.items():
+            assert api.get_path("md_step", n) == api.get_path("md_run", n) == path
