@@ -284,7 +284,8 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
                          arch_name().c_str(), o, prec, n_bucket(n), (long long)n, c.p, c.wg, c.splits, c.algo, c.path,
                          c.base, ms);
         };
-        line(op, best, best_ms);
+        // (the forces' line first: loading it may set the md calls too)
+        line(md_op && n <= kSmallRunMax ? (int)CB_OP_FORCES : op, best, best_ms);
         if (md_op && n <= kSmallRunMax) line(CB_OP_MD_RUN, md_best, md_ms);
         std::fclose(f);
     }
@@ -297,6 +298,11 @@ cb_status cb_load_tuning(const char* cache_path) {
     if (!f) return ok();
     const std::string arch = arch_name();
     char line[512];
+    // Files without "base" hold what tuning an md call at n <= kSmallRunMax set
+    // as two lines of md ops, the forces' and the md calls': the n and prec of
+    // such a first line, while the second may follow.
+    long long pair_n = 0;
+    int pair_prec = 0;
 
     while (std::fgets(line, sizeof line, f)) {
         char a[64] = {0};
@@ -324,12 +330,17 @@ cb_status cb_load_tuning(const char* cache_path) {
             c.path = path;
         }
         if (op == CB_OP_FORCES || op == CB_OP_MD_STEP || op == CB_OP_MD_RUN) {
-            // as cb_autotune: a forces line also sets the md calls above
-            // kSmallRunMax ions; an md line sets the md calls (and forces,
-            // unless it is the one-launch step)
+            // as cb_autotune: above kSmallRunMax ions any of these lines sets
+            // the forces and the md calls, up to there its own
             const bool md_line = op != CB_OP_FORCES;
             if (c.algo == ALGO_SMALL && n > kSmallRunMax) continue;
-            if (c.algo != ALGO_SMALL) put_cfg(CB_OP_FORCES, n, prec, c);
+            bool forces = !md_line || n > kSmallRunMax;
+            if (md_line && n <= kSmallRunMax && base < 0) {
+                forces = (n != pair_n || prec != pair_prec) && c.algo != ALGO_SMALL;
+                pair_n = forces ? n : 0;
+                pair_prec = prec;
+            }
+            if (forces) put_cfg(CB_OP_FORCES, n, prec, c);
             if (md_line || n > kSmallRunMax) {
                 put_cfg(CB_OP_MD_STEP, n, prec, c);
                 put_cfg(CB_OP_MD_RUN, n, prec, c);
@@ -340,7 +351,6 @@ cb_status cb_load_tuning(const char* cache_path) {
         } else {
             put_cfg(op, n, prec, c);
         }
-
     }
     std::fclose(f);
     return ok();

@@ -57,3 +57,20 @@ def test_tuning_times_the_bands(api):  # noqa: F811
         assert api.get_config("energy", n)["tuned"] and api.get_path("energy", n) == "bands"
     finally:
         _drop(api, n)
+
+
+@pytest.mark.parametrize("op,n", [("md_run", 300), ("md_step", 5000), ("forces", 7000), ("md_run", 8192), ("md_run", 9000)])
+def test_file_restores_what_tuning_set(api, tmp_path, op, n):  # noqa: F811
+    f = str(tmp_path / "tune.jsonl")
+    entries = lambda: {(o, k): (api.get_config(o, k), api.get_path(o, k)) for o in OPS for k in (n, 3 * n // 4)}  # noqa: E731
+    untuned = entries()
+    try:
+        api.autotune(op, n, "fp64", f)
+        tuned = entries()
+        assert tuned["forces", n][0]["tuned"]
+        _drop(api, n)
+        assert entries() == untuned
+        api.load_tuning(f)
+        assert entries() == tuned
+    finally:
+        _drop(api, n)
