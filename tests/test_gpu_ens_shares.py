@@ -65,3 +65,22 @@ def test_tiles_of_a_large_ensemble(api, prec):  # noqa: F811
     for jl in (256, 512):
         _agree(_run(api, sizes, prec, 2, 2, True, dict(p=4, wg=4, splits=jl, algo=2)), want, sizes)
     assert api.poll_flags() == 0
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_two_wave_finish(api, prec):  # noqa: F811
+    """From 4096 chunks of 64 ions on, two waves finish a chunk instead of
+    eight."""
+    g = np.random.Generator(np.random.PCG64(17))
+    sizes = [n for n in EDGES if n <= 1024] + [int(n) for n in g.integers(64, 1025, 560)]
+    units = pairs = 0
+    for n in sizes:  # the rule that picks the path: rows, shares and tiles by estimated time
+        nI, C = -(-n // 256), -(-n // 16)
+        units += nI * C - 16 * (nI * (nI - 1) // 2)
+        pairs += n * n
+    assert sum(-(-n // 64) for n in sizes) >= 4096
+    assert 15e-6 + 3.3e-9 * units < min(5e-6 + pairs / 1.25e12, 40e-6 + 3e-9 * units)
+    for nsteps, every, init in ((0, 1, True), (4, 2, True), (3, 0, False)):
+        _agree(_run(api, sizes, prec, nsteps, every, init, None),
+               _run(api, sizes, prec, nsteps, every, init, PERSISTENT), sizes)
+    assert api.poll_flags() == 0
