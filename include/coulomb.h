@@ -326,6 +326,19 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
  * calls take the path of untuned ones. */
 cb_status cb_load_tuning(const char* cache_path);
 
+/* For tests: the steps of md_run (one run, accelerations as given) by the
+ * launch whose workgroups stay resident, with a bound of `spins` polls on each
+ * of their waits.  0: the launch gives up at once; -1: it is not admitted
+ * beside other runs, which gives up too; the closing launch then takes the
+ * steps.  The first two 32-bit words of ws say afterwards whether the last of
+ * its launches gave up (1 or 0), and the waves it was admitted with (0: not).
+ * Records (energies as md_run's) are those of the steps, from the second row
+ * on.  Arguments as md_run's; CB_EINVAL for a run that does not take the
+ * resident launch (n, nsteps or ws_bytes). */
+cb_status cb_rows_run_spins(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap,
+                            double t0, double dt, int64_t nsteps, double eps2, int32_t prec, double* energies,
+                            int64_t every, int32_t spins, void* ws, size_t ws_bytes, void* stream);
+
 /* The launch configuration of `op` at (n, prec), which its next call will use
  * unless cb_get_path says otherwise:
  * out[0] = algorithm (0: every ordered pair evaluated, j-split partial sums;

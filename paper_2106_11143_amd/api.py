@@ -30,7 +30,8 @@ CB_ADJ_FINAL = 1
 
 EXPORTS = ("cb_workspace_size", "coulomb_forces", "coulomb_forces_range", "coulomb_pair_stage", "coulomb_energy",
            "coulomb_trap_grad", "cb_trap_k", "coulomb_forces_noalloc", "md_step", "md_run", "coulomb_hvp", "md_adjoint_step", "cb_poll_flags",
-           "cb_last_error", "cb_autotune", "cb_load_tuning", "cb_get_config", "cb_get_path", "cb_set_config")
+           "cb_last_error", "cb_autotune", "cb_load_tuning", "cb_get_config", "cb_get_path", "cb_set_config",
+           "cb_rows_run_spins")
 
 
 class CoulombError(RuntimeError):
@@ -98,6 +99,8 @@ def lib() -> C.CDLL:
                 L.cb_get_config.argtypes = [i32, i64, i32, C.POINTER(C.c_int32)]
                 L.cb_get_path.argtypes = [i32, i64, i32, C.POINTER(C.c_int32)]
                 L.cb_set_config.argtypes = [i32, i64, i32, i32, i32, i32, i32]
+                L.cb_rows_run_spins.argtypes = [i64, C.POINTER(State), _P, _P, C.POINTER(Trap), d, d, i64, d, i32, _P,
+                                                i64, i32, _P, sz, _P]
                 for name in EXPORTS:
                     if name not in ("cb_workspace_size", "cb_last_error"):
                         getattr(L, name).restype = C.c_int

@@ -641,4 +641,28 @@ cb_status md_run(int32_t nrun, const int64_t* offsets, const cb_state* s, const 
     return md_single(n, s, q, m, &traps[0], t0, dt, nsteps, eps2, prec, flags, energies, every, ws, CB_OP_MD_RUN, st);
 }
 
+cb_status cb_rows_run_spins(int64_t n, const cb_state* s, const double* q, const double* m, const cb_trap* trap,
+                            double t0, double dt, int64_t nsteps, double eps2, int32_t prec, double* energies,
+                            int64_t every, int32_t spins, void* ws, size_t ws_bytes, void* stream) {
+    cb_status rc = check_common("cb_rows_run_spins", n, prec, eps2, ws, ws_bytes, 0);
+    if (rc) return rc;
+    if (prec == CB_MIXED_F32D) return fail(CB_EUNSUPPORTED, "cb_rows_run_spins: CB_MIXED_F32D is for the forces only");
+    if (!(dt > 0.0) || !std::isfinite(dt) || !std::isfinite(t0))
+        return fail(CB_EINVAL, "cb_rows_run_spins: need finite t0 and dt > 0");
+    if (energies && every < 1) return fail(CB_EINVAL, "cb_rows_run_spins: every must be >= 1 when energies are requested");
+    if (!trap_ok(trap, "cb_rows_run_spins", &rc)) return rc;
+    if (!state_ok(s, n, q, m, "cb_rows_run_spins", &rc)) return rc;
+    if (!rows_run_fits(n, nsteps, ws_bytes))
+        return fail(CB_EINVAL, "cb_rows_run_spins: not a run that takes the resident launch");
+    if (energies) {
+        double* arr[9] = {s->x, s->y, s->z, s->vx, s->vy, s->vz, s->ax, s->ay, s->az};
+        for (auto a : arr)
+            if (overlaps2(a, n, energies, 4 * (nsteps / every + 1)))
+                return fail(CB_EINVAL, "cb_rows_run_spins: energies overlaps the state");
+    }
+    rc = rows_run(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, energies, every, spins, ws,
+                  static_cast<hipStream_t>(stream));
+    return rc ? rc : ok();
+}
+
 }  // extern "C"

@@ -119,15 +119,3 @@ cb_status rows_run(int64_t n, const cb_state* s, const double* q, const double* 
 }
 
 }  // namespace cb
-
-// rows_run with the bound on its waits given (0: it gives up at once, -1: it is
-// not admitted), for the test of those paths; the accelerations are the state's.
-extern "C" cb_status cb_rows_run_spins(int64_t n, const cb_state* s, const double* q, const double* m,
-                                       const cb_trap* trap, double t0, double dt, int64_t nsteps, double eps2,
-                                       int32_t prec, double* energies, int64_t every, int32_t spins, void* ws,
-                                       size_t ws_bytes, void* stream) {
-    if (!cb::rows_run_fits(n, nsteps, ws_bytes) || prec < CB_FP64 || prec > CB_FP32_RSQ || (energies && every < 1))
-        return cb::fail(CB_EINVAL, "cb_rows_run_spins: not a run that takes this path");
-    return cb::rows_run(n, s, q, m, trap, t0, dt, nsteps, eps2, prec, energies, every, spins, ws,
-                        static_cast<hipStream_t>(stream));
-}
