@@ -485,9 +485,13 @@ cb_status md_run_batched(int32_t nrun, const int64_t* offsets, const cb_state* s
         if (5e-6 + pairs / 1.25e12 < std::min(shares, tiles))
             return md_run_rows_ensemble(nrun, offsets, s, q, m, traps, t0, dt, nsteps, eps2, prec, flags, energies,
                                         every, static_cast<char*>(ws) + LE.aux, ws_bytes - LE.aux, st);
-        if (shares < tiles && share_ens_fits(nrun, offsets, ws_bytes - LE.aux))
-            return md_run_shares_ensemble(nrun, offsets, s, q, m, traps, t0, dt, nsteps, eps2, prec, flags, energies,
-                                          every, static_cast<char*>(ws) + LE.aux, ws_bytes - LE.aux, st);
+        if (shares < tiles) {
+            bool taken = false;
+            const cb_status rc =
+                md_run_shares_ensemble(nrun, offsets, s, q, m, traps, t0, dt, nsteps, eps2, prec, flags, energies, every,
+                                       static_cast<char*>(ws) + LE.aux, ws_bytes - LE.aux, &taken, st);
+            if (taken) return rc;
+        }
         ec.algo = ALGO_SYM_LDS;
         ec.p = 4;
         ec.splits = pairs >= 1073741824.0 ? 512 : 256;

@@ -286,15 +286,14 @@ cb_status rows_run(int64_t n, const cb_state* s, const double* q, const double* 
 cb_status rows_forces(int prec, int64_t n, const double* x, const double* y, const double* z, const double* q,
                       const double* m, const TrapK& k, double eps2, unsigned mode, double* fx, double* fy, double* fz,
                       double* u_out, void* ws, hipStream_t st);
-// md_run of an ensemble on equal shares of its runs' pairs (shares.hip), the
-// units of 256 ions by 16 that they hold, and whether its tables and partials
-// fit ws_bytes.
+// md_run of an ensemble on equal shares of its runs' pairs (shares.hip), and
+// the units of 256 ions by 16 that they hold.  *taken: whether its tables and
+// partials fit ws_bytes (else nothing is done).
 double share_ens_units(int32_t nrun, const int64_t* offsets);
-bool share_ens_fits(int32_t nrun, const int64_t* offsets, size_t ws_bytes);
 cb_status md_run_shares_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* s, const double* q,
                                  const double* m, const cb_trap* traps, double t0, double dt, int64_t nsteps,
                                  double eps2, int32_t prec, uint32_t flags, double* energies, int64_t every, void* ws,
-                                 size_t ws_bytes, hipStream_t st);
+                                 size_t ws_bytes, bool* taken, hipStream_t st);
 // md_run_rows for an ensemble of runs, one launch per step over all of them.
 cb_status md_run_rows_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* s, const double* q,
                                const double* m, const cb_trap* traps, double t0, double dt, int64_t nsteps,

@@ -438,11 +438,6 @@ double share_ens_units(int32_t nrun, const int64_t* offsets) {
     return units;
 }
 
-bool share_ens_fits(int32_t nrun, const int64_t* offsets, size_t ws_bytes) {
-    ShareEns E;
-    return share_ens(nrun, offsets, E) && E.bytes <= ws_bytes;
-}
-
 template <int PREC>
 static void go_share_ens(bool pot, const ShareEns& E, const int4* runs, const int2* first, const cb_state* s,
                          const double* q, double eps2, double* Pi, double* R, double* Et, hipStream_t st) {
@@ -463,10 +458,10 @@ static void go_finish_ens(const ShareStep& S, unsigned g, const int4* runs, cons
 cb_status md_run_shares_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* s, const double* q,
                                  const double* m, const cb_trap* traps, double t0, double dt, int64_t nsteps,
                                  double eps2, int32_t prec, uint32_t flags, double* energies, int64_t every, void* ws,
-                                 size_t ws_bytes, hipStream_t st) {
+                                 size_t ws_bytes, bool* taken, hipStream_t st) {
     ShareEns E;
-    if (!share_ens(nrun, offsets, E) || ws_bytes < E.bytes)
-        return fail(CB_ENOWS, "md_run: the ensemble path needs %zu workspace bytes, has %zu", E.bytes, ws_bytes);
+    *taken = share_ens(nrun, offsets, E) && E.bytes <= ws_bytes;
+    if (!*taken) return CB_OK;
     const size_t slots = (size_t)E.all.N + E.rows, nch = E.chunks.size();
     char* base = static_cast<char*>(ws);
     auto carve = [&](size_t bytes) {
