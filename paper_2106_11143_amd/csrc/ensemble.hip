@@ -543,8 +543,6 @@ static EnsTables ens_tables(int nrun, const int64_t* offsets, int IB, int JL) {
 // step; 1 wave measured the same as 2, 8 waves 1.41).
 constexpr unsigned kFinishTwoWaves = 4096;
 
-static int whole_ib(int64_t nmax) { return (int)((nmax + 63) / 64 * 64); }
-
 // Upper bound of ens_tables(...).bytes over every ensemble of ntot ions in
 // nrun runs of at most kMaxBatchIons, for every allowed (P, JL).  A run of n
 // ions has at most n^2 / (2 IB JL) + n / IB off-diagonal tiles and, over
@@ -587,12 +585,9 @@ cb_status md_run_ensemble(int32_t nrun, const int64_t* offsets, const cb_state* 
                           const double* m, const cb_trap* traps, double t0, double dt, int64_t nsteps, double eps2,
                           int32_t prec, uint32_t flags, double* energies, int64_t every, int P, int JL, void* ws,
                           size_t ws_bytes, hipStream_t st) {
-    if (P != 0 && !ens_cfg_ok(P, JL))
+    if (!ens_cfg_ok(P, JL))
         return fail(CB_EINVAL, "md_run: ensemble configuration p=%d JL=%d not supported", P, JL);
-    int64_t nmax = 0;
-    for (int r = 0; r < nrun; ++r) nmax = std::max<int64_t>(nmax, offsets[r + 1] - offsets[r]);
-    const int IB = P == 0 ? whole_ib(nmax) : 64 * P;
-    if (P == 0) JL = 256;
+    const int IB = 64 * P;
     const EnsTables E = ens_tables(nrun, offsets, IB, JL);
     if (ws_bytes < E.bytes)
         return fail(CB_ENOWS, "md_run: the ensemble path needs %zu workspace bytes, has %zu", E.bytes, ws_bytes);

@@ -118,11 +118,6 @@ __device__ __forceinline__ void load_group(JGroupT<WQ>& g, int jg, int last, con
     }
 }
 
-// The value of lane 0 (uniform).
-__device__ __forceinline__ double uniform_lane0(double v) {
-    return pack_d(__builtin_amdgcn_readfirstlane(lo_u(v)), __builtin_amdgcn_readfirstlane(hi_u(v)));
-}
-
 // Whether every ion of an i-block (the lane's P charges) and every ion of
 // the j range [j0, j1), j1 > j0, carry one charge each, and those charges
 // (qI, qJ): the tile is then one of the paper's single-species N-body
@@ -136,7 +131,7 @@ __device__ __forceinline__ bool tile_charges(const double (&qi)[P], const double
     // (the first 64 j's charges are requested ahead of the others' wait)
     const int jl = j0 + (int)__lane_id();
     const double v = q[min(jl, j1 - 1)];
-    const double q0 = uniform_lane0(qi[0]), q1 = q[j0];
+    const double q0 = uniform(qi[0]), q1 = q[j0];
     bool one = __builtin_isfinite(q0) && __builtin_isfinite(q1);
 #pragma unroll
     for (int p = 0; p < P; ++p) one &= qi[p] == q0;

@@ -84,10 +84,6 @@ __device__ __forceinline__ void mark(double* p) {
 }
 __device__ __forceinline__ bool unset(double v) { return hi_u(v) == static_cast<unsigned>(kUnset >> 32); }
 
-__device__ __forceinline__ double uniform(double v) {
-    return pack_d(__builtin_amdgcn_readfirstlane(lo_u(v)), __builtin_amdgcn_readfirstlane(hi_u(v)));
-}
-
 constexpr int kRunI = 4;  // ions per workgroup
 
 template <int W, bool REC>

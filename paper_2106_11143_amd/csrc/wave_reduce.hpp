@@ -16,6 +16,11 @@ __device__ __forceinline__ unsigned hi_u(double d) {
     return static_cast<unsigned>(__builtin_bit_cast(unsigned long long, d) >> 32);
 }
 
+// The first lane's value (uniform).
+__device__ __forceinline__ double uniform(double v) {
+    return pack_d(__builtin_amdgcn_readfirstlane(lo_u(v)), __builtin_amdgcn_readfirstlane(hi_u(v)));
+}
+
 // lanes 0-31 return a(l) + a(l+32); lanes 32-63 return b(l-32) + b(l).
 __device__ __forceinline__ double swap32_add(double a, double b) {
     const auto lo = __builtin_amdgcn_permlane32_swap(lo_u(a), lo_u(b), false, false);
