@@ -363,8 +363,8 @@ cb_status cb_rows_run_spins(int64_t n, const cb_state* s, const double* q, const
 cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);
 
 /* The path of the next call of `op` (forces, energy, md_step, md_run of one
- * run, HVP, adjoint; coulomb_trap_grad takes that of the forces, or with the
- * energy that of the energy) at (n, prec), to *path_out:
+ * run, HVP, adjoint; CB_OP_GRAD: coulomb_trap_grad with the energy, which
+ * without it takes that of the forces) at (n, prec), to *path_out:
  * 0 = the launches that cb_get_config reports;
  * 1 = whole rows of the pair sum per workgroup in one launch (as algorithm 3);
  * 2 = the Newton's-third-law pairs in equal shares per workgroup;
@@ -372,7 +372,7 @@ cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);
  *     fit the workspace.
  * An untuned entry of the forces, energy, md_step or md_run takes 1 up to 6144
  * ions, 2 up to 57344 (except where the reported tiles fill the chip evenly), 3
- * beyond 2^18.  A tuned entry takes them where they were faster, an entry set
+ * beyond 2^18; the energy alone 0 from 2401 to 6144 (CB_FP32_RSQ to 8192).  A tuned entry takes them where they were faster, an entry set
  * by cb_set_config runs as set, and CB_MIXED_F32D always runs as reported.
  * CB_EINVAL for a NULL path_out, n outside [1, 2^28], an op that is none of
  * these (an ensemble's path follows the sizes of its runs, see md_run) or a

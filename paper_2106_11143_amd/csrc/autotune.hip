@@ -164,7 +164,7 @@ cb_status cb_autotune(int32_t op, int64_t n, int32_t prec, const char* cache_pat
     // forces and energy at sizes that take another path by default: the whole
     // call with the best configuration (pair launch and epilogue) against that
     // path, which the entry then takes if it is faster
-    const int alt = default_path(op, n);
+    const int alt = default_path(op, n, prec);
     if (rc == CB_OK && best.p != 0 && alt != PATH_CFG) {
         DevBuf out, fws;
         const int cop = energy_only ? CB_OP_ENERGY : CB_OP_FORCES;
@@ -322,7 +322,7 @@ cb_status cb_load_tuning(const char* cache_path) {
             // The line's path counts where it was timed against what an untuned
             // call takes at n.  Lines without the fields were not; those without
             // the second alone were, except against bands.
-            c.base = default_path(op, n);
+            c.base = default_path(op, n, prec);
             const bool timed = base >= 0 ? base == c.base : path >= 0 && c.base != PATH_BANDS;
             if (timed && c.algo == ALGO_SMALL) path = PATH_ROWS;
             else if (!timed || (path != PATH_CFG && path != c.base && !(path == PATH_SHARES && n <= kSmallRunMax)))

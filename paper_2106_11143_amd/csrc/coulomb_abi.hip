@@ -86,8 +86,7 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
     LaunchCfg c;
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
-    c.path = default_path(op, n);
-    (void)prec;
+    c.path = default_path(op, n, prec);
     if (op == CB_OP_MD_ENSEMBLE) {
         // Stepped ensemble path (ensemble.hip).  While this entry is untuned,
         // md_run_batched picks the path and (p, JL) from the run sizes.
@@ -147,8 +146,7 @@ LaunchCfg direct_cfg(int op, int64_t n, int prec) {
     LaunchCfg c;
     c.tuned = 0;
     c.algo = ALGO_DIRECT;
-    c.path = default_path(op, n);
-    (void)prec;
+    c.path = default_path(op, n, prec);
     c.wg = 64;
     c.p = 1;
     const int64_t waves = (n + 64 * c.p - 1) / (64 * c.p);
@@ -186,7 +184,7 @@ LaunchCfg get_cfg(int op, int64_t n, int prec) {
     // A bucket spans sizes with different default paths (32768 to 65536 ions:
     // tiles, or equal shares, 33500 ions 548 / 426 us): what was timed at one
     // size decides for those alone that have the same.
-    const int path = default_path(op, n);
+    const int path = default_path(op, n, prec);
     if (c.base >= 0 && c.base != path) c.path = path;
     return c;
 }
@@ -202,7 +200,12 @@ void drop_cfg(int op, int64_t n, int prec) {
 }
 
 int path_of(int op, int64_t n, int prec) {
-    return prec != CB_MIXED_F32D ? get_cfg(op, n, prec).path : (int)PATH_CFG;
+    if (prec == CB_MIXED_F32D) return PATH_CFG;
+    if (op != CB_OP_GRAD) return get_cfg(op, n, prec).path;
+    // (an entry that was forced, or timed against another path, is one for the
+    // gradient with the energy too)
+    const LaunchCfg c = get_cfg(CB_OP_ENERGY, n, prec);
+    return c.tuned && c.base != PATH_CFG ? c.path : default_path(CB_OP_FORCES, n, prec);
 }
 
 bool valid_cfg(int op, const LaunchCfg& c) {
@@ -253,6 +256,7 @@ WsLayout ws_layout(int op, int64_t n, int32_t nrun, int32_t nvec, int32_t prec) 
     // (coulomb_trap_grad's force stage follows the forces' configuration, or
     // the energy's when it also returns the energy: the larger of the two)
     const int cfg_op = op == CB_OP_GRAD ? CB_OP_ENERGY : op;
+    const int path = path_of(op, n, prec);
     // the tiles' pair energies too: energies, energy records, the gradient's energy
     const bool pot = (op == CB_OP_ENERGY || op == CB_OP_MD_RUN || op == CB_OP_GRAD);
     if (op == CB_OP_GRAD) op = CB_OP_MD_STEP;  // the same buffers: force stage, potential partials, energy blocks
@@ -263,10 +267,10 @@ WsLayout ws_layout(int op, int64_t n, int32_t nrun, int32_t nvec, int32_t prec) 
         size_t part = sizeof(double) * (size_t)kMaxSplits * 3 * (hv ? nv : 1) * N;
         const bool force_op = sym_op(op);
         LaunchCfg c = get_cfg(cfg_op, n, prec);
-        bool shares = force_op && c.path == PATH_SHARES;
+        bool shares = force_op && path == PATH_SHARES;
         if (cfg_op == CB_OP_ENERGY) {  // coulomb_trap_grad: the forces' stage too
             const LaunchCfg f = get_cfg(CB_OP_FORCES, n, prec);
-            shares = shares || f.path == PATH_SHARES;
+            shares = shares || path_of(CB_OP_FORCES, n, prec) == PATH_SHARES;
             if (is_sym(f.algo) && sym_cfg_ok(f.p, f.wg, f.splits) &&
                 (!is_sym(c.algo) || sym_ws_bytes(n, f.p, f.splits, true, sym_rows(f.algo)) >
                                         sym_ws_bytes(n, c.p, c.splits, true, sym_rows(c.algo))))
@@ -353,7 +357,8 @@ cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]) {
 }
 
 cb_status cb_get_path(int32_t op, int64_t n, int32_t prec, int32_t* path_out) {
-    if (!path_out || n < 1 || n > kMaxIons || op < 0 || op > CB_OP_ADJOINT || prec < 0 || prec > CB_MIXED_F32D)
+    if (!path_out || n < 1 || n > kMaxIons || op < 0 || op == CB_OP_MD_ENSEMBLE || op > CB_OP_GRAD || prec < 0 ||
+        prec > CB_MIXED_F32D)
         return fail(CB_EINVAL, "cb_get_path: bad argument");
     *path_out = path_of(op, n, prec);
     return ok();

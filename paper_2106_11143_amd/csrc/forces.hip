@@ -548,7 +548,7 @@ cb_status coulomb_trap_grad(int64_t n, const double* x, const double* y, const d
     for (auto o : outs)
         if (u_out && overlaps2(o, n, u_out, 1)) return fail(CB_EINVAL, "coulomb_trap_grad: u_out aliases an output");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (evaluated(u_out ? CB_OP_ENERGY : CB_OP_FORCES, prec, n, x, y, z, q, m,
+    if (evaluated(u_out ? CB_OP_GRAD : CB_OP_FORCES, prec, n, x, y, z, q, m,
                   m ? trap_k(*trap, t) : TrapK{0.0, 0.0, 0.0}, eps2, want_g ? EPI_GRAD : 0u, gx, gy, gz, u_out,
                   at(ws, L.part), st, &rc))
         return rc;

@@ -158,14 +158,24 @@ constexpr bool tiles_fit(int64_t n) {
 // 8192 43.4 / 48.5, 12001 71.7 / 104, 16000 114 / 181, 20001 168 / 210, 24577 240 /
 // 243, 27999 307 / 309, 30000 348 / 371, 33500 426 / 548, 40000 588 /
 // 714, 49152 865 / 906, 57344 1161 / 1239, 65536 1490 / 1485).
-constexpr int default_path(int op, int64_t n) {
+//
+// The energy alone takes the potential-only all-pairs launches where rows
+// and shares, which sum the forces too, are slower (us per coulomb_energy, rows
+// or shares / those: FP64 2000 ions 10.0 / 12.9, 2500 15.3 / 15.2, 3000 16.9 /
+// 14.9, 4096 20.9 / 18.6, 5000 33.0 / 24.7, 6144 39.2 / 31.1, 6145 31.5 / 34.5,
+// 8192 42.2 / 44.5; the FP32 estimate 6144 31.4 / 24.7, 8192 36.2 / 33.4, 9000
+// 41.2 / 43.4).
+constexpr int default_path(int op, int64_t n, int prec) {
+    if (op == CB_OP_ENERGY && n > 2400 && n <= (prec == CB_FP32_RSQ ? 8192 : kRowsMaxN)) return PATH_CFG;
     if (op != CB_OP_FORCES && op != CB_OP_ENERGY && op != CB_OP_MD_STEP && op != CB_OP_MD_RUN) return PATH_CFG;
     return n <= kRowsMaxN ? PATH_ROWS : n <= kSharesMaxN && !tiles_fit(n) ? PATH_SHARES : n > kSymMaxN ? PATH_BANDS : PATH_CFG;
 }
 LaunchCfg default_cfg(int op, int64_t n, int prec);
 LaunchCfg direct_cfg(int op, int64_t n, int prec);
 LaunchCfg get_cfg(int op, int64_t n, int prec);
-int path_of(int op, int64_t n, int prec);  // the path of a call (CB_MIXED_F32D runs as configured)
+// The path of a call.  CB_OP_GRAD: of the gradient with the energy, whose
+// configuration is the energy's.
+int path_of(int op, int64_t n, int prec);
 void put_cfg(int op, int64_t n, int prec, LaunchCfg c);
 void drop_cfg(int op, int64_t n, int prec);
 bool valid_cfg(int op, const LaunchCfg& c);

@@ -9,14 +9,19 @@ FORCE_OPS = ("forces", "energy", "md_step", "md_run")
 
 
 @pytest.mark.parametrize("n,path", [
-    (1, "rows"), (6144, "rows"), (6145, "shares"), (32767, "shares"), (32768, "config"), (33500, "shares"),
+    (1, "rows"), (2400, "rows"), (2401, "rows"), (6144, "rows"), (6145, "shares"), (8192, "shares"), (8193, "shares"), (32767, "shares"), (32768, "config"), (33500, "shares"),
     (39900, "config"), (57344, "shares"), (57345, "config"), (262144, "config"), (262145, "bands"),
     (1 << 28, "bands")])
 def test_untuned(api, n, path):  # noqa: F811
     for op in FORCE_OPS:
         for prec in ("fp64", "mixed", "ieee", "fp32"):
             api.reset_config(op, n, prec)  # (an entry that another test left)
-            assert api.get_path(op, n, prec) == path
+            if op == "energy" and 2400 < n <= (8192 if prec == "fp32" else 6144):
+                assert api.get_path(op, n, prec) == "config"  # the potential alone
+            else:
+                assert api.get_path(op, n, prec) == path
+            if op == "energy":  # the gradient with the energy
+                assert api.get_path("grad", n, prec) == path
     assert api.get_path("forces", n, "mixed_f32d") == "config"
     assert api.get_path("hvp", n) == api.get_path("adjoint", n) == "config"
 
@@ -28,7 +33,7 @@ def test_forced_entries_run_as_set(api):  # noqa: F811
             api.reset_config(op, n, "fp64")
             api.reset_config(op, n, "mixed")
             untuned = api.get_path(op, n)
-            assert untuned != "config"
+            assert untuned != "config" or op == "energy"
             api.set_config(op, n, "fp64", **cfg)
             try:
                 assert api.get_path(op, n) == "config"
@@ -38,12 +43,32 @@ def test_forced_entries_run_as_set(api):  # noqa: F811
             assert api.get_path(op, n) == untuned
 
 
+def test_gradient_with_the_energy(api):  # noqa: F811
+    """Its configuration is the energy's: a forced one runs as set; its workspace
+    holds the shares that it takes where neither energy nor forces take them."""
+    for n, untuned in ((5000, "rows"), (7000, "shares")):
+        api.reset_config("energy", n)
+        assert api.get_path("grad", n) == untuned
+        api.set_config("energy", n, "fp64", p=1, wg=64, splits=8, algo=0)
+        assert api.get_path("grad", n) == "config"
+        api.reset_config("energy", n)
+    n = 7000
+    api.reset_config("forces", n, "fp32")
+    size = api.workspace_size("grad", n, prec="fp32")
+    assert (api.get_path("energy", n, "fp32"), api.get_path("grad", n, "fp32")) == ("config", "shares")
+    api.set_config("forces", n, "fp32", p=1, wg=64, splits=8, algo=0)
+    try:
+        assert api.workspace_size("grad", n, prec="fp32") == size
+    finally:
+        api.reset_config("forces", n, "fp32")
+
+
 def test_bad_arguments(api):  # noqa: F811
     L = api.lib()
     import ctypes as C
     out = C.c_int32(-1)
     assert L.cb_get_path(0, 100, 0, None) == api.CB_EINVAL
-    for op, n, prec in ((-1, 100, 0), (6, 100, 0), (7, 100, 0), (0, 0, 0), (0, (1 << 28) + 1, 0), (0, 100, 5), (0, 100, -1)):
+    for op, n, prec in ((-1, 100, 0), (6, 100, 0), (8, 100, 0), (0, 0, 0), (0, (1 << 28) + 1, 0), (0, 100, 5), (0, 100, -1)):
         assert L.cb_get_path(op, n, prec, C.byref(out)) == api.CB_EINVAL
     assert out.value == -1
 
