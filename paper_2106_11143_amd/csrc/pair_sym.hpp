@@ -90,6 +90,15 @@ __device__ __forceinline__ double sym_s(double r2, double q, const SeriesK& K) {
     return s;
 }
 
+// Whether a pair energy has to come from the refined r^-1 to be as accurate as
+// the direct kernel's: r^2 r^-3 has the error of r^-3, which where the series
+// ends after one term or none is five or three times that of r^-1 (energy of
+// 12001 ions, mixed: 7.2e-15 against 1.4e-15).
+template <int PREC>
+constexpr bool energy_y() {
+    return PREC == PREC_MIXED || PREC == PREC_FP32;
+}
+
 // Coordinates (and charges, when WQ) of a group of 4 j's.  The j index is
 // uniform over the wave, so these are scalar loads into SGPRs (32 of them;
 // two groups fit beside the rest of the kernel's scalar registers, eight j's
@@ -154,10 +163,11 @@ __device__ __forceinline__ bool tile_charges(const double (&qi)[P], const double
 // DIAG: the j's lie in the lane's own i-block (ion i0 + 64 p + lane of lane's
 // p-th): only the pairs j > i count, so the lane's ions are taken up to the
 // group's own sub-block of 64 (groups start at multiples of 4 from i0).
+// EY: the pair energies from r^-1 itself (energy_y).
 // POT: the pair energies too, into one sum per lane, pe += q_i q_j r^-1
 // (r^-1 when UNI), from r^-1 = r^2 r^-3: one or two operations per pair and
 // no reaction (each unordered pair's energy is counted once, here).
-template <int PREC, int P, int RED, bool TAIL, bool UNI, bool POT, bool DIAG = false>
+template <int PREC, int P, int RED, bool TAIL, bool UNI, bool POT, bool DIAG = false, bool EY = false>
 __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int live, int j0, int JL, double eps2,
                                           const double (&xi)[P], const double (&yi)[P], const double (&zi)[P],
                                           const double (&qi)[P], double (&ia)[P][3], double& pe, const SeriesK& K,
@@ -174,8 +184,9 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
             for (int u = 0; u < kGroupJ; ++u) {
                 const double dx = xi[p] - jd.x[u], dy = yi[p] - jd.y[u], dz = zi[p] - jd.z[u];
                 const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
-                double s = sym_s<PREC>(r2, UNI ? 1.0 : qi[p], K);
-                if ((TAIL && u >= live) || jg + u <= i0 + p * 64 + (int)(threadIdx.x & 63)) s = 0.0;
+                double s, y = 0.0;
+                inv_r<PREC, true, EY>(r2, UNI ? 1.0 : qi[p], K, s, y);
+                if ((TAIL && u >= live) || jg + u <= i0 + p * 64 + (int)(threadIdx.x & 63)) s = y = 0.0;
                 double sq = s;
                 if constexpr (!UNI) sq = s * jd.q[u];
                 ia[p][0] = __builtin_fma(dx, sq, ia[p][0]);
@@ -184,7 +195,8 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
                 jv[3 * u + 0] = __builtin_fma(dx, s, jv[3 * u + 0]);
                 jv[3 * u + 1] = __builtin_fma(dy, s, jv[3 * u + 1]);
                 jv[3 * u + 2] = __builtin_fma(dz, s, jv[3 * u + 2]);
-                if constexpr (POT) pe = __builtin_fma(r2, sq, pe);
+                if constexpr (EY) pe = UNI ? pe + y : __builtin_fma(y * qi[p], jd.q[UNI ? 0 : u], pe);
+                else if constexpr (POT) pe = __builtin_fma(r2, sq, pe);
             }
             asm volatile("" : "+v"(ia[p][0]), "+v"(ia[p][1]), "+v"(ia[p][2]));
         }
@@ -197,8 +209,9 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
         for (int p = 0; p < P; ++p) {
             const double dx = xi[p] - xj, dy = yi[p] - yj, dz = zi[p] - zj;
             const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
-            double s = sym_s<PREC>(r2, UNI ? 1.0 : qi[p], K);  // r^-3 (UNI) or q_i r^-3
-            if (TAIL && u >= live) s = 0.0;
+            double s, y = 0.0;  // r^-3 (UNI) or q_i r^-3; r^-1
+            inv_r<PREC, true, EY>(r2, UNI ? 1.0 : qi[p], K, s, y);
+            if (TAIL && u >= live) s = y = 0.0;
             double sq = s;
             if constexpr (!UNI) sq = s * jd.q[u];  // q_i q_j r^-3
             ia[p][0] = __builtin_fma(dx, sq, ia[p][0]);
@@ -207,7 +220,8 @@ __device__ __forceinline__ void sym_group(const JGroupT<!UNI>& jd, int jg, int l
             a0 = __builtin_fma(dx, s, a0);
             a1 = __builtin_fma(dy, s, a1);
             a2 = __builtin_fma(dz, s, a2);
-            if constexpr (POT) pe = __builtin_fma(r2, sq, pe);  // r^2 (q_i q_j) r^-3
+            if constexpr (EY) pe = UNI ? pe + y : __builtin_fma(y * qi[p], jd.q[UNI ? 0 : u], pe);
+            else if constexpr (POT) pe = __builtin_fma(r2, sq, pe);  // r^2 (q_i q_j) r^-3
         }
         jv[3 * u + 0] = a0;
         jv[3 * u + 1] = a1;

@@ -89,6 +89,7 @@ __device__ __forceinline__ void share_wave(const double* __restrict__ x, const d
                                            const double (&yi)[P], const double (&zi)[P], const double (&qi)[P],
                                            double qI, double qJ, double (&ia)[P][3], double& pe,
                                            double* __restrict__ red, double* __restrict__ Rt) {
+    constexpr bool EY = POT && energy_y<PREC>();
     const SeriesK K;
     const int jfull = j0 + (j1 - j0) / kGroupJ * kGroupJ;
     int jg = j0;
@@ -104,16 +105,16 @@ __device__ __forceinline__ void share_wave(const double* __restrict__ x, const d
             __builtin_amdgcn_sched_barrier(0);
             load_group<false>(nxt, jn < jfull ? jn : jg, 0, x, y, z, q);
             __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the arithmetic
-            sym_group<PREC, P, 1, false, UNI, POT, DIAG>(cur, jg, kGroupJ, jb, stride, eps2, xi, yi, zi, qi, ia, pe, K, qI,
-                                                         Rt, red, jb);
+            sym_group<PREC, P, 1, false, UNI, POT, DIAG, EY>(cur, jg, kGroupJ, jb, stride, eps2, xi, yi, zi, qi, ia, pe,
+                                                             K, qI, Rt, red, jb);
             cur = nxt;
         }
     }
     if (jg < j1) {  // the last, partial group: j's from j1 on are masked
         JGroupT<!UNI> tail;
         load_group<true>(tail, jg, j1 - jg - 1, x, y, z, q);
-        sym_group<PREC, P, 1, true, UNI, POT, DIAG>(tail, jg, j1 - jg, jb, stride, eps2, xi, yi, zi, qi, ia, pe, K, qI,
-                                                    Rt, red, jb);
+        sym_group<PREC, P, 1, true, UNI, POT, DIAG, EY>(tail, jg, j1 - jg, jb, stride, eps2, xi, yi, zi, qi, ia, pe, K,
+                                                        qI, Rt, red, jb);
     }
     if constexpr (UNI) {
         const double sc = qI * qJ;
