@@ -372,7 +372,8 @@ cb_status cb_get_config(int32_t op, int64_t n, int32_t prec, int32_t out[5]);
  *     fit the workspace.
  * An untuned entry of the forces, energy, md_step or md_run takes 1 up to 6144
  * ions, 2 up to 57344 (except where the reported tiles fill the chip evenly), 3
- * beyond 2^18; the energy alone 0 from 2401 to 6144 (CB_FP32_RSQ to 8192).  A tuned entry takes them where they were faster, an entry set
+ * beyond 2^18; the energy alone 0 from 2401 to 6144 (CB_MIXED and CB_FP32_RSQ
+ * to 8750).  A tuned entry takes them where they were faster, an entry set
  * by cb_set_config runs as set, and CB_MIXED_F32D always runs as reported.
  * CB_EINVAL for a NULL path_out, n outside [1, 2^28], an op that is none of
  * these (an ensemble's path follows the sizes of its runs, see md_run) or a

@@ -162,11 +162,14 @@ constexpr bool tiles_fit(int64_t n) {
 // The energy alone takes the potential-only all-pairs launches where rows
 // and shares, which sum the forces too, are slower (us per coulomb_energy, rows
 // or shares / those: FP64 2000 ions 10.0 / 12.9, 2500 15.3 / 15.2, 3000 16.9 /
-// 14.9, 4096 20.9 / 18.6, 5000 33.0 / 24.7, 6144 39.2 / 31.1, 6145 31.5 / 34.5,
-// 8192 42.2 / 44.5; the FP32 estimate 6144 31.4 / 24.7, 8192 36.2 / 33.4, 9000
-// 41.2 / 43.4).
+// 14.9, 4096 20.9 / 18.6, 5000 33.0 / 24.7, 6144 39.2 / 31.1, 6145 32.3 / 36.4,
+// 8192 41.8 / 44.6; mixed 7000 35.1 / 33.6, 8192 42.6 / 40.1, 8704 46.2 / 44.3,
+// 8800 46.5 / 49.3; the FP32 estimate 8193 37.4 / 33.3, 8704 39.7 / 37.0, 8800
+// 39.9 / 40.2).
+constexpr int64_t kPotAloneMinN = 2401;
+constexpr int64_t pot_alone_max(int prec) { return prec == CB_MIXED || prec == CB_FP32_RSQ ? 8750 : kRowsMaxN; }
 constexpr int default_path(int op, int64_t n, int prec) {
-    if (op == CB_OP_ENERGY && n > 2400 && n <= (prec == CB_FP32_RSQ ? 8192 : kRowsMaxN)) return PATH_CFG;
+    if (op == CB_OP_ENERGY && n >= kPotAloneMinN && n <= pot_alone_max(prec)) return PATH_CFG;
     if (op != CB_OP_FORCES && op != CB_OP_ENERGY && op != CB_OP_MD_STEP && op != CB_OP_MD_RUN) return PATH_CFG;
     return n <= kRowsMaxN ? PATH_ROWS : n <= kSharesMaxN && !tiles_fit(n) ? PATH_SHARES : n > kSymMaxN ? PATH_BANDS : PATH_CFG;
 }

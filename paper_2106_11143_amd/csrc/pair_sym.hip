@@ -74,11 +74,17 @@ static bool go_sym_pr(int P, int red, bool pot, int n, int JL, int64_t T, const 
 }
 
 // The row-group kernel (kSymRows i-blocks per workgroup), for P = 4, 6, 8.
-template <int PREC, bool POT>
+// EY: the energies from r^-1 itself (the bands, with kBandP ions per lane).
+template <int PREC, bool POT, bool EY>
 static bool go_sym_rows(int P, int n, int JL, int64_t T, const double* x, const double* y, const double* z,
                         const double* q, double eps2, const int2* tiles, double* Pi, double* R, double* Et,
                         hipStream_t st) {
     const unsigned g = (unsigned)T, b = 64 * kSymRows;
+    if constexpr (EY) {
+        if (P != kBandP) return false;
+        k_pair_sym_rows<PREC, kBandP, POT, true><<<g, b, 0, st>>>(n, x, y, z, q, eps2, JL, tiles, Pi, R, Et);
+        return true;
+    }
     switch (P) {
         case 4: k_pair_sym_rows<PREC, 4, POT><<<g, b, 0, st>>>(n, x, y, z, q, eps2, JL, tiles, Pi, R, Et); return true;
         case 6: k_pair_sym_rows<PREC, 6, POT><<<g, b, 0, st>>>(n, x, y, z, q, eps2, JL, tiles, Pi, R, Et); return true;
@@ -87,12 +93,13 @@ static bool go_sym_rows(int P, int n, int JL, int64_t T, const double* x, const 
     }
 }
 
-template <int PREC>
+template <int PREC, bool BAND>
 static bool go_sym_rows_p(int P, bool pot, int n, int JL, int64_t T, const double* x, const double* y,
                           const double* z, const double* q, double eps2, const int2* tiles, double* Pi, double* R,
                           double* Et, hipStream_t st) {
-    return pot ? go_sym_rows<PREC, true>(P, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st)
-               : go_sym_rows<PREC, false>(P, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+    constexpr bool EY = BAND && energy_y<PREC>();
+    return pot ? go_sym_rows<PREC, true, EY>(P, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st)
+               : go_sym_rows<PREC, false, false>(P, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
 }
 
 template <int PREC, bool BAND>
@@ -125,14 +132,15 @@ static cb_status finish(int prec, bool pot, unsigned nb, int n, int IB, int JL, 
     return check_launch("k_sym_finish");
 }
 
+template <bool BAND>
 static bool go_rows_prec(int prec, int P, bool pot, int n, int JL, int64_t T, const double* x, const double* y,
                          const double* z, const double* q, double eps2, const int2* tiles, double* Pi, double* R,
                          double* Et, hipStream_t st) {
     switch (prec) {
-        case PREC_FP64: return go_sym_rows_p<PREC_FP64>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
-        case PREC_MIXED: return go_sym_rows_p<PREC_MIXED>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
-        case PREC_IEEE: return go_sym_rows_p<PREC_IEEE>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
-        case PREC_FP32: return go_sym_rows_p<PREC_FP32>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_FP64: return go_sym_rows_p<PREC_FP64, BAND>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_MIXED: return go_sym_rows_p<PREC_MIXED, BAND>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_IEEE: return go_sym_rows_p<PREC_IEEE, BAND>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        case PREC_FP32: return go_sym_rows_p<PREC_FP32, BAND>(P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
         default: return false;
     }
 }
@@ -178,7 +186,7 @@ cb_status launch_pair_sym(int prec, const LaunchCfg& c, int n, const double* x, 
     base += al256(sizeof(double) * 3 * (size_t)JL * (T + 1));
     double* Et = pot ? reinterpret_cast<double*>(base) : nullptr;
     if (T > 0 && W > 1) {
-        const bool okk = go_rows_prec(prec, P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
+        const bool okk = go_rows_prec<false>(prec, P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st);
         if (!okk) return fail(CB_EINVAL, "launch_pair_sym: unsupported precision %d / p %d", prec, P);
         if ((rc = check_launch("k_pair_sym_rows"))) return rc;
     } else if (T > 0) {
@@ -240,7 +248,7 @@ cb_status launch_pair_sym_bands(int prec, int n, const double* x, const double* 
         cb_status rc = check_launch("k_sym_plan");
         if (rc) return rc;
         if (T > 0) {
-            if (!go_rows_prec(prec, P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st))
+            if (!go_rows_prec<true>(prec, P, pot, n, JL, T, x, y, z, q, eps2, tiles, Pi, R, Et, st))
                 return fail(CB_EINVAL, "launch_pair_sym_bands: unsupported precision %d", prec);
             if ((rc = check_launch("k_pair_sym_rows"))) return rc;
         }

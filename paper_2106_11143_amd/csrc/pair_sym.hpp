@@ -384,7 +384,7 @@ constexpr int kRowStride = kRowChunk + 1;  // doubles per component row of a sla
 // one); on return it holds the group at jnext (the next chunk's first, when
 // jnext >= 0), requested during this chunk's last whole group, so that only
 // two groups of j data are held in the loop.
-template <int PREC, int P, bool UNI, bool POT>
+template <int PREC, int P, bool UNI, bool POT, bool EY>
 __device__ __forceinline__ void sym_rows_chunk(const double* __restrict__ x, const double* __restrict__ y,
                                                const double* __restrict__ z, const double* __restrict__ q,
                                                double eps2, int cs, int ce, int jnext, JGroupT<!UNI>& cur,
@@ -399,22 +399,22 @@ __device__ __forceinline__ void sym_rows_chunk(const double* __restrict__ x, con
         const int jn = jg + kGroupJ;
         load_group<false>(nxt, jn < jfull ? jn : (jnext >= 0 ? jnext : jg), 0, x, y, z, q);
         __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the arithmetic
-        sym_group<PREC, P, 1, false, UNI, POT>(cur, jg, kGroupJ, cs, kRowStride, eps2, xi, yi, zi, qi, ia, pe, K, qI,
-                                               slabw, red);
+        sym_group<PREC, P, 1, false, UNI, POT, false, EY>(cur, jg, kGroupJ, cs, kRowStride, eps2, xi, yi, zi, qi, ia,
+                                                          pe, K, qI, slabw, red);
         cur = nxt;
     }
     if (jg < ce) {  // the last, partial group: j's from ce on are masked
         JGroupT<!UNI> tail;
         load_group<true>(tail, jg, ce - jg - 1, x, y, z, q);
-        sym_group<PREC, P, 1, true, UNI, POT>(tail, jg, ce - jg, cs, kRowStride, eps2, xi, yi, zi, qi, ia, pe, K, qI,
-                                              slabw, red);
+        sym_group<PREC, P, 1, true, UNI, POT, false, EY>(tail, jg, ce - jg, cs, kRowStride, eps2, xi, yi, zi, qi, ia,
+                                                         pe, K, qI, slabw, red);
     }
 }
 
 // The j loop of a row-group tile (the workgroup's 64-j chunks of [c0, c1),
 // each wave's pairs from j0 on) and the stores of its partials.  UNI is
 // uniform over the workgroup, so every wave meets every barrier.
-template <int PREC, int P, bool UNI, bool POT>
+template <int PREC, int P, bool UNI, bool POT, bool EY>
 __device__ __forceinline__ void sym_rows_tile(const double* __restrict__ x, const double* __restrict__ y,
                                               const double* __restrict__ z, const double* __restrict__ q,
                                               double eps2, int JL, int t, int w, int c0, int c1, int j0, bool live,
@@ -440,7 +440,7 @@ __device__ __forceinline__ void sym_rows_tile(const double* __restrict__ x, cons
         const int cn = cs + kRowChunk;  // the next chunk, when it holds a whole group
         const int jnext = cn + kGroupJ <= min(c1, cn + kRowChunk) ? cn : -1;
         if (live && cs >= j0)
-            sym_rows_chunk<PREC, P, UNI, POT>(x, y, z, q, eps2, cs, ce, jnext, cur, xi, yi, zi, qi, ia, pe,
+            sym_rows_chunk<PREC, P, UNI, POT, EY>(x, y, z, q, eps2, cs, ce, jnext, cur, xi, yi, zi, qi, ia, pe,
                                               UNI ? qI : 1.0, slabw, red);
         else
             for (int u = lane; u < 3 * kRowStride; u += 64) slabw[u] = 0.0;
@@ -469,7 +469,7 @@ __device__ __forceinline__ void sym_rows_tile(const double* __restrict__ x, cons
     }
 }
 
-template <int PREC, int P, bool POT>
+template <int PREC, int P, bool POT, bool EY = false>
 __global__ void __launch_bounds__(64 * kSymRows, (sym_waves<PREC, P, POT>()))
     k_pair_sym_rows(int n, const double* __restrict__ x, const double* __restrict__ y,
                     const double* __restrict__ z, const double* __restrict__ q, double eps2, int JL,
@@ -507,11 +507,11 @@ __global__ void __launch_bounds__(64 * kSymRows, (sym_waves<PREC, P, POT>()))
     if (!uni && lane == 0) nonuni = 1;
     __syncthreads();
     if (nonuni == 0)
-        sym_rows_tile<PREC, P, true, POT>(x, y, z, q, eps2, JL, t, w, c0, c1, j0, live, xi, yi, zi, qi, qI, qJ, slab,
-                                          red_buf[w], Pi, R, Et);
+        sym_rows_tile<PREC, P, true, POT, EY>(x, y, z, q, eps2, JL, t, w, c0, c1, j0, live, xi, yi, zi, qi, qI, qJ,
+                                              slab, red_buf[w], Pi, R, Et);
     else
-        sym_rows_tile<PREC, P, false, POT>(x, y, z, q, eps2, JL, t, w, c0, c1, j0, live, xi, yi, zi, qi, qI, qJ,
-                                           slab, red_buf[w], Pi, R, Et);
+        sym_rows_tile<PREC, P, false, POT, EY>(x, y, z, q, eps2, JL, t, w, c0, c1, j0, live, xi, yi, zi, qi, qI, qJ,
+                                               slab, red_buf[w], Pi, R, Et);
 }
 
 // Per ion k: direct pairs inside its own i-block, plus its i sums over the
@@ -552,6 +552,7 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
                                                                   const double* __restrict__ Et,
                                                                   double* __restrict__ F, double* __restrict__ phi,
                                                                   int G0, int G1) {
+    constexpr bool EY = POT && BAND && energy_y<PREC>();
     constexpr int NS = POT ? 10 : 9;  // per lane: direct 3, i sums 3, reactions 3 (+ the energy share)
     __shared__ double red[kFinishParts][NS][64];
     const int lane = threadIdx.x & 63;
@@ -574,8 +575,9 @@ __global__ void __launch_bounds__(64 * kFinishParts) k_sym_finish(int n, int IB,
     for (int j = lo; j < hi; ++j) {
         const double dx = xk - x[j], dy = yk - y[j], dz = zk - z[j];
         const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, eps2)));
-        double s = sym_s<PREC>(r2, q[j], K);  // q_j r^-3
-        if (POT) ps = j > kc ? __builtin_fma(r2, s, ps) : ps;  // q_j r^-1 of the later ions
+        double s, y = 0.0;
+        inv_r<PREC, true, EY>(r2, q[j], K, s, y);  // q_j r^-3 (and r^-1)
+        if (POT) ps = j > kc ? (EY ? __builtin_fma(q[j], y, ps) : __builtin_fma(r2, s, ps)) : ps;  // later ions
         if (j == kc) s = 0.0;
         d0 = __builtin_fma(dx, s, d0);
         d1 = __builtin_fma(dy, s, d1);

@@ -257,11 +257,15 @@ size_t share_ws_bytes(int64_t n, bool pot) {
     return pot ? std::max(f, share_carve(n, true, nullptr).bytes) : f;
 }
 
-template <int PREC, int P, bool POT>
+// Energies from r^-1 itself (energy_y) below the sizes at which the tiles are
+// configured, whose energies are r^2 r^-3 (mixed, 28000 ions: 322 us against 313).
+constexpr int kShareEyMaxN = 16383;
+
+template <int PREC, int P, bool POT, bool EY = false>
 static void go_share(int n, int N, const double* x, const double* y, const double* z, const double* q, double eps2,
                      const ShareWs& W, hipStream_t st) {
     const ShareCut c = share_cut(n, P, N);
-    k_share_pairs<PREC, P, POT><<<(unsigned)c.N, 64 * kShareWaves, 0, st>>>(c, x, y, z, q, eps2, W.Pi, W.R, W.Et);
+    k_share_pairs<PREC, P, POT, EY><<<(unsigned)c.N, 64 * kShareWaves, 0, st>>>(c, x, y, z, q, eps2, W.Pi, W.R, W.Et);
 }
 
 template <int PREC>
@@ -269,7 +273,11 @@ static void go_share_p(bool pot, int n, const double* x, const double* y, const 
                        double eps2, const ShareWs& W, hipStream_t st) {
     const ShareShape h = share_shape(n, pot);
     switch (h.P) {
-        case 4: pot ? go_share<PREC, 4, true>(n, h.N, x, y, z, q, eps2, W, st) : go_share<PREC, 4, false>(n, h.N, x, y, z, q, eps2, W, st); break;
+        case 4:
+            if (!pot) go_share<PREC, 4, false>(n, h.N, x, y, z, q, eps2, W, st);
+            else if (energy_y<PREC>() && n <= kShareEyMaxN) go_share<PREC, 4, true, energy_y<PREC>()>(n, h.N, x, y, z, q, eps2, W, st);
+            else go_share<PREC, 4, true>(n, h.N, x, y, z, q, eps2, W, st);
+            break;
         default: go_share<PREC, 8, false>(n, h.N, x, y, z, q, eps2, W, st); break;
     }
 }

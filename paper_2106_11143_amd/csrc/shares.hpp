@@ -81,15 +81,14 @@ __host__ __device__ __forceinline__ int unit_share(const ShareCut& c, int u) {
 
 // Pairs of one wave: j's [j0, j1) against the lane's P ions of the block at
 // jb, reactions to Rt[c * stride + j - jb], i sums into ia, pair energy into
-// pe.  DIAG: j's of the block itself (see sym_group).
-template <int PREC, int P, bool UNI, bool POT, bool DIAG>
+// pe.  DIAG: j's of the block itself, EY: energies from r^-1 (see sym_group).
+template <int PREC, int P, bool UNI, bool POT, bool DIAG, bool EY>
 __device__ __forceinline__ void share_wave(const double* __restrict__ x, const double* __restrict__ y,
                                            const double* __restrict__ z, const double* __restrict__ q, double eps2,
                                            int j0, int j1, int jb, int stride, const double (&xi)[P],
                                            const double (&yi)[P], const double (&zi)[P], const double (&qi)[P],
                                            double qI, double qJ, double (&ia)[P][3], double& pe,
                                            double* __restrict__ red, double* __restrict__ Rt) {
-    constexpr bool EY = POT && energy_y<PREC>();
     const SeriesK K;
     const int jfull = j0 + (j1 - j0) / kGroupJ * kGroupJ;
     int jg = j0;
@@ -137,7 +136,7 @@ union ShareLds {
 // Units [ua, ub) of the nu of row I of a run of n ions, by the workgroup: i
 // sums to Pt[3][IB], reactions to Rt[c nu kShareJ + j - I IB], the pair energy
 // (POT) to Et[0].
-template <int PREC, int P, bool POT>
+template <int PREC, int P, bool POT, bool EY>
 __device__ __forceinline__ void share_row(int n, const double* __restrict__ x, const double* __restrict__ y,
                                           const double* __restrict__ z, const double* __restrict__ q, double eps2,
                                           int I, int nu, int ua, int ub, ShareLds<P>& lds, double (&esum)[kShareWaves],
@@ -165,14 +164,14 @@ __device__ __forceinline__ void share_row(int n, const double* __restrict__ x, c
     if (j1 > jo) {
         double qI, qJ;
         if (tile_charges<P>(qi, q, jo, j1, qI, qJ))
-            share_wave<PREC, P, true, POT, false>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, qI, qJ, ia, pe,
+            share_wave<PREC, P, true, POT, false, EY>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, qI, qJ, ia, pe,
                                                   lds.red[w], Rt);
         else
-            share_wave<PREC, P, false, POT, false>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, 1.0, 1.0, ia,
+            share_wave<PREC, P, false, POT, false, EY>(x, y, z, q, eps2, jo, j1, ib, stride, xi, yi, zi, qi, 1.0, 1.0, ia,
                                                    pe, lds.red[w], Rt);
     }
     if (j0 < min(j1, jd))
-        share_wave<PREC, P, false, POT, true>(x, y, z, q, eps2, j0, min(j1, jd), ib, stride, xi, yi, zi, qi, 1.0, 1.0,
+        share_wave<PREC, P, false, POT, true, EY>(x, y, z, q, eps2, j0, min(j1, jd), ib, stride, xi, yi, zi, qi, 1.0, 1.0,
                                               ia, pe, lds.red[w], Rt);
     if constexpr (POT) {
 #pragma unroll
@@ -198,7 +197,7 @@ __device__ __forceinline__ void share_row(int n, const double* __restrict__ x, c
 // reactions of row I on its j's to R[3 row_unit(I) kShareJ + c row_units(I)
 // kShareJ + j - I IB], pair energies (POT) to Et[blockIdx.x + I].  cut: the
 // run's.
-template <int PREC, int P, bool POT>
+template <int PREC, int P, bool POT, bool EY>
 __global__ void __launch_bounds__(64 * kShareWaves, (sym_waves<PREC, P, POT>()))
     k_share_pairs(ShareCut cut, const double* __restrict__ x, const double* __restrict__ y,
                   const double* __restrict__ z, const double* __restrict__ q, double eps2, double* __restrict__ Pi,
@@ -221,7 +220,7 @@ __global__ void __launch_bounds__(64 * kShareWaves, (sym_waves<PREC, P, POT>()))
         const int u0 = row_unit(cut, I), nu = row_units(cut, I);
         const int ue = min(uend, u0 + nu);  // this share's units of the row: [u, ue)
         const size_t slot = (size_t)(g + I);
-        share_row<PREC, P, POT>(cut.n, x, y, z, q, eps2, I, nu, u - u0, ue - u0, lds, esum, Pi + slot * 3 * 64 * P,
+        share_row<PREC, P, POT, EY>(cut.n, x, y, z, q, eps2, I, nu, u - u0, ue - u0, lds, esum, Pi + slot * 3 * 64 * P,
                                 R + (size_t)3 * u0 * kShareJ, Et + slot);
         u = ue;
         if (u < uend) __syncthreads();  // the next row rewrites the buffers
@@ -253,7 +252,7 @@ __global__ void __launch_bounds__(64 * kShareWaves, (sym_waves<PREC, P, POT>()))
             const int u0 = ru.w + row_unit(cut, I), nu = row_units(cut, I);
             const int ue = min(uend, u0 + nu);
             const size_t slot = (size_t)(g + ru.z + I);
-            share_row<PREC, P, POT>(ru.y, x + ru.x, y + ru.x, z + ru.x, q + ru.x, eps2, I, nu, u - u0, ue - u0, lds,
+            share_row<PREC, P, POT, POT && energy_y<PREC>()>(ru.y, x + ru.x, y + ru.x, z + ru.x, q + ru.x, eps2, I, nu, u - u0, ue - u0, lds,
                                     esum, Pi + slot * 3 * 64 * P, R + (size_t)3 * u0 * kShareJ, Et + slot);
             u = ue;
             if (u < uend) __syncthreads();

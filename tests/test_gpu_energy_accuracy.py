@@ -29,7 +29,7 @@ def _inputs(n):
 
 @pytest.mark.parametrize("one_charge", [False, True])
 @pytest.mark.parametrize("prec", ["mixed", "fp32"])
-@pytest.mark.parametrize("n", [6145, 9000, 12001, 30000])
+@pytest.mark.parametrize("n", [6145, 9000, 12001, 16383])
 def test_one_run(api, n, prec, one_charge):  # noqa: F811
     from _gpu_util import dev, state_tensors
     st, (x, y, z), q, qd, m, trap = _inputs(n)
@@ -57,3 +57,14 @@ def test_ensemble(api, prec):  # noqa: F811
                              prec=prec)[:, 0, 1].cpu().numpy()
     want = _forced(api, "md_ensemble", int(offs[-1]), prec, run, p=4, wg=512, splits=1, algo=0)
     assert np.all(np.abs(run() - want) <= TOL * want)
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp32"])
+def test_bands(api, prec):  # noqa: F811
+    n = 262145
+    _, (x, y, z), _, q, m, trap = _inputs(n)
+    u = _forced(api, "energy", n, prec, lambda: api.coulomb_energy(x, y, z, q, 0.0, prec).item(), **DIRECT)
+    assert api.get_path("energy", n, prec) == "bands"
+    assert abs(api.coulomb_energy(x, y, z, q, 0.0, prec).item() - u) <= TOL * u
+    g = api.coulomb_trap_grad(x, y, z, q, prec=prec, energy=True)[1].item()
+    assert abs(g - u) <= TOL * u

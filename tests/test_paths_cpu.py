@@ -9,14 +9,14 @@ FORCE_OPS = ("forces", "energy", "md_step", "md_run")
 
 
 @pytest.mark.parametrize("n,path", [
-    (1, "rows"), (2400, "rows"), (2401, "rows"), (6144, "rows"), (6145, "shares"), (8192, "shares"), (8193, "shares"), (32767, "shares"), (32768, "config"), (33500, "shares"),
+    (1, "rows"), (2400, "rows"), (2401, "rows"), (6144, "rows"), (6145, "shares"), (8750, "shares"), (8751, "shares"), (32767, "shares"), (32768, "config"), (33500, "shares"),
     (39900, "config"), (57344, "shares"), (57345, "config"), (262144, "config"), (262145, "bands"),
     (1 << 28, "bands")])
 def test_untuned(api, n, path):  # noqa: F811
     for op in FORCE_OPS:
         for prec in ("fp64", "mixed", "ieee", "fp32"):
             api.reset_config(op, n, prec)  # (an entry that another test left)
-            if op == "energy" and 2400 < n <= (8192 if prec == "fp32" else 6144):
+            if op == "energy" and 2400 < n <= (8750 if prec in ("mixed", "fp32") else 6144):
                 assert api.get_path(op, n, prec) == "config"  # the potential alone
             else:
                 assert api.get_path(op, n, prec) == path
