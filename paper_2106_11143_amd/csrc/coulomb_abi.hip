@@ -127,11 +127,13 @@ LaunchCfg default_cfg(int op, int64_t n, int prec) {
         // Hessian-vector products by Newton's third law (hvp_sym.hpp): two
         // ions per lane (the four-vector pass keeps 24 vector components and
         // 24 sums per lane), up to four vectors per pass (wg), short segments
-        // for enough tiles, the shortest where the tiles are few (us on
-        // MI355X, segments of 64 / 128: one vector 4096 ions 39.6 / 55.6, 6000
-        // 55.4 / 66.2, 8192 70.7 / 74.0, 10000 90.5 / 102.6, 16384 196.0 / 194.7;
-        // eight 4096 97.7 / 113.9, 6500 193.0 / 213.8, 7500 247.7 / 262.2, 8192
-        // 281 / 276, 16384 1049 / 995)
+        // for enough tiles, the shortest where the tiles are few.  An entry
+        // serves any number of vectors, and eight set the line (us on MI355X,
+        // segments of 64 / 128, eight: 4096 ions 97.7 / 113.9, 6500 193.0 /
+        // 213.8, 7500 247.7 / 262.2, 8192 281 / 276, 16384 1049 / 995); one
+        // vector alone would take the short ones to about 16000 ions (4096 39.6
+        // / 55.6, 6000 55.4 / 66.2, 8192 70.7 / 74.0, 10000 90.5 / 102.6, 16384
+        // 196.0 / 194.7)
         c.algo = ALGO_SYM_LDS;
         c.wg = 4;
         c.p = 2;
