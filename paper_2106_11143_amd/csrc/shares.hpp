@@ -18,9 +18,9 @@
 // What bounds these sizes is how evenly the pairs share the chip: one-wave
 // tiles of 256 x 256 ions (42 us of a SIMD each) leave some SIMDs a tile more
 // than others, and the direct kernel evaluates every pair twice.  Equal
-// shares, all resident at once, end together: 12001 ions take 71.7 us per
-// evaluation (64 us of it the pair launch, 50 at the FP64 issue rate) against
-// 104 with the direct kernel, 20001 168 against 210 with tiles.
+// shares, all resident at once, end together: 12001 ions of one charge take
+// 71.7 us per evaluation (64 us of it the pair launch, 50 at the FP64 issue
+// rate) against 104 with the direct kernel, 20001 168 against 210 with tiles.
 #pragma once
 #include <hip/hip_runtime.h>
 
