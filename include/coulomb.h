@@ -214,10 +214,10 @@ cb_status coulomb_energy(int64_t n, const double* x, const double* y, const doub
  * (trap ignored).  gx, gy, gz: outputs (device, n doubles each), all three
  * or none; u_out: output (device, one double: U in J) or NULL; at least one
  * of the two is requested.  Outputs must not alias inputs or each other.
- * The gradient alone takes the configured force stage (CB_OP_FORCES); with
- * the energy, the all-pairs kernel evaluates forces and potentials in one
- * pass (CB_OP_ENERGY's configuration).  The trap terms are added in the same
- * element-wise pass that finishes the Coulomb sums.  Workspace:
+ * The gradient alone takes the forces' path and configuration (CB_OP_FORCES);
+ * with the energy, forces and pair energies come from one pass (the path of
+ * CB_OP_GRAD, CB_OP_ENERGY's configuration).  The trap terms are added in the
+ * same element-wise pass that finishes the Coulomb sums.  Workspace:
  * cb_workspace_size(CB_OP_GRAD, n, 1, 1, prec).  (Used by the autograd
  * functions and the minimiser, so that no trap arithmetic runs outside the
  * library.) */
