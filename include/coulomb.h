@@ -100,7 +100,8 @@ typedef enum {
 /* Operation codes for cb_workspace_size / cb_autotune.  CB_OP_MD_ENSEMBLE
  * only keys the launch configuration of md_run with nrun > 1
  * (cb_get_config / cb_set_config); its workspace is that of CB_OP_MD_RUN.
- * CB_OP_GRAD only sizes the workspace of coulomb_trap_grad (whose launches
+ * CB_OP_GRAD sizes the workspace of coulomb_trap_grad, and names its path with
+ * the energy in cb_get_path (its launches
  * follow the CB_OP_FORCES and CB_OP_ENERGY configurations). */
 typedef enum { CB_OP_FORCES = 0, CB_OP_ENERGY = 1, CB_OP_MD_STEP = 2, CB_OP_MD_RUN = 3,
                CB_OP_HVP = 4, CB_OP_ADJOINT = 5, CB_OP_MD_ENSEMBLE = 6, CB_OP_GRAD = 7 } cb_op;
